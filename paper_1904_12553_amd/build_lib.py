@@ -20,6 +20,7 @@ LIB = os.path.join(HERE, "libnplbm.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 SOURCES = ["step_kernel.hip", "step_kernel_mixed.hip", "step_kernel_remark1.hip",
+           "tile_kernel.hip", "tile_kernel_mixed.hip", "tile_kernel_remark1.hip",
            "step3d_kernel.hip", "aux_kernels.hip", "aux3d_kernels.hip", "nplbm_host.cpp",
            "nplbm_api.cpp", "nplbm_server.cpp"]
 

@@ -57,6 +57,9 @@ int64_t state_pitch(const nplbm_params *p);
 // step-kernel scheme (kSchemeCentral / kSchemeMixed / kSchemeRemark1) of a
 // validated parameter set
 int step_scheme(const nplbm_params *p);
+// geometry of one 2-D domain: step_geom, and the tile kernel where its rule
+// picks it
+StepGeom domain_geom(const nplbm_params *p);
 int resident_step_blocks(int N, int precision, int scheme);
 void build_strips(int nx, int ny, int dom, const StepGeom &geom, std::vector<StripDesc> &out,
                   int target = 0);

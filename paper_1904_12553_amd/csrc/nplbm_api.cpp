@@ -27,7 +27,7 @@ struct nplbm_domain {
   DomDesc *desc_dev = nullptr;
   StripDesc *strips_dev = nullptr;
   int nstrips = 0;
-  StepGeom geom{64, 60, 1};  // strip geometry of the step kernel
+  StepGeom geom{64, 60, 1, 2};  // strip geometry of the step kernel
   bool d3 = false;           // 3-D (D3Q15) domain
   int ty = 8;                // tile rows of the 3-D step kernel
   int64_t t = 0;
@@ -50,8 +50,8 @@ hipError_t launch_any_step(nplbm_domain *d, const StepArgs &a) {
   if (d->d3)
     return launch_step3(d->p.N, d->p.precision, d->ty, a, d->nstrips, d->p.nx, d->p.ny, d->p.nz,
                         d->stream);
-  return launch_step(d->p.N, d->p.precision, step_scheme(&d->p), d->geom.bw, a, d->nstrips,
-                     d->stream);
+  return launch_geom_step(d->p.N, d->p.precision, step_scheme(&d->p), d->geom, a, d->nstrips,
+                          &d->desc, d->stream);
 }
 
 // resident 3-D step workgroups on the device (0 if unknown)
@@ -269,7 +269,7 @@ int nplbm_create(const nplbm_params *p, void *stream, void *device_mem, size_t d
     if (const char *env = std::getenv("NPLBM_TARGET_BLOCKS")) target = std::atoi(env);
     build_tiles3(p->nx, p->ny, p->nz, 0, d->ty, target, strips);
   } else {
-    d->geom = step_geom(p->N, p->precision, step_scheme(p));
+    d->geom = domain_geom(p);
     build_strips(p->nx, p->ny, 0, d->geom, strips, single_domain_target(p));
   }
   xcd_order(strips);

@@ -479,6 +479,45 @@ StepGeom step_geom(int N, int precision, int scheme) {
   return g;
 }
 
+// Which kernel steps a 2-D domain.  The tile kernel while both copies of the
+// state, 2 x 10 N words per node, fit the 256 MB Infinity Cache: it reads the
+// halo of each tile again, which is cheap from there, and has a thread for
+// every node where marching strips leave compute units idle (100^2 N = 3 FP64
+// 7.0 against 45 us a step; 512^2: N = 3 FP64 23 against 67, N = 4 FP32 19
+// against 61, N = 8 FP32 41 against 64; at the edge, 768^2 N = 5 FP32, 236
+// MB, 46 against 78).  Beyond it the second read goes to HBM and the marching
+// kernel, which reads every population once, is faster (768^2 N = 3 FP64,
+// 283 MB, 64 against 76, but 1024^2 N = 3 FP64 116 against 100, N = 5 FP32
+// 119 against 100, 768^2 N = 4 FP64 96 against 87).
+// Tiles have 8 rows; 4 in FP64 with few phases while that still gives each
+// compute unit at most one tile (160^2 N = 3: 6.9 against 7.5 us; 180^2, two
+// tiles on some, 8.4 against 7.7; mixed N = 5 160^2 13.3 against 12.8; FP32
+// measures the same or slower with 4).
+// A set NPLBM_TX, NPLBM_BW, NPLBM_MIN_STRIP_H or NPLBM_TARGET_BLOCKS asks for
+// strips; NPLBM_TILE = 0 (strips), 4 or 8 overrides.
+StepGeom domain_geom(const nplbm_params *p) {
+  constexpr int64_t kCacheBytes = (int64_t)256 << 20;
+  constexpr int64_t kComputeUnits = 256;
+  const int scheme = step_scheme(p);
+  StepGeom g = step_geom(p->N, p->precision, scheme);
+  for (const char *e : {"NPLBM_TX", "NPLBM_BW", "NPLBM_MIN_STRIP_H", "NPLBM_TARGET_BLOCKS"})
+    if (std::getenv(e)) return g;
+  const int64_t rows = p->ny;
+  const int64_t state = 2 * 10 * (int64_t)p->N * (p->precision / 8) * state_pitch(p) * rows;
+  if (state <= kCacheBytes) {
+    const int64_t tiles4 = (int64_t)((p->nx + kTileWidth - 1) / kTileWidth) * ((rows + 3) / 4);
+    const bool few = p->precision == 64 && p->N <= (scheme == kSchemeCentral ? 5 : 3);
+    g.ty = few && tiles4 <= kComputeUnits ? 4 : 8;
+  }
+  if (const char *e = std::getenv("NPLBM_TILE")) {
+    const int t = std::atoi(e);
+    if (t == 0) g.ty = 0;
+    if (g.ty && t == 8) g.ty = 8;
+    if (g.ty && t == 4 && p->precision == 64 && p->N <= kTile4MaxN) g.ty = 4;
+  }
+  return g;
+}
+
 // Strip decomposition of one domain for the marching step kernel.  Strips
 // are geom.tx interior columns wide and H rows tall, H chosen so that the whole
 // launch has about `target` workgroups; neighbouring strip rows march in
@@ -486,6 +525,21 @@ StepGeom step_geom(int N, int precision, int scheme) {
 // time (both at their start or both at their end).
 void build_strips(int nx, int ny, int dom, const StepGeom &geom, std::vector<StripDesc> &out,
                   int target) {
+  if (geom.ty) {
+    for (int y = 0; y < ny; y += geom.ty)
+      for (int x = 0; x < nx; x += kTileWidth) {
+        StripDesc s;
+        std::memset(&s, 0, sizeof s);
+        s.dom = dom;
+        s.x0 = x;
+        s.x1 = std::min(nx, x + kTileWidth);
+        s.y0 = y;
+        s.y1 = std::min(ny, y + geom.ty);
+        s.dir = 1;
+        out.push_back(s);
+      }
+    return;
+  }
   const int kTX = geom.tx;
   const int unit = std::max(1, std::min(geom.unit, kTX));
   if (target <= 0) {

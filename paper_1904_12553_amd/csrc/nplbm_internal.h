@@ -19,7 +19,13 @@ struct StepGeom {
   int tx;    // maximum interior columns per strip (<= bw, or bw - 2 halo when the rows hold their halo)
   int unit;  // strip widths are multiples of this many columns (one cache line)
   int halo;  // halo columns on each side
+  int ty = 0;  // > 0: the domain is stepped by the tile kernel, tiles of this many rows
 };
+// Tiles of the tile kernel are kTileWidth columns (one 128-byte line in FP32)
+// by ty = 8 rows, or 4 (built for FP64 up to kTile4MaxN phases), one thread
+// per node.
+constexpr int kTileWidth = 32;
+constexpr int kTile4MaxN = 5;
 // Gradient schemes (nplbm_params.grad_scheme): central isotropic (eq:N31a)
 // or the isotropic mixed scheme of eq:N40 (sign of its two-hop term read as
 // negative).
@@ -134,11 +140,44 @@ struct StepArgs {
   int32_t pad_;
 };
 
+// What the tile kernel needs of one domain before its first load: source and
+// destination of each state group (0: h, 1: g, 2: prev) for this step, bytes
+// between planes and of one row block, lattice size and walls.
+struct TileDom {
+  const void *src[3];
+  void *dst[3];
+  uint32_t pb, rb[3];
+  int32_t nx, ny, wall;
+};
+// A launch over one domain (ntx > 0) gets the above and its tile grid by
+// value: ntx tiles a row, div = ceil(2^32 / ntx), ntile in all, per = ntile
+// over the 8 XCDs rounded up.  A launch over several domains (ntx = 0) reads
+// them from the strip table and the descriptors, two dependent loads later.
+struct TileArgs {
+  StepArgs s;
+  TileDom d;
+  uint32_t ntx, div, ntile, per;
+};
+
 // Launchers (defined in the .hip files).  All are asynchronous on `st`.
 hipError_t launch_step(int N, int precision, int scheme, int bw, const StepArgs &a,
                        int nblocks, hipStream_t st);
 // resident step-kernel workgroups per compute unit (0 if unknown)
 int step_blocks_per_cu(int N, int precision, int scheme, int bw);
+// one step by the tile kernel (tile_kernel.hip)
+hipError_t launch_tile(int N, int precision, int scheme, int ty, const TileArgs &a, int nblocks,
+                       hipStream_t st);
+hipError_t launch_tile_central(int N, int precision, int ty, const TileArgs &a, int nblocks,
+                               hipStream_t st);
+hipError_t launch_tile_mixed(int N, int precision, int ty, const TileArgs &a, int nblocks,
+                             hipStream_t st);
+hipError_t launch_tile_remark1(int N, int precision, int ty, const TileArgs &a, int nblocks,
+                               hipStream_t st);
+// One step by the kernel a geometry names.  one: the descriptor of the only
+// domain of the launch (its substep parity is a.substep's), or null where
+// the table holds several.
+hipError_t launch_geom_step(int N, int precision, int scheme, const StepGeom &g, const StepArgs &a,
+                            int nblocks, const DomDesc *one, hipStream_t st);
 // the same for one scheme (one translation unit each)
 hipError_t launch_step_central(int N, int precision, int bw, const StepArgs &a, int nblocks,
                                hipStream_t st);

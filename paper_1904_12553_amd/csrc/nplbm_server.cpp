@@ -80,6 +80,7 @@ struct nplbm_server {
   size_t strips_cap = 0;
   struct Group {
     int N, precision, scheme;
+    StepGeom geom;
     size_t off, count;
   };
   std::vector<Group> groups;
@@ -184,16 +185,23 @@ int rebuild(nplbm_server *s) {
   for (int sch : {kSchemeCentral, kSchemeMixed, kSchemeRemark1})
     for (int prec : {32, 64})
       for (int N = 2; N <= kMaxN; ++N) {
-        std::vector<StripDesc> g;
-        for (int slot = 0; slot < s->max_slots; ++slot) {
-          Req *r = s->slots[slot];
-          if (!r || r->p.N != N || r->p.precision != prec || step_scheme(&r->p) != sch) continue;
-          build_strips(r->p.nx, r->p.ny, slot, step_geom(N, prec, sch), g);
+        // one table per kernel: strips (ty = 0) and tiles of each height
+        for (int ty : {0, 4, 8}) {
+          std::vector<StripDesc> g;
+          StepGeom geom{};
+          for (int slot = 0; slot < s->max_slots; ++slot) {
+            Req *r = s->slots[slot];
+            if (!r || r->p.N != N || r->p.precision != prec || step_scheme(&r->p) != sch) continue;
+            const StepGeom rg = domain_geom(&r->p);
+            if (rg.ty != ty) continue;
+            geom = rg;
+            build_strips(r->p.nx, r->p.ny, slot, rg, g);
+          }
+          if (g.empty()) continue;
+          xcd_order(g);
+          s->groups.push_back({N, prec, sch, geom, all.size(), g.size()});
+          all.insert(all.end(), g.begin(), g.end());
         }
-        if (g.empty()) continue;
-        xcd_order(g);
-        s->groups.push_back({N, prec, sch, all.size(), g.size()});
-        all.insert(all.end(), g.begin(), g.end());
       }
   // the resident set is marked clean only once its graph exists: a failed
   // rebuild leaves it dirty, so the next pump tries again
@@ -255,9 +263,8 @@ int rebuild(nplbm_server *s) {
       a.strips = s->strips_dev + gr.off;
       a.doms = s->descs_dev;
       a.substep = q;
-      le = launch_step(gr.N, gr.precision, gr.scheme,
-                       step_geom(gr.N, gr.precision, gr.scheme).bw, a, (int)gr.count,
-                       nside ? s->side[gi % nside] : s->stream);
+      le = launch_geom_step(gr.N, gr.precision, gr.scheme, gr.geom, a, (int)gr.count,
+                            nullptr, nside ? s->side[gi % nside] : s->stream);
       if (le != hipSuccess) break;
     }
   for (int j = 0; j < nside && le == hipSuccess; ++j) {

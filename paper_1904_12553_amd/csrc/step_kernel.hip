@@ -57,35 +57,15 @@
 // population that would be pulled from outside is the node's own opposite
 // post-collision population), with mirror ghost rows for the phi and C
 // stencils next to a wall.
-#include "buffer_io.h"
-#include "lattice.h"
-#include "nplbm_internal.h"
+#include "node_math.h"
 
 namespace nplbm {
-
-// Address spaces: the descriptors and constants are read-only for the whole
-// launch and uniform per workgroup, so they are read through constant
-// (scalar-load) pointers.
-#define NPL_CONST __attribute__((address_space(4)))
 
 #ifndef NPL_WAVES_PER_EU
 #define NPL_KERNEL_ATTR
 #else
 #define NPL_KERNEL_ATTR __attribute__((amdgpu_waves_per_eu(NPL_WAVES_PER_EU)))
 #endif
-
-template <typename Real>
-__device__ __forceinline__ const NPL_CONST Consts<Real> *consts_of(const NPL_CONST DomDesc *d);
-template <>
-__device__ __forceinline__ const NPL_CONST Consts<double> *consts_of<double>(
-    const NPL_CONST DomDesc *d) {
-  return &d->cd;
-}
-template <>
-__device__ __forceinline__ const NPL_CONST Consts<float> *consts_of<float>(
-    const NPL_CONST DomDesc *d) {
-  return &d->cf;
-}
 
 // What one thread pulls for one node ahead of stage A and keeps until it
 // collides that node in stage C one iteration later.
@@ -151,17 +131,6 @@ __global__ void __launch_bounds__(kBW * kRows) NPL_KERNEL_ATTR k_step(StepArgs a
   const void *gs = D->g[par], *gd = D->g[par ^ 1];
   const void *pvs = D->prev[par], *pvd = D->prev[par ^ 1];
   const NPL_CONST Consts<Real> &K = *consts_of<Real>(D);
-  // The NS part of the collision (density, u, p, g^eq, G and the g update)
-  // is evaluated in FP64 arithmetic in both modes; the FP32 mode still
-  // stores FP32 populations.  Evaluated in FP32, the rounding of g^eq
-  // and of the update leaves each node's momentum off by a fraction of an
-  // ulp, in the same direction wherever the flow state repeats (inside a
-  // moving droplet), so droplets gain momentum steadily and interfaces drift
-  // as t^2: FP32 vs FP64 on the 512^2 N = 4 droplet collision went from
-  // 2.6e-5 to 7e-8 in c after 2000 steps (2e-3 to 7e-7 after 50000), for
-  // 2.7% more kernel time, most of which the evaluation per pair of
-  // opposite directions below won back.
-  using Acc = double;
   const NPL_CONST Consts<double> &KD = *consts_of<double>(D);
   const int nx = D->nx, ny = D->ny;
   const bool wall = D->wall != 0;
@@ -245,14 +214,6 @@ __global__ void __launch_bounds__(kBW * kRows) NPL_KERNEL_ATTR k_step(StepArgs a
     kk = b ? oppk(k) : k;
     co = b ? xcu : (cx == 1 ? xw : (cx == -1 ? xe : xcu));
     return b ? 0 : (cy == 1 ? 1 : (cy == -1 ? 2 : 0));
-  };
-
-  // lo part of phi_i: the stored deviation of h_0 plus the moving populations
-  auto lo_sum = [&](const Real (&h)[9]) {
-    Real lo = h[0];
-#pragma unroll
-    for (int k = 1; k < 9; ++k) lo += h[k];
-    return lo;
   };
 
   // ---- pull the CH populations and stored phi of march index m ----
@@ -448,36 +409,12 @@ __global__ void __launch_bounds__(kBW * kRows) NPL_KERNEL_ATTR k_step(StepArgs a
     const int sc = ring<kCR>(mB);
     // C at ring column x
     auto chem = [&](int x) {
-      Real phi[M], lap[M];
-#pragma unroll
-      for (int i = 0; i < M; ++i) {
-        const Real c = sphi[s0][i][x];
-        const Real e = sphi[s0][i][x + 1], w = sphi[s0][i][x - 1];
-        const Real n = sphi[s1][i][x], s = sphi[s2][i][x];
-        const Real ne = sphi[s1][i][x + 1], nw = sphi[s1][i][x - 1];
-        const Real se = sphi[s2][i][x + 1], sw = sphi[s2][i][x - 1];
-        // eq:N31b on D2Q9: (4 sum_axis + sum_diag - 20 zeta) / 6
-        lap[i] = (Real(4) * ((e + w) + (n + s)) + ((ne + nw) + (se + sw)) - Real(20) * c) *
-                 (Real(1) / Real(6));
-        phi[i] = c;
-      }
-      Real wv[N];
-#pragma unroll
-      for (int k = 0; k < N; ++k) {
-        Real ck = K.ca[k];
-#pragma unroll
-        for (int i = 0; i < M; ++i) ck += K.cA[k][i] * phi[i];
-        wv[k] = ck * (Real(1) - ck) * (Real(1) - Real(2) * ck);
-      }
-#pragma unroll
-      for (int i = 0; i < M; ++i) {
-        Real Ci = Real(0);
-#pragma unroll
-        for (int j = 0; j < M; ++j) Ci -= K.lam[i][j] * lap[j];
-#pragma unroll
-        for (int k = 0; k < N; ++k) Ci += K.KH[k][i] * wv[k];
-        sC[sc][i][x] = Ci;
-      }
+      chem_node<N, Real>(
+          K,
+          [&](int i, int dx, int dy) {
+            return sphi[dy == 0 ? s0 : (dy > 0 ? s1 : s2)][i][x + dx];
+          },
+          [&](int i, Real v) { sC[sc][i][x] = v; });
     };
     if constexpr (kIL) {
       // ring columns 1 .. ncol + 2 kHalo - 2: lane l takes l + 1, and the
@@ -505,12 +442,10 @@ __global__ void __launch_bounds__(kBW * kRows) NPL_KERNEL_ATTR k_step(StepArgs a
       Real Jx = Real(0), Jy = Real(0);
 #pragma unroll
       for (int i = 0; i < M; ++i) {
-        const Real e = sC[q0][i][x + 1], w = sC[q0][i][x - 1];
-        const Real n = sC[qN][i][x], s = sC[qS][i][x];
-        const Real ne = sC[qN][i][x + 1], nw = sC[qN][i][x - 1];
-        const Real se = sC[qS][i][x + 1], sw = sC[qS][i][x - 1];
-        const Real gx = (Real(4) * (e - w) + ((ne - nw) + (se - sw))) * (Real(1) / Real(12));
-        const Real gy = (Real(4) * (n - s) + ((ne + nw) - (se + sw))) * (Real(1) / Real(12));
+        Real gx, gy;
+        grad_central<Real>(
+            [&](int dx, int dy) { return sC[dy == 0 ? q0 : (dy > 0 ? qN : qS)][i][x + dx]; }, gx,
+            gy);
         Jx += K.Jc[i] * gx;
         Jy += K.Jc[i] * gy;
       }
@@ -535,34 +470,8 @@ __global__ void __launch_bounds__(kBW * kRows) NPL_KERNEL_ATTR k_step(StepArgs a
   // the NS arithmetic (with them in stage C, three register sets spilled
   // 172 B per lane at N = 5 in FP32).  The sums are the ones stage C forms
   // for the other schemes, over the phases in the same order.
-  struct PhiGrad {
-    Real grs, gys, Fxs, Fys;  // sum_i rA_i grad phi_i, sum_i C_i grad phi_i
-  };
-  auto grad2 = [&](const Real (*f)[M][kRW], int r0, int rN, int rS, int rN2, int rS2, int i,
-                   Real &gx, Real &gy) {
-    // eq:N40 summed over the D2Q9 directions.  Per direction c the
-    // difference is -z(x+2c) + 5 z(x+c) - 3 z(x) - z(x-c); with w_c, c_x
-    // and 1/(4 c_s^2) the z(x) terms cancel and opposite directions pair:
-    //   d/dx = [24 (E - W) - 4 (E2 - W2) + 6 (NE - NW + SE - SW)
-    //           - (NE2 - NW2 + SE2 - SW2)] / 48
-    // (E2 = z(x+2, y), NE2 = z(x+2, y+2), ...), and likewise d/dy.
-    const Real e = f[r0][i][pos + 1], w = f[r0][i][pos - 1];
-    const Real e2 = f[r0][i][pos + 2], w2 = f[r0][i][pos - 2];
-    const Real n = f[rN][i][pos], s = f[rS][i][pos];
-    const Real n2 = f[rN2][i][pos], s2 = f[rS2][i][pos];
-    const Real ne = f[rN][i][pos + 1], nw = f[rN][i][pos - 1];
-    const Real se = f[rS][i][pos + 1], sw = f[rS][i][pos - 1];
-    const Real ne2 = f[rN2][i][pos + 2], nw2 = f[rN2][i][pos - 2];
-    const Real se2 = f[rS2][i][pos + 2], sw2 = f[rS2][i][pos - 2];
-    gx = (Real(24) * (e - w) - Real(4) * (e2 - w2) + Real(6) * ((ne - nw) + (se - sw)) -
-          ((ne2 - nw2) + (se2 - sw2))) *
-         (Real(1) / Real(48));
-    gy = (Real(24) * (n - s) - Real(4) * (n2 - s2) + Real(6) * ((ne + nw) - (se + sw)) -
-          ((ne2 + nw2) - (se2 + sw2))) *
-         (Real(1) / Real(48));
-  };
   auto stageG = [&](int mC) {
-    PhiGrad G{Real(0), Real(0), Real(0), Real(0)};
+    GradSums<Real> G{};
     if constexpr (kTwoHop) {
       if (!interior || mC < 0 || mC >= H) return G;
       const int p0 = ring<kPR>(mC), pN = ring<kPR>(mC + dir), pS = ring<kPR>(mC - dir);
@@ -571,7 +480,12 @@ __global__ void __launch_bounds__(kBW * kRows) NPL_KERNEL_ATTR k_step(StepArgs a
 #pragma unroll
       for (int i = 0; i < M; ++i) {
         Real gx, gy;
-        grad2(sphi, p0, pN, pS, pN2, pS2, i, gx, gy);
+        grad_two_hop<Real>(
+            [&](int dx, int dy) {
+              const int r = dy == 0 ? p0 : dy == 1 ? pN : dy == -1 ? pS : dy == 2 ? pN2 : pS2;
+              return sphi[r][i][pos + dx];
+            },
+            gx, gy);
         const Real Ci = sC[q0][i][pos];
         G.grs += K.rA[i] * gx;
         G.gys += K.rA[i] * gy;
@@ -584,69 +498,57 @@ __global__ void __launch_bounds__(kBW * kRows) NPL_KERNEL_ATTR k_step(StepArgs a
 
   // ---- stage C: collide march index mC with what was pulled for it ----
   auto stageC = [&](int mC, const Pulled<M, Real> &P, const PulledNS<Real> &Q,
-                    const PhiGrad &G) {
+                    GradSums<Real> G) {
     if (!interior || mC < 0 || mC >= H) return;
     const int yp = row_of(mC);
     const int p0 = ring<kPR>(mC), pN = ring<kPR>(mC + dir), pS = ring<kPR>(mC - dir);
     const int q0 = ring<kCR>(mC), qN = ring<kCR>(mC + dir), qS = ring<kCR>(mC - dir);
-    Real phi[M], Cv[M], gpx[M], gpy[M], gCx[M], gCy[M];
+    Real phi[M], Cv[M];
+#pragma unroll
+    for (int i = 0; i < M; ++i) {
+      phi[i] = sphi[p0][i][pos];
+      Cv[i] = sC[q0][i][pos];
+    }
     if constexpr (!kTwoHop) {
-      // eq:N31a on D2Q9: d/dx = [4 (E - W) + (NE - NW + SE - SW)] / 12
-      auto grad = [&](const Real (*f)[M][kRW], int r0, int rN, int rS, int i, Real &gx,
-                      Real &gy) {
-        const Real e = f[r0][i][pos + 1], w = f[r0][i][pos - 1];
-        const Real n = f[rN][i][pos], s = f[rS][i][pos];
-        const Real ne = f[rN][i][pos + 1], nw = f[rN][i][pos - 1];
-        const Real se = f[rS][i][pos + 1], sw = f[rS][i][pos - 1];
-        gx = (Real(4) * (e - w) + ((ne - nw) + (se - sw))) * (Real(1) / Real(12));
-        gy = (Real(4) * (n - s) + ((ne + nw) - (se + sw))) * (Real(1) / Real(12));
-      };
 #pragma unroll
       for (int i = 0; i < M; ++i) {
-        phi[i] = sphi[p0][i][pos];
-        Cv[i] = sC[q0][i][pos];
-        grad(sphi, p0, pN, pS, i, gpx[i], gpy[i]);
-        if constexpr (!kR1) grad(sC, q0, qN, qS, i, gCx[i], gCy[i]);
+        Real gx, gy;
+        grad_central<Real>(
+            [&](int dx, int dy) {
+              return sphi[dy == 0 ? p0 : (dy > 0 ? pN : pS)][i][pos + dx];
+            },
+            gx, gy);
+        G.grs += K.rA[i] * gx;
+        G.gys += K.rA[i] * gy;
+        G.Fxs += Cv[i] * gx;
+        G.Fys += Cv[i] * gy;
+        if constexpr (!kR1) {
+          grad_central<Real>(
+              [&](int dx, int dy) {
+                return sC[dy == 0 ? q0 : (dy > 0 ? qN : qS)][i][pos + dx];
+              },
+              gx, gy);
+          G.Jxs += K.Jc[i] * gx;
+          G.Jys += K.Jc[i] * gy;
+        }
       }
     } else {
       // the C gradients (eq:N40) here; the phi gradients came from stage G
       const int qN2 = ring<kCR>(mC + 2 * dir), qS2 = ring<kCR>(mC - 2 * dir);
 #pragma unroll
       for (int i = 0; i < M; ++i) {
-        phi[i] = sphi[p0][i][pos];
-        Cv[i] = sC[q0][i][pos];
-        grad2(sC, q0, qN, qS, qN2, qS2, i, gCx[i], gCy[i]);
+        Real gx, gy;
+        grad_two_hop<Real>(
+            [&](int dx, int dy) {
+              const int r = dy == 0 ? q0 : dy == 1 ? qN : dy == -1 ? qS : dy == 2 ? qN2 : qS2;
+              return sC[r][i][pos + dx];
+            },
+            gx, gy);
+        G.Jxs += K.Jc[i] * gx;
+        G.Jys += K.Jc[i] * gy;
       }
     }
-    // density, relaxation, forces
-    // (the sums over phases of the gradient terms stay in the state type:
-    // measured, FP64 there changes nothing)
-    Acc rho = KD.ra;
-    Real grs = Real(0), gys = Real(0), Fxs = Real(0), Fys = Real(0), Jxs = Real(0), Jys = Real(0);
-#pragma unroll
-    for (int i = 0; i < M; ++i) {
-      rho += KD.rA[i] * phi[i];
-      if constexpr (!kTwoHop) {
-        grs += K.rA[i] * gpx[i];
-        gys += K.rA[i] * gpy[i];
-        Fxs += Cv[i] * gpx[i];
-        Fys += Cv[i] * gpy[i];
-      }
-      if constexpr (!kR1) {
-        Jxs += K.Jc[i] * gCx[i];
-        Jys += K.Jc[i] * gCy[i];
-      }
-    }
-    if constexpr (kTwoHop) {
-      grs = G.grs;
-      gys = G.gys;
-      Fxs = G.Fxs;
-      Fys = G.Fys;
-    }
-    const Acc grx = grs, gry = gys, Jx = Jxs, Jy = Jys;
-    Acc Fx = Fxs, Fy = Fys;
-    Fx += rho * KD.gx;
-    Fy += rho * KD.gy;
+    Acc divx = Acc(0), divy = Acc(0);
     if constexpr (kR1) {
       // Remark 1: F -= div(J~ u), (div)_x = d_x q0 + d_y q1,
       // (div)_y = d_x q2 + d_y q3, eq:N31a on the product ring; a row
@@ -658,122 +560,22 @@ __global__ void __launch_bounds__(kBW * kRows) NPL_KERNEL_ATTR k_step(StepArgs a
       const int s0 = ring<kQR>(mC);
       const int sN = ghost(mC + dir) ? s0 : ring<kQR>(mC + dir);
       const int sS = ghost(mC - dir) ? s0 : ring<kQR>(mC - dir);
-      auto ddx = [&](int c) {
-        return (Acc(4) * (sQ[s0][c][pos + 1] - sQ[s0][c][pos - 1]) +
-                ((sQ[sN][c][pos + 1] - sQ[sN][c][pos - 1]) +
-                 (sQ[sS][c][pos + 1] - sQ[sS][c][pos - 1]))) *
-               (Acc(1) / Acc(12));
+      auto q = [&](int c) {
+        return [&, c](int dx, int dy) {
+          return sQ[dy == 0 ? s0 : (dy > 0 ? sN : sS)][c][pos + dx];
+        };
       };
-      auto ddy = [&](int c) {
-        return (Acc(4) * (sQ[sN][c][pos] - sQ[sS][c][pos]) +
-                ((sQ[sN][c][pos + 1] + sQ[sN][c][pos - 1]) -
-                 (sQ[sS][c][pos + 1] + sQ[sS][c][pos - 1]))) *
-               (Acc(1) / Acc(12));
-      };
-      Fx -= ddx(0) + ddy(1);
-      Fy -= ddx(2) + ddy(3);
+      divx = ddx_central(q(0)) + ddy_central(q(1));
+      divy = ddx_central(q(2)) + ddy_central(q(3));
     }
-    Acc itau, srcg, theta;
-    if (KD.const_tau) {
-      itau = KD.itau_g;
-      srcg = KD.src_g;
-      theta = KD.theta_g;
-    } else {
-      Acc mu = KD.ma;
-#pragma unroll
-      for (int i = 0; i < M; ++i) mu += KD.mA[i] * phi[i];
-      // tau_g = 1/2 + mu / (rho c_s^2)  (eq:N21_1 with nu = mu / rho)
-      const Acc tm = Acc(3) * mu / rho;  // tau_g - 1/2
-      itau = Acc(1) / (Acc(0.5) + tm);
-      srcg = Acc(1) - Acc(0.5) * itau;
-      theta = Acc(1) / tm;
-    }
-    Acc g[9];
-#pragma unroll
-    for (int k = 1; k < 9; ++k) g[k] = Q.g[k];
-    const Acc irho = Acc(1) / rho;
-    const Acc mx = (g[1] - g[3]) + (g[5] - g[6]) + (g[8] - g[7]);
-    const Acc my = (g[2] - g[4]) + (g[5] + g[6]) - (g[7] + g[8]);
-    const Acc ux = (mx + Acc(0.5) * Fx) * irho;  // eq:N22_1
-    const Acc uy = (my + Acc(0.5) * Fy) * irho;
-    Acc sumg = g[1];
-#pragma unroll
-    for (int k = 2; k < 9; ++k) sumg += g[k];
-    const Acc usq = ux * ux + uy * uy;
-    const Acc udr = ux * grx + uy * gry;
-    // eq:N23: p = c_s^2 / (1 - w_0) [sum_{k!=0} g_k + u.grad(rho)/2 + rho s_0(u)]
-    const Acc p = Acc(0.6) * (sumg + Acc(0.5) * udr - Acc(2) / Acc(3) * rho * usq);
-    const Acc uF = ux * Fx + uy * Fy;
-    const Acc Ju = Jx * ux + Jy * uy;
-    // isotropic part of eq:N20_1: u.grad(rho) - tr(T) / (2 c_s^2)
-    const Acc gbase =
-        udr - Acc(1.5) * (Acc(2) * uF + Acc(2) / Acc(3) * udr + (kR1 ? Acc(0) : theta * Ju));
     const Rsrc wh = row_rsrc(hd, rbh, yp), wg = row_rsrc(gd, rbg, yp),
                wp = row_rsrc(pvd, rbp, yp);
-    // g* = (1 - 1/tau) g + g^eq / tau + (1 - 1/(2 tau)) G (eq:24), with
-    // g^eq (eq:25) and G (eq:N20_1) split into the parts even and odd in
-    // c_k: opposite directions share the even part and negate the odd one,
-    // so each pair is evaluated once
-    const Acc keep = Acc(1) - itau;
-    const Acc e0 = Acc(3) * p - Acc(1.5) * rho * usq;
-#pragma unroll
-    for (int k = 1; k < 9; ++k) {
-      if (oppk(k) < k) continue;
-      const int ko = oppk(k);
-      const Acc cx = Acc(cxk(k)), cy = Acc(cyk(k));
-      const Acc w = wk<Acc>(k);
-      const Acc cu = cx * ux + cy * uy;
-      const Acc cF = cx * Fx + cy * Fy;
-      const Acc cr = cx * grx + cy * gry;
-      const Acc cJ = cx * Jx + cy * Jy;
-      const Acc ev =
-          w * (itau * (e0 + Acc(4.5) * rho * cu * cu) +
-               srcg * (gbase + Acc(4.5) * cu *
-                                   (Acc(2) * cF + Acc(2) / Acc(3) * cr +
-                                    (kR1 ? Acc(0) : theta * cJ))));
-      const Acc od = w * Acc(3) * (itau * rho * cu + srcg * cF);
-      bst<Real, kNTS>(wg, xcu, (uint32_t)(k - 1) * pb, keep * g[k] + ev + od);
-      bst<Real, kNTS>(wg, xcu, (uint32_t)(ko - 1) * pb, keep * g[ko] + ev - od);
-    }
-    // CH collisions
-    const Real pux = Q.pu[0], puy = Q.pu[1];
-#pragma unroll
-    for (int i = 0; i < M; ++i) {
-      const Real pp = P.hi[i];  // phi_i of the previous step (stored)
-      const Real psx = phi[i] * ux, psy = phi[i] * uy;
-      const Real dx = psx - pp * pux, dy = psy - pp * puy;  // eq:N27
-      const Real ec = K.eta_i[i] * Cv[i];
-      const Real it = K.itau_i[i], sr = K.src_i[i];
-      // h* = (1 - 1/tau_i) h + h^eq / tau_i + R_k with h^eq (eq:N25) and R_k
-      // (eq:N26) split into the parts even and odd in c_k, per pair of
-      // opposite directions
-      const Real keep = Real(1) - it;
-      Real hsum = Real(0);
-#pragma unroll
-      for (int k = 1; k < 9; ++k) {
-        if (oppk(k) < k) continue;
-        const int ko = oppk(k);
-        const Real cx = Real(cxk(k)), cy = Real(cyk(k));
-        const Real w = wk<Real>(k);
-        const Real ev = it * w * ec;
-        const Real od = w * Real(3) * (it * (cx * psx + cy * psy) + sr * (cx * dx + cy * dy));
-        const Real hn = keep * P.h[i][k] + ev + od;
-        const Real ho = keep * P.h[i][ko] + ev - od;
-        hsum += hn + ho;
-        bst<Real, kNTS>(wh, xcu, (uint32_t)(i * 9 + k) * pb, hn);
-        bst<Real, kNTS>(wh, xcu, (uint32_t)(i * 9 + ko) * pb, ho);
-      }
-      // phi_i = hi + lo exactly; phi[i] = fl(hi + lo) is stored as the new
-      // previous phi and the k = 0 slot keeps (hi + lo - phi[i]) - sum h_k
-      // (error-free two-sum for the rounding part).
-      const Real lo = lo_sum(P.h[i]);
-      const Real bb = phi[i] - pp;
-      const Real err = (pp - (phi[i] - bb)) + (lo - bb);
-      bst<Real, kNTS>(wh, xcu, (uint32_t)(i * 9) * pb, err - hsum);
-      bst<Real, kNTS>(wp, xcu, (uint32_t)i * pb, phi[i]);
-    }
-    bst<Real, kNTS>(wp, xcu, (uint32_t)M * pb, ux);
-    bst<Real, kNTS>(wp, xcu, (uint32_t)(M + 1) * pb, uy);
+    collide_node<N, Real, kR1>(
+        K, KD, phi, Cv, G, divx, divy, [&](int i) -> const Real(&)[9] { return P.h[i]; }, P.hi, Q.g,
+        Q.pu,
+        [&](int plane, Real v) { bst<Real, kNTS>(wg, xcu, (uint32_t)plane * pb, v); },
+        [&](int plane, Real v) { bst<Real, kNTS>(wh, xcu, (uint32_t)plane * pb, v); },
+        [&](int plane, Real v) { bst<Real, kNTS>(wp, xcu, (uint32_t)plane * pb, v); });
   };
 
   // March over iterations j (march index mA = 2j - kRamp + row).  Each does
@@ -819,7 +621,7 @@ __global__ void __launch_bounds__(kBW * kRows) NPL_KERNEL_ATTR k_step(StepArgs a
       stageA(mA, buf);
       __syncthreads();
       pull_ns(mA - kLag, ns);
-      const PhiGrad g1 = stageG(mA - kLag);
+      const GradSums<Real> g1 = stageG(mA - kLag);
       pull_ch(mA - kLag, buf);
       stageB(mA - 1);
       __syncthreads();
@@ -840,7 +642,7 @@ __global__ void __launch_bounds__(kBW * kRows) NPL_KERNEL_ATTR k_step(StepArgs a
       halo_phi(mA, hv);
       __syncthreads();
       pull_ns(mA - kLag, ns);
-      const PhiGrad g1 = stageG(mA - kLag);
+      const GradSums<Real> g1 = stageG(mA - kLag);
       stageB(mA - 1);
       __syncthreads();
       if constexpr (kR1) {
@@ -864,7 +666,7 @@ __global__ void __launch_bounds__(kBW * kRows) NPL_KERNEL_ATTR k_step(StepArgs a
       halo_phi(mA, hv);
       __syncthreads();
       pull_ns(mA - kLag, ns);
-      const PhiGrad g1 = stageG(mA - kLag);
+      const GradSums<Real> g1 = stageG(mA - kLag);
       pull_ch(mA + 2, next);
       halo_pull(mA + 2, hv);
       stageB(mA - 1);
@@ -889,7 +691,7 @@ __global__ void __launch_bounds__(kBW * kRows) NPL_KERNEL_ATTR k_step(StepArgs a
       halo_phi(mA, hv);
       __syncthreads();
       pull_ns(mA - kLag, ns);
-      const PhiGrad g1 = stageG(mA - kLag);
+      const GradSums<Real> g1 = stageG(mA - kLag);
       stageB(mA - 1);
       __syncthreads();
       stageC(mA - kLag, held, ns, g1);

@@ -1,0 +1,470 @@
+// tile_kernel.hip -- the time step of a 2-D domain (D2Q9) by tiles, for
+// lattices too small to fill the chip with marching strips (gfx950).
+//
+// The marching kernel (step_kernel.hip) reads every population once but
+// walks its strip two rows at a time, and one iteration is a serial chain of
+// loads, LDS stages and two barriers (about 4 us with few workgroups on the
+// chip), so a small lattice -- a few strips of 16 rows and more -- leaves
+// most compute units idle and is bound by that chain: 44 us a step on the
+// 100 x 100 N = 3 FP64 droplet, seven workgroups.  Here one launch gives
+// every node a thread of its own and goes through the chain once: a
+// workgroup owns a tile of 32 x TY nodes (one cache line of FP32 wide) and
+//
+//   stage A: each thread pulls the CH populations of its node (kept in
+//            registers for the collision) and the workgroup shares out the
+//            halo nodes around the tile, one (node, phase) pair per thread,
+//            so all loads of the step, the NS populations too, are in flight
+//            together; phi_i (eq:N28) -> LDS;
+//   stage B: chemical potentials (eq:N18, eq:N17 with eq:N31b) on the tile
+//            and the ring the gradients need -> LDS;
+//   stage J: Remark 1 only, the products J~_b u_a on the tile and a ring
+//            of one -> LDS;
+//   stage C: gradients, forces, both collisions, store.
+//
+// The halo populations are pulled again by the neighbouring tiles (1.7 times
+// the CH reads at TY = 8, 2.3 at TY = 4), from L2 or MALL at the sizes this
+// kernel runs at.  Every node's arithmetic is that of node_math.h, as in the
+// marching kernel, and a halo phi is summed in the order its own tile sums
+// it, so the state does not depend on which kernel or tile advanced a node.
+#include "node_math.h"
+
+namespace nplbm {
+
+// This translation unit instantiates the kernel for one scheme, NPL_GS (0
+// central, 1 mixed, 2 Remark 1), as step_kernel.hip does.
+#ifndef NPL_GS
+#define NPL_GS 0
+#endif
+
+namespace {
+
+constexpr int kTW = kTileWidth;  // columns of a tile
+
+// One word of each 64-byte line of the constants in use, kept alive by an
+// empty asm.
+template <int N, typename Real>
+__device__ __forceinline__ void touch_consts(const NPL_CONST Consts<Real> &K) {
+  constexpr int kLine = 64 / (int)sizeof(Real);
+  Real s = K.gx;
+  auto range = [&](const NPL_CONST Real *p, int n) {
+#pragma unroll
+    for (int i = 0; i < n + kLine - 1; i += kLine) s += p[i < n ? i : n - 1];
+  };
+  range(&K.ca[0], N);
+  range(&K.cA[0][0], (N - 1) * kMaxM + N - 1);
+  range(&K.ra, 2);
+  range(&K.rA[0], N - 1);
+  range(&K.lam[0][0], (N - 2) * kMaxM + N - 1);
+  range(&K.KH[0][0], (N - 1) * kMaxM + N - 1);
+  range(&K.Jc[0], 4 * kMaxM);
+  asm volatile("" ::"v"(s));
+}
+
+template <int N, typename Real, int TY, int kGS>
+__global__ void __launch_bounds__(kTW * TY) k_tile(TileArgs a) {
+  constexpr int M = N - 1;
+  constexpr bool kTwoHop = kGS == kSchemeMixed;  // eq:N40 first derivatives
+  constexpr bool kR1 = kGS == kSchemeRemark1;    // Remark 1 force distribution
+  constexpr int kNT = kTW * TY;
+  // Many phases in FP64: the own populations, three and more rounds of halo
+  // items and the NS ones together exceed the registers of two waves per
+  // SIMD.  These variants finish the own phi before the halo and take the
+  // halo three items at a time (512^2 FP64 Remark 1 N = 6: 63 us a step
+  // against 78; up to N = 5 it costs a few percent).
+  constexpr bool kGrouped = sizeof(Real) == 8 && M * 8 + (kGS == kSchemeRemark1 ? 8 : 0) >= 48;
+  // phi is needed kHalo nodes around a node that collides, C kHalo - 1
+  constexpr int kHalo = kGS ? 3 : 2, kRing = kHalo - 1;
+  constexpr int kPW = kTW + 2 * kHalo, kPR = TY + 2 * kHalo;
+  constexpr int kCW = kTW + 2 * kRing, kCR = TY + 2 * kRing;
+  constexpr int kQW = kTW + 2, kQR = TY + 2;
+  __shared__ Real sphi[M][kPR][kPW];
+  __shared__ Real sC[M][kCR][kCW];
+  __shared__ Real sQ[kR1 ? 4 : 1][kR1 ? kQR : 1][kQW];  // J~_x u_x, J~_y u_x, J~_x u_y, J~_y u_y
+
+  // The tile and its domain: by value for a launch over one domain (block b
+  // runs on XCD b % 8; each XCD gets a contiguous run of the row-major
+  // tiles, so neighbouring tiles share an L2), from the tables otherwise.
+  int x0, y0, ncol, nrow;
+  TileDom d;
+  const NPL_CONST DomDesc *D = (const NPL_CONST DomDesc *)a.s.doms;
+  if (a.ntx) {
+    const uint32_t t = (blockIdx.x & 7) * a.per + (blockIdx.x >> 3);
+    if (t >= a.ntile) return;
+    const uint32_t r = __umulhi(t, a.div);
+    d = a.d;
+    x0 = (int)(t - r * a.ntx) * kTW;
+    y0 = (int)r * TY;
+    ncol = min(kTW, d.nx - x0);
+    nrow = min(TY, d.ny - y0);
+  } else {
+    const NPL_CONST StripDesc *sp = (const NPL_CONST StripDesc *)a.s.strips + blockIdx.x;
+    if (sp->dom < 0) return;
+    D += sp->dom;
+    if (a.s.substep >= D->steps_left) return;
+    const int par = (a.s.substep + D->parity0) & 1;
+    x0 = sp->x0;
+    y0 = sp->y0;
+    ncol = sp->x1 - x0;
+    nrow = sp->y1 - y0;
+    d.src[0] = D->h[par];
+    d.src[1] = D->g[par];
+    d.src[2] = D->prev[par];
+    d.dst[0] = D->h[par ^ 1];
+    d.dst[1] = D->g[par ^ 1];
+    d.dst[2] = D->prev[par ^ 1];
+    d.pb = (uint32_t)D->ps[0] * (uint32_t)sizeof(Real);
+    for (int G = 0; G < 3; ++G) d.rb[G] = (uint32_t)D->rs[G] * (uint32_t)sizeof(Real);
+    d.nx = D->nx;
+    d.ny = D->ny;
+    d.wall = D->wall;
+  }
+  const NPL_CONST Consts<Real> &K = *consts_of<Real>(D);
+  const NPL_CONST Consts<double> &KD = *consts_of<double>(D);
+  const int nx = d.nx, ny = d.ny;
+  const bool wall = d.wall != 0;
+  constexpr uint32_t SZ = sizeof(Real);
+  const uint32_t pb = d.pb, rbh = d.rb[0], rbg = d.rb[1], rbp = d.rb[2];
+  // one resource per group: the host picks this kernel only for domains
+  // whose groups stay below 2^31 bytes
+  const Rsrc rh = row_rsrc(d.src[0], rbh * (uint32_t)ny, 0),
+             rg = row_rsrc(d.src[1], rbg * (uint32_t)ny, 0),
+             rp = row_rsrc(d.src[2], rbp * (uint32_t)ny, 0);
+
+  const int tid = threadIdx.x;
+  const int lx = tid % kTW, ly = tid / kTW;
+  // Lattice node of tile position (px, py), px, py >= -kHalo: periodic in
+  // x; periodic or mirrored at the walls in y.  Positions more than kHalo
+  // beyond a ragged edge are never asked for.
+  auto col_of = [&](int px) {
+    int x = x0 + px;
+    x = x < 0 ? x + nx : x;
+    return x >= nx ? x - nx : x;
+  };
+  auto row_of = [&](int py) {
+    int y = y0 + py;
+    if (wall)
+      y = y < 0 ? -1 - y : (y >= ny ? 2 * ny - 1 - y : y);
+    else
+      y = y < 0 ? y + ny : (y >= ny ? y - ny : y);
+    return y;
+  };
+  // Byte offsets, direction plane included, of the populations arriving at
+  // node (x, y) in a group with row block rb: from x - c_k, or the node's
+  // own opposite direction when x - c_k lies beyond a wall.
+  auto sources = [&](int x, int y, uint32_t rb, uint32_t (&o)[9]) {
+    const uint32_t c0 = (uint32_t)x * SZ;
+    const uint32_t cw = (uint32_t)(x == 0 ? nx - 1 : x - 1) * SZ;
+    const uint32_t ce = (uint32_t)(x == nx - 1 ? 0 : x + 1) * SZ;
+    const uint32_t r0 = (uint32_t)y * rb;
+    const uint32_t rs = (uint32_t)(y == 0 ? ny - 1 : y - 1) * rb;
+    const uint32_t rn = (uint32_t)(y == ny - 1 ? 0 : y + 1) * rb;
+    const bool bs = wall && y == 0, bn = wall && y == ny - 1;
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+      const int cx = cxk(k), cy = cyk(k);
+      const uint32_t c = cx == 1 ? cw : (cx == -1 ? ce : c0);
+      const uint32_t r = cy == 1 ? rs : (cy == -1 ? rn : r0);
+      const bool b = (cy == 1 && bs) || (cy == -1 && bn);
+      o[k] = b ? r0 + c0 + (uint32_t)oppk(k) * pb : r + c + (uint32_t)k * pb;
+    }
+  };
+
+  // ---- stage A: all loads of the step ----
+  // own node; threads up to kHalo beyond a ragged edge bring halo nodes
+  const bool own = lx < ncol + kHalo && ly < nrow + kHalo;
+  const bool interior = lx < ncol && ly < nrow;
+  // Columns past a ragged right end are stored too: they fall into the
+  // padding of the row pitch, which nothing reads, and whole lines store
+  // faster than parts of one (100 x 96 N = 2 FP32: 5.5 us against 6.5 us).
+  const bool storing = ly < nrow;
+  const int x = own ? col_of(lx) : 0, y = own ? row_of(ly) : 0;
+  Real h[M][9], hi[M], g[9], pu[2];
+  if (own) {
+    uint32_t o[9];
+    sources(x, y, rbh, o);
+#pragma unroll
+    for (int i = 0; i < M; ++i)
+#pragma unroll
+      for (int k = 0; k < 9; ++k) h[i][k] = bld<Real>(rh, o[k], (uint32_t)(i * 9) * pb);
+    const uint32_t op = (uint32_t)y * rbp + (uint32_t)x * SZ;
+#pragma unroll
+    for (int i = 0; i < M; ++i) hi[i] = bld<Real>(rp, op, (uint32_t)i * pb);
+  }
+  // halo nodes: position q of the frame around the tile, one phase each
+  constexpr int kTop = kHalo * kPW;                   // whole rows below and above
+  constexpr int kHN = 2 * kTop + TY * 2 * kHalo;      // nodes of the frame
+  constexpr int kRounds = (kHN * M + kNT - 1) / kNT;  // items per thread
+  auto frame = [&](int q, int &px, int &py) {
+    if (q < 2 * kTop) {
+      const int r = q / kPW;
+      px = q % kPW - kHalo;
+      py = r < kHalo ? r - kHalo : r - kHalo + TY;
+    } else {
+      const int s = q - 2 * kTop, c = s % (2 * kHalo);
+      px = c < kHalo ? c - kHalo : c - kHalo + kTW;
+      py = s / (2 * kHalo);
+    }
+  };
+  auto load_item = [&](int r, Real (&v)[10]) {
+    const int it = tid + r * kNT;
+    const int i = it / kHN;
+    int px, py;
+    frame(it % kHN, px, py);
+    if (i < M && px < ncol + kHalo && py < nrow + kHalo) {
+      const int xn = col_of(px), yn = row_of(py);
+      uint32_t o[9];
+      sources(xn, yn, rbh, o);
+      const uint32_t ip = (uint32_t)(i * 9) * pb;
+#pragma unroll
+      for (int k = 0; k < 9; ++k) v[k] = bld<Real>(rh, o[k] + ip, 0u);
+      v[9] = bld<Real>(rp, (uint32_t)yn * rbp + (uint32_t)xn * SZ + (uint32_t)i * pb, 0u);
+    }
+  };
+  auto store_item = [&](int r, const Real (&v)[10]) {
+    const int it = tid + r * kNT;
+    const int i = it / kHN;
+    int px, py;
+    frame(it % kHN, px, py);
+    if (i < M && px < ncol + kHalo && py < nrow + kHalo) {
+      Real lo = v[0];
+#pragma unroll
+      for (int k = 1; k < 9; ++k) lo += v[k];
+      sphi[i][py + kHalo][px + kHalo] = v[9] + lo;
+    }
+  };
+  auto store_own = [&]() {
+    if (own)
+#pragma unroll
+      for (int i = 0; i < M; ++i)
+        sphi[i][ly + kHalo][lx + kHalo] = hi[i] + lo_sum(h[i]);  // eq:N28
+  };
+  constexpr int kGroup = kGrouped ? 3 : kRounds;
+  if constexpr (kGrouped) {
+    store_own();
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  Real hv[kGroup][10];
+#pragma unroll
+  for (int r = 0; r < kGroup; ++r) load_item(r, hv[r]);
+  if (interior) {
+    uint32_t o[9];
+    sources(x, y, rbg, o);
+#pragma unroll
+    for (int k = 1; k < 9; ++k) g[k] = bld<Real>(rg, o[k] - pb, 0u);
+    const uint32_t op = (uint32_t)y * rbp + (uint32_t)x * SZ;
+    pu[0] = bld<Real>(rp, op, (uint32_t)M * pb);
+    pu[1] = bld<Real>(rp, op, (uint32_t)(M + 1) * pb);
+  }
+  // Read one word of every cache line of constants while the loads above are
+  // in flight, so that the scalar loads of the later stages hit the scalar
+  // cache (cold at the start of a launch) instead of waiting in turn.
+  touch_consts<N>(K);
+  if constexpr (sizeof(Real) == 4) touch_consts<N>(KD);
+  if constexpr (!kGrouped) store_own();
+#pragma unroll
+  for (int r = 0; r < kGroup; ++r) store_item(r, hv[r]);
+  if constexpr (kGrouped) {
+#pragma unroll
+    for (int q = kGroup; q < kRounds; q += kGroup) {
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int r = 0; r < kGroup; ++r)
+        if (q + r < kRounds) load_item(q + r, hv[r]);
+#pragma unroll
+      for (int r = 0; r < kGroup; ++r)
+        if (q + r < kRounds) store_item(q + r, hv[r]);
+    }
+  }
+  __syncthreads();
+
+  // ---- stage B: chemical potentials on the tile and kRing around it ----
+  // (ghost positions beyond a wall are evaluated on the mirrored phi, which
+  // gives the mirror of C bit for bit: the sums pair opposite neighbours)
+  for (int q = tid; q < kCW * kCR; q += kNT) {
+    const int cx = q % kCW, cy = q / kCW;
+    if (cx < ncol + 2 * kRing && cy < nrow + 2 * kRing)
+      chem_node<N, Real>(
+          K, [&](int i, int dx, int dy) { return sphi[i][cy + 1 + dy][cx + 1 + dx]; },
+          [&](int i, Real v) { sC[i][cy][cx] = v; });
+  }
+  __syncthreads();
+
+  // ---- stage J (Remark 1): J~ and the products J~_b u_a ----
+  // J~ from the eq:N31a gradients of C on the tile and one node around it,
+  // u the stored velocity of the previous step.  Rows beyond a wall are not
+  // formed: stage C reads the row they mirror.
+  if constexpr (kR1) {
+    for (int q = tid; q < kQW * kQR; q += kNT) {
+      const int qx = q % kQW, qy = q / kQW;
+      const int r = y0 + qy - 1;
+      if (qx < ncol + 2 && qy < nrow + 2 && !(wall && (r < 0 || r >= ny))) {
+        Real Jx = Real(0), Jy = Real(0);
+#pragma unroll
+        for (int i = 0; i < M; ++i) {
+          Real gx, gy;
+          grad_central<Real>([&](int dx, int dy) { return sC[i][qy + 1 + dy][qx + 1 + dx]; }, gx,
+                             gy);
+          Jx += K.Jc[i] * gx;
+          Jy += K.Jc[i] * gy;
+        }
+        const uint32_t op =
+            (uint32_t)row_of(qy - 1) * rbp + (uint32_t)col_of(qx - 1) * SZ + (uint32_t)M * pb;
+        const Real ux = bld<Real>(rp, op, 0u), uy = bld<Real>(rp, op + pb, 0u);
+        sQ[0][qy][qx] = Jx * ux;
+        sQ[1][qy][qx] = Jy * ux;
+        sQ[2][qy][qx] = Jx * uy;
+        sQ[3][qy][qx] = Jy * uy;
+      }
+    }
+    __syncthreads();
+  }
+
+  // ---- stage C: gradients and collisions ----
+  if (!storing) return;
+  Real phi[M], Cv[M];
+  GradSums<Real> G{};
+  int lc = lx;
+#pragma unroll
+  for (int i = 0; i < M; ++i) {
+    phi[i] = sphi[i][ly + kHalo][lx + kHalo];
+    Cv[i] = sC[i][ly + kRing][lx + kRing];
+    // The next phase's LDS reads wait for this phase's sums (their index
+    // passes through an empty asm that takes them).  Left alone the compiler
+    // issues the reads of all phases first and holds them: 216 against 108
+    // registers for FP32 mixed N = 5 (512^2: 29.9 against 25.0 us a step),
+    // and spills for FP64 mixed N >= 7 (N = 8, 512^2: 288 against 111 us).
+    asm("" : "+v"(lc) : "v"(G.grs), "v"(G.gys), "v"(G.Fxs), "v"(G.Fys), "v"(G.Jxs), "v"(G.Jys));
+    auto fp = [&](int dx, int dy) { return sphi[i][ly + kHalo + dy][lc + kHalo + dx]; };
+    auto fc = [&](int dx, int dy) { return sC[i][ly + kRing + dy][lc + kRing + dx]; };
+    Real gx, gy;
+    if constexpr (kTwoHop)
+      grad_two_hop<Real>(fp, gx, gy);
+    else
+      grad_central<Real>(fp, gx, gy);
+    G.grs += K.rA[i] * gx;
+    G.gys += K.rA[i] * gy;
+    G.Fxs += Cv[i] * gx;
+    G.Fys += Cv[i] * gy;
+    if constexpr (!kR1) {
+      if constexpr (kTwoHop)
+        grad_two_hop<Real>(fc, gx, gy);
+      else
+        grad_central<Real>(fc, gx, gy);
+      G.Jxs += K.Jc[i] * gx;
+      G.Jys += K.Jc[i] * gy;
+    }
+  }
+  Acc divx = Acc(0), divy = Acc(0);
+  if constexpr (kR1) {
+    const int s0 = ly + 1;
+    const int sN = wall && y0 + ly == ny - 1 ? s0 : s0 + 1, sS = wall && y0 + ly == 0 ? s0 : s0 - 1;
+    auto q = [&](int c) {
+      return [&, c](int dx, int dy) {
+        return sQ[c][dy == 0 ? s0 : (dy > 0 ? sN : sS)][lx + 1 + dx];
+      };
+    };
+    divx = ddx_central(q(0)) + ddy_central(q(1));
+    divy = ddx_central(q(2)) + ddy_central(q(3));
+  }
+  const Rsrc wh = row_rsrc(d.dst[0], rbh * (uint32_t)ny, 0),
+             wg = row_rsrc(d.dst[1], rbg * (uint32_t)ny, 0),
+             wp = row_rsrc(d.dst[2], rbp * (uint32_t)ny, 0);
+  const uint32_t oc = (uint32_t)(x0 + lx) * SZ, yr = (uint32_t)(y0 + ly);
+  const uint32_t oh = yr * rbh + oc, og = yr * rbg + oc, op = yr * rbp + oc;
+  // plain stores: the state is read back by the next launch from L2 or MALL
+  collide_node<N, Real, kR1>(
+      K, KD, phi, Cv, G, divx, divy,
+      [&](int i) -> const Real(&)[9] { return h[i]; },
+      hi, g, pu,
+      [&](int plane, Real v) { bst<Real, false>(wg, og, (uint32_t)plane * pb, v); },
+      [&](int plane, Real v) { bst<Real, false>(wh, oh, (uint32_t)plane * pb, v); },
+      [&](int plane, Real v) { bst<Real, false>(wp, op, (uint32_t)plane * pb, v); });
+}
+
+template <int N>
+hipError_t launch_n(int precision, int ty, const TileArgs &a, int nblocks, hipStream_t st) {
+  if (ty == 4) {
+    if constexpr (N <= kTile4MaxN) {
+      if (precision != 64) return hipErrorInvalidValue;
+      hipLaunchKernelGGL((k_tile<N, double, 4, NPL_GS>), dim3(nblocks), dim3(kTW * 4), 0, st, a);
+      return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
+  }
+  if (ty != 8) return hipErrorInvalidValue;
+  if (precision == 64)
+    hipLaunchKernelGGL((k_tile<N, double, 8, NPL_GS>), dim3(nblocks), dim3(kTW * 8), 0, st, a);
+  else
+    hipLaunchKernelGGL((k_tile<N, float, 8, NPL_GS>), dim3(nblocks), dim3(kTW * 8), 0, st, a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+#if NPL_GS == 0
+#define NPL_SCHEME_FN(name) name##_central
+#elif NPL_GS == 1
+#define NPL_SCHEME_FN(name) name##_mixed
+#else
+#define NPL_SCHEME_FN(name) name##_remark1
+#endif
+
+hipError_t NPL_SCHEME_FN(launch_tile)(int N, int precision, int ty, const TileArgs &a,
+                                      int nblocks, hipStream_t st) {
+  if (nblocks <= 0) return hipSuccess;
+  switch (N) {
+    case 2: return launch_n<2>(precision, ty, a, nblocks, st);
+    case 3: return launch_n<3>(precision, ty, a, nblocks, st);
+    case 4: return launch_n<4>(precision, ty, a, nblocks, st);
+    case 5: return launch_n<5>(precision, ty, a, nblocks, st);
+    case 6: return launch_n<6>(precision, ty, a, nblocks, st);
+    case 7: return launch_n<7>(precision, ty, a, nblocks, st);
+    case 8: return launch_n<8>(precision, ty, a, nblocks, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+#if NPL_GS == 0
+hipError_t launch_tile(int N, int precision, int scheme, int ty, const TileArgs &a, int nblocks,
+                       hipStream_t st) {
+  return scheme == kSchemeMixed     ? launch_tile_mixed(N, precision, ty, a, nblocks, st)
+         : scheme == kSchemeRemark1 ? launch_tile_remark1(N, precision, ty, a, nblocks, st)
+                                    : launch_tile_central(N, precision, ty, a, nblocks, st);
+}
+
+hipError_t launch_geom_step(int N, int precision, int scheme, const StepGeom &g, const StepArgs &a,
+                            int nblocks, const DomDesc *one, hipStream_t st) {
+  if (!g.ty) return launch_step(N, precision, scheme, g.bw, a, nblocks, st);
+  TileArgs t{};
+  t.s = a;
+  if (one) {
+    const int par = (a.substep + one->parity0) & 1;
+    const uint32_t sz = (uint32_t)(precision / 8);
+    t.d.src[0] = one->h[par];
+    t.d.src[1] = one->g[par];
+    t.d.src[2] = one->prev[par];
+    t.d.dst[0] = one->h[par ^ 1];
+    t.d.dst[1] = one->g[par ^ 1];
+    t.d.dst[2] = one->prev[par ^ 1];
+    t.d.pb = (uint32_t)one->ps[0] * sz;
+    for (int G = 0; G < 3; ++G) t.d.rb[G] = (uint32_t)one->rs[G] * sz;
+    t.d.nx = one->nx;
+    t.d.ny = one->ny;
+    t.d.wall = one->wall;
+    t.ntx = (uint32_t)((one->nx + kTileWidth - 1) / kTileWidth);
+    // t = div * ntile stays below 2^32 for every lattice the host's rule
+    // admits, so the high product is the exact quotient; ntx = 1 has no
+    // 32-bit reciprocal and takes the table
+    t.div = (uint32_t)((((uint64_t)1 << 32) + t.ntx - 1) / t.ntx);
+    t.ntile = t.ntx * (uint32_t)((one->ny + g.ty - 1) / g.ty);
+    t.per = (t.ntile + 7) / 8;
+    if (t.ntx == 1)
+      t.ntx = 0;
+    else
+      nblocks = (int)(t.per * 8);
+  }
+  return launch_tile(N, precision, scheme, g.ty, t, nblocks, st);
+}
+#endif
+
+}  // namespace nplbm

@@ -1,0 +1,55 @@
+"""The tile kernel of small 2-D lattices against the marching kernel and the
+oracle.  Both kernels evaluate the same expressions per node, so after any
+number of steps c, u and p are bitwise equal (NPLBM_TILE = 0 asks for the
+marching kernel); in FP64 they match the oracle within 1e-10 max-abs, the
+bound of every FP64 parity test.  Sizes sit where a 32 x 8 (or 32 x 4) tile
+can go wrong: lattices below one tile and below the halo, one node past an
+edge, one tile column (launched through the table), several XCD runs."""
+import os
+
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle.accept import oracle_accepts
+from tests.gpu_util import gpu_domain, maxabs, oracle_run
+
+pytestmark = pytest.mark.gpu
+SCHEMES = {"central": {}, "mixed": {"grad_scheme": 1}, "remark1": {"force_form": 1}}
+
+
+def _macro(w, precision, steps, tile, **over):
+    saved = os.environ.pop("NPLBM_TILE", None)
+    if tile is not None:
+        os.environ["NPLBM_TILE"] = tile
+    try:
+        d = gpu_domain(w, precision=precision, **over)
+    finally:
+        os.environ.pop("NPLBM_TILE", None)
+        if saved is not None:
+            os.environ["NPLBM_TILE"] = saved
+    d.step(steps)
+    out = d.macro()
+    d.close()
+    return out
+
+
+@pytest.mark.parametrize("nx,ny", [(4, 4), (5, 9), (32, 8), (33, 7), (64, 17), (35, 31),
+                                   (161, 130)])
+@pytest.mark.parametrize("scheme", list(SCHEMES))
+@pytest.mark.parametrize("N", [2, 3, 5, 8])
+def test_tiles_equal_strips_and_oracle(N, scheme, nx, ny):
+    steps = 15
+    sig = {"sigma_range": (0.95e-3, 1.05e-3)} if N > 5 else {}
+    for wall in (False, True):
+        w = W.random_smooth(N, nx, ny, seed=700 + N + nx + wall, wall_y=wall,
+                            accept=oracle_accepts, **sig)
+        print(f"case tile N={N} {scheme} {nx}x{ny} wall={wall} steps={steps}", flush=True)
+        o = oracle_run(w, steps, **SCHEMES[scheme]).macro()
+        for precision in (64, 32):
+            strips = _macro(w, precision, steps, "0", **SCHEMES[scheme])
+            for tile in (None, "8"):
+                got = _macro(w, precision, steps, tile, **SCHEMES[scheme])
+                assert all(np.array_equal(a, b) for a, b in zip(got, strips)), (precision, tile)
+            if precision == 64:
+                assert max(maxabs(a, b) for a, b in zip(got, o)) < 1e-10
