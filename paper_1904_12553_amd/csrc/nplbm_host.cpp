@@ -483,21 +483,20 @@ StepGeom step_geom(int N, int precision, int scheme) {
 // state, 2 x 10 N words per node, fit the 256 MB Infinity Cache: it reads the
 // halo of each tile again, which is cheap from there, and has a thread for
 // every node where marching strips leave compute units idle (100^2 N = 3 FP64
-// 7.0 against 45 us a step; 512^2: N = 3 FP64 23 against 67, N = 4 FP32 19
+// 5.7 against 45 us a step; 512^2: N = 3 FP64 23 against 67, N = 4 FP32 19
 // against 61, N = 8 FP32 41 against 64; at the edge, 768^2 N = 5 FP32, 236
 // MB, 46 against 78).  Beyond it the second read goes to HBM and the marching
 // kernel, which reads every population once, is faster (768^2 N = 3 FP64,
 // 283 MB, 64 against 76, but 1024^2 N = 3 FP64 116 against 100, N = 5 FP32
 // 119 against 100, 768^2 N = 4 FP64 96 against 87).
 // Tiles have 8 rows; 4 in FP64 with few phases while that still gives each
-// compute unit at most one tile (160^2 N = 3: 6.9 against 7.5 us; 180^2, two
-// tiles on some, 8.4 against 7.7; mixed N = 5 160^2 13.3 against 12.8; FP32
-// measures the same or slower with 4).
+// compute unit at most one tile (160^2 N = 3: 6.1 against 7.1 us; two tiles
+// on some units at 180^2 were slower, as was mixed N = 5; FP32 measures the
+// same or slower with 4).
 // A set NPLBM_TX, NPLBM_BW, NPLBM_MIN_STRIP_H or NPLBM_TARGET_BLOCKS asks for
 // strips; NPLBM_TILE = 0 (strips), 4 or 8 overrides.
 StepGeom domain_geom(const nplbm_params *p) {
   constexpr int64_t kCacheBytes = (int64_t)256 << 20;
-  constexpr int64_t kComputeUnits = 256;
   const int scheme = step_scheme(p);
   StepGeom g = step_geom(p->N, p->precision, scheme);
   for (const char *e : {"NPLBM_TX", "NPLBM_BW", "NPLBM_MIN_STRIP_H", "NPLBM_TARGET_BLOCKS"})

@@ -26,6 +26,7 @@ struct StepGeom {
 // per node.
 constexpr int kTileWidth = 32;
 constexpr int kTile4MaxN = 5;
+constexpr int kComputeUnits = 256;  // of the chip
 // Gradient schemes (nplbm_params.grad_scheme): central isotropic (eq:N31a)
 // or the isotropic mixed scheme of eq:N40 (sign of its two-hop term read as
 // negative).

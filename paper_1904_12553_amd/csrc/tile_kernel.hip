@@ -40,6 +40,23 @@ namespace {
 
 constexpr int kTW = kTileWidth;  // columns of a tile
 
+// Position q of the frame of width H around the tile, q < 2 H (kTW + 2 H + TY),
+// counted from the frame's corner: the rows below and above, then the columns
+// beside the tile.
+template <int H, int TY>
+__device__ __forceinline__ void frame_at(int q, int &px, int &py) {
+  constexpr int kW = kTW + 2 * H, kTop = H * kW;
+  if (q < 2 * kTop) {
+    const int r = q / kW;
+    px = q % kW;
+    py = r < H ? r : r + TY;
+  } else {
+    const int s = q - 2 * kTop, c = s % (2 * H);
+    px = c < H ? c : c + kTW;
+    py = s / (2 * H) + H;
+  }
+}
+
 // One word of each 64-byte line of the constants in use, kept alive by an
 // empty asm.
 template <int N, typename Real>
@@ -60,8 +77,11 @@ __device__ __forceinline__ void touch_consts(const NPL_CONST Consts<Real> &K) {
   asm volatile("" ::"v"(s));
 }
 
-template <int N, typename Real, int TY, int kGS>
-__global__ void __launch_bounds__(kTW * TY) k_tile(TileArgs a) {
+// kHelp: the workgroup has a second set of kTW x TY threads that takes the
+// halo items of stage A and the rings of stages B and J, so that a node's own
+// thread goes through its own part only.
+template <int N, typename Real, int TY, int kGS, bool kHelp>
+__global__ void __launch_bounds__(kTW * TY * (kHelp ? 2 : 1)) k_tile(TileArgs a) {
   constexpr int M = N - 1;
   constexpr bool kTwoHop = kGS == kSchemeMixed;  // eq:N40 first derivatives
   constexpr bool kR1 = kGS == kSchemeRemark1;    // Remark 1 force distribution
@@ -131,7 +151,10 @@ __global__ void __launch_bounds__(kTW * TY) k_tile(TileArgs a) {
              rp = row_rsrc(d.src[2], rbp * (uint32_t)ny, 0);
 
   const int tid = threadIdx.x;
-  const int lx = tid % kTW, ly = tid / kTW;
+  // helpers hold no node (uniform over a wave)
+  const bool helper = kHelp && __builtin_amdgcn_readfirstlane(tid / kNT) != 0;
+  const int ht = tid % kNT;  // thread number among the halo's threads
+  const int lx = ht % kTW, ly = ht / kTW;
   // Lattice node of tile position (px, py), px, py >= -kHalo: periodic in
   // x; periodic or mirrored at the walls in y.  Positions more than kHalo
   // beyond a ragged edge are never asked for.
@@ -171,12 +194,12 @@ __global__ void __launch_bounds__(kTW * TY) k_tile(TileArgs a) {
 
   // ---- stage A: all loads of the step ----
   // own node; threads up to kHalo beyond a ragged edge bring halo nodes
-  const bool own = lx < ncol + kHalo && ly < nrow + kHalo;
-  const bool interior = lx < ncol && ly < nrow;
+  const bool own = !helper && lx < ncol + kHalo && ly < nrow + kHalo;
+  const bool interior = !helper && lx < ncol && ly < nrow;
   // Columns past a ragged right end are stored too: they fall into the
   // padding of the row pitch, which nothing reads, and whole lines store
   // faster than parts of one (100 x 96 N = 2 FP32: 5.5 us against 6.5 us).
-  const bool storing = ly < nrow;
+  const bool storing = !helper && ly < nrow;
   const int x = own ? col_of(lx) : 0, y = own ? row_of(ly) : 0;
   Real h[M][9], hi[M], g[9], pu[2];
   if (own) {
@@ -191,25 +214,15 @@ __global__ void __launch_bounds__(kTW * TY) k_tile(TileArgs a) {
     for (int i = 0; i < M; ++i) hi[i] = bld<Real>(rp, op, (uint32_t)i * pb);
   }
   // halo nodes: position q of the frame around the tile, one phase each
-  constexpr int kTop = kHalo * kPW;                   // whole rows below and above
-  constexpr int kHN = 2 * kTop + TY * 2 * kHalo;      // nodes of the frame
+  constexpr int kHN = 2 * kHalo * (kPW + TY);         // nodes of the frame
   constexpr int kRounds = (kHN * M + kNT - 1) / kNT;  // items per thread
-  auto frame = [&](int q, int &px, int &py) {
-    if (q < 2 * kTop) {
-      const int r = q / kPW;
-      px = q % kPW - kHalo;
-      py = r < kHalo ? r - kHalo : r - kHalo + TY;
-    } else {
-      const int s = q - 2 * kTop, c = s % (2 * kHalo);
-      px = c < kHalo ? c - kHalo : c - kHalo + kTW;
-      py = s / (2 * kHalo);
-    }
-  };
   auto load_item = [&](int r, Real (&v)[10]) {
-    const int it = tid + r * kNT;
+    const int it = ht + r * kNT;
     const int i = it / kHN;
     int px, py;
-    frame(it % kHN, px, py);
+    frame_at<kHalo, TY>(it % kHN, px, py);
+    px -= kHalo;
+    py -= kHalo;
     if (i < M && px < ncol + kHalo && py < nrow + kHalo) {
       const int xn = col_of(px), yn = row_of(py);
       uint32_t o[9];
@@ -221,10 +234,12 @@ __global__ void __launch_bounds__(kTW * TY) k_tile(TileArgs a) {
     }
   };
   auto store_item = [&](int r, const Real (&v)[10]) {
-    const int it = tid + r * kNT;
+    const int it = ht + r * kNT;
     const int i = it / kHN;
     int px, py;
-    frame(it % kHN, px, py);
+    frame_at<kHalo, TY>(it % kHN, px, py);
+    px -= kHalo;
+    py -= kHalo;
     if (i < M && px < ncol + kHalo && py < nrow + kHalo) {
       Real lo = v[0];
 #pragma unroll
@@ -243,9 +258,11 @@ __global__ void __launch_bounds__(kTW * TY) k_tile(TileArgs a) {
     store_own();
     __builtin_amdgcn_sched_barrier(0);
   }
+  const bool halo = !kHelp || helper;  // who brings the halo
   Real hv[kGroup][10];
+  if (halo)
 #pragma unroll
-  for (int r = 0; r < kGroup; ++r) load_item(r, hv[r]);
+    for (int r = 0; r < kGroup; ++r) load_item(r, hv[r]);
   if (interior) {
     uint32_t o[9];
     sources(x, y, rbg, o);
@@ -261,9 +278,9 @@ __global__ void __launch_bounds__(kTW * TY) k_tile(TileArgs a) {
   touch_consts<N>(K);
   if constexpr (sizeof(Real) == 4) touch_consts<N>(KD);
   if constexpr (!kGrouped) store_own();
+  if (halo) {
 #pragma unroll
-  for (int r = 0; r < kGroup; ++r) store_item(r, hv[r]);
-  if constexpr (kGrouped) {
+    for (int r = 0; r < kGroup; ++r) store_item(r, hv[r]);
 #pragma unroll
     for (int q = kGroup; q < kRounds; q += kGroup) {
       __builtin_amdgcn_sched_barrier(0);
@@ -280,12 +297,20 @@ __global__ void __launch_bounds__(kTW * TY) k_tile(TileArgs a) {
   // ---- stage B: chemical potentials on the tile and kRing around it ----
   // (ghost positions beyond a wall are evaluated on the mirrored phi, which
   // gives the mirror of C bit for bit: the sums pair opposite neighbours)
-  for (int q = tid; q < kCW * kCR; q += kNT) {
-    const int cx = q % kCW, cy = q / kCW;
+  auto chem_at = [&](int cx, int cy) {
     if (cx < ncol + 2 * kRing && cy < nrow + 2 * kRing)
       chem_node<N, Real>(
           K, [&](int i, int dx, int dy) { return sphi[i][cy + 1 + dy][cx + 1 + dx]; },
           [&](int i, Real v) { sC[i][cy][cx] = v; });
+  };
+  if constexpr (kHelp) {
+    for (int q = helper ? ht : 0; q < (helper ? 2 * kRing * (kCW + TY) : 1); q += kNT) {
+      int cx = lx + kRing, cy = ly + kRing;
+      if (helper) frame_at<kRing, TY>(q, cx, cy);
+      chem_at(cx, cy);
+    }
+  } else {
+    for (int q = tid; q < kCW * kCR; q += kNT) chem_at(q % kCW, q / kCW);
   }
   __syncthreads();
 
@@ -294,8 +319,7 @@ __global__ void __launch_bounds__(kTW * TY) k_tile(TileArgs a) {
   // u the stored velocity of the previous step.  Rows beyond a wall are not
   // formed: stage C reads the row they mirror.
   if constexpr (kR1) {
-    for (int q = tid; q < kQW * kQR; q += kNT) {
-      const int qx = q % kQW, qy = q / kQW;
+    auto prod_at = [&](int qx, int qy) {
       const int r = y0 + qy - 1;
       if (qx < ncol + 2 && qy < nrow + 2 && !(wall && (r < 0 || r >= ny))) {
         Real Jx = Real(0), Jy = Real(0);
@@ -315,6 +339,15 @@ __global__ void __launch_bounds__(kTW * TY) k_tile(TileArgs a) {
         sQ[2][qy][qx] = Jx * uy;
         sQ[3][qy][qx] = Jy * uy;
       }
+    };
+    if constexpr (kHelp) {
+      for (int q = helper ? ht : 0; q < (helper ? 2 * (kQW + TY) : 1); q += kNT) {
+        int qx = lx + 1, qy = ly + 1;
+        if (helper) frame_at<1, TY>(q, qx, qy);
+        prod_at(qx, qy);
+      }
+    } else {
+      for (int q = tid; q < kQW * kQR; q += kNT) prod_at(q % kQW, q / kQW);
     }
     __syncthreads();
   }
@@ -381,22 +414,38 @@ __global__ void __launch_bounds__(kTW * TY) k_tile(TileArgs a) {
       [&](int plane, Real v) { bst<Real, false>(wp, op, (uint32_t)plane * pb, v); });
 }
 
+// Whether a launch of nblocks tiles gets the helper threads: while every
+// workgroup is resident at once, one per compute unit, or two where the
+// registers allow four waves per SIMD (N x bytes <= 20: at most 128).  A step
+// with and without them: 64^2 FP32 N = 5 7.4 / 8.9 us, 256 x 256 9.4 / 10.9;
+// 256 x 416 (416 tiles) 13.6 / 14.5, FP64 N = 3 there 13.5 / 12.1; 512^2
+// FP32 N = 5 (1024 tiles) 25.0 / 23.0.
+template <int N, typename Real>
+constexpr int help_limit() {
+  return kComputeUnits * (N * (int)sizeof(Real) <= 20 ? 2 : 1);
+}
+
+template <int N, typename Real, int TY>
+hipError_t launch_t(const TileArgs &a, int nblocks, hipStream_t st) {
+  if (nblocks <= help_limit<N, Real>())
+    hipLaunchKernelGGL((k_tile<N, Real, TY, NPL_GS, true>), dim3(nblocks), dim3(kTW * TY * 2), 0,
+                       st, a);
+  else
+    hipLaunchKernelGGL((k_tile<N, Real, TY, NPL_GS, false>), dim3(nblocks), dim3(kTW * TY), 0, st,
+                       a);
+  return hipGetLastError();
+}
+
 template <int N>
 hipError_t launch_n(int precision, int ty, const TileArgs &a, int nblocks, hipStream_t st) {
   if (ty == 4) {
-    if constexpr (N <= kTile4MaxN) {
-      if (precision != 64) return hipErrorInvalidValue;
-      hipLaunchKernelGGL((k_tile<N, double, 4, NPL_GS>), dim3(nblocks), dim3(kTW * 4), 0, st, a);
-      return hipGetLastError();
-    }
+    if constexpr (N <= kTile4MaxN)
+      if (precision == 64) return launch_t<N, double, 4>(a, nblocks, st);
     return hipErrorInvalidValue;
   }
   if (ty != 8) return hipErrorInvalidValue;
-  if (precision == 64)
-    hipLaunchKernelGGL((k_tile<N, double, 8, NPL_GS>), dim3(nblocks), dim3(kTW * 8), 0, st, a);
-  else
-    hipLaunchKernelGGL((k_tile<N, float, 8, NPL_GS>), dim3(nblocks), dim3(kTW * 8), 0, st, a);
-  return hipGetLastError();
+  return precision == 64 ? launch_t<N, double, 8>(a, nblocks, st)
+                         : launch_t<N, float, 8>(a, nblocks, st);
 }
 
 }  // namespace

@@ -4,7 +4,9 @@ number of steps c, u and p are bitwise equal (NPLBM_TILE = 0 asks for the
 marching kernel); in FP64 they match the oracle within 1e-10 max-abs, the
 bound of every FP64 parity test.  Sizes sit where a 32 x 8 (or 32 x 4) tile
 can go wrong: lattices below one tile and below the halo, one node past an
-edge, one tile column (launched through the table), several XCD runs."""
+edge, one tile column (launched through the table), several XCD runs, and
+the three tile counts between which the launch changes (one and two tiles
+per compute unit)."""
 import os
 
 import numpy as np
@@ -35,7 +37,7 @@ def _macro(w, precision, steps, tile, **over):
 
 
 @pytest.mark.parametrize("nx,ny", [(4, 4), (5, 9), (32, 8), (33, 7), (64, 17), (35, 31),
-                                   (161, 130)])
+                                   (161, 130), (256, 272), (200, 520)])
 @pytest.mark.parametrize("scheme", list(SCHEMES))
 @pytest.mark.parametrize("N", [2, 3, 5, 8])
 def test_tiles_equal_strips_and_oracle(N, scheme, nx, ny):
