@@ -192,9 +192,9 @@ int nplbm_diagnostics(nplbm_domain *d, double *mass_out, double *max_sum_dev,
  *   out_dev  caller-owned device buffer of N + 2 doubles: sum_x c_k for
  *            k = 0..N-1, then max_x |sum_k c_k - 1|, then the number of
  *            nodes with a non-finite c_k (as a double).
- * Asynchronous on the domain's stream; enqueues kernels only (the FP64
- * read-back into the domain's own read-back planes, then the reduction) and
- * reads the state current at enqueue time.  The reduction's partial records
+ * Asynchronous on the domain's stream; enqueues kernels only (the reduction
+ * over the populations, then the sum of its partial records) and reads the
+ * state current at enqueue time.  The reduction's partial records
  * live in a static device array of the library (1024 x 10 doubles + 16, about
  * 82 KB, held on each GPU it runs on until the process ends) instead of the
  * domain's allocation: every call on one GPU shares it, so calls that

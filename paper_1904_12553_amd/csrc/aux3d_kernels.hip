@@ -3,6 +3,7 @@
 // per node on dense (nz x ny x nx) FP64 planes.  Not in the time loop.
 #include "lattice3.h"
 #include "nplbm_internal.h"
+#include "reduce.h"
 
 namespace nplbm {
 
@@ -10,15 +11,23 @@ namespace {
 
 constexpr int kT3 = 256;
 
+// a in [-n, 2 n): the callers step one node
 __device__ __forceinline__ int wrap3i(int a, int n) {
-  a %= n;
-  return a < 0 ? a + n : a;
+  return a < 0 ? a + n : (a >= n ? a - n : a);
 }
 
 struct Geo3 {
   int nx, ny, nz;
   bool wall;
 };
+
+// coordinates of dense node id (a domain has at most 2^30 nodes)
+__device__ __forceinline__ void coords3(const Geo3 &g, int64_t id, int &x, int &y, int &z) {
+  const uint32_t row = (uint32_t)id / (uint32_t)g.nx;
+  x = (int)((uint32_t)id - row * (uint32_t)g.nx);
+  z = (int)(row / (uint32_t)g.ny);
+  y = (int)(row - (uint32_t)z * (uint32_t)g.ny);
+}
 
 // dense index of (x + dx, y + dy, z + dz): periodic in x and y; in z
 // periodic or a mirror ghost beyond a wall
@@ -72,15 +81,17 @@ __global__ void k3_init_phi(PhiMap3 pm, int M, const double *c, double *phi, int
 }
 
 // C_i from phi (eq:N18 line 3 with eq:N17)
-__global__ void k3_chem(const DomDesc *dd, int M, const double *phi, double *C) {
+template <int M>
+__global__ void __launch_bounds__(kT3) k3_chem(const DomDesc *dd, const double *phi, double *C) {
   const Geo3 g{dd->nx, dd->ny, dd->nz, dd->wall != 0};
   const int64_t n = (int64_t)g.nx * g.ny * g.nz;
   const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (id >= n) return;
-  const int x = (int)(id % g.nx), y = (int)((id / g.nx) % g.ny), z = (int)(id / ((int64_t)g.nx * g.ny));
+  int x, y, z;
+  coords3(g, id, x, y, z);
   const Consts<double> &K = dd->cd;
-  const int N = M + 1;
-  double ph[kMaxM], lp[kMaxM], wv[kMaxN];
+  constexpr int N = M + 1;
+  double ph[M], lp[M], wv[N];
   for (int i = 0; i < M; ++i) {
     ph[i] = phi[(int64_t)i * n + id];
     lp[i] = lap3d(phi + (int64_t)i * n, g, x, y, z);
@@ -102,15 +113,15 @@ __global__ void k3_chem(const DomDesc *dd, int M, const double *phi, double *C) 
 // step kernel reads the population arriving at this node (at x - c_k, or
 // in the opposite direction at the node itself across a wall); the k = 0
 // slot holds h_0 - phi_stored
-template <typename Real>
-__global__ void k3_init_dist(const DomDesc *dd, int M, const double *phi, const double *C,
-                             const double *u) {
+template <int M, typename Real>
+__global__ void __launch_bounds__(kT3) k3_init_dist(const DomDesc *dd, const double *phi,
+                                                    const double *C, const double *u) {
   const Geo3 gg{dd->nx, dd->ny, dd->nz, dd->wall != 0};
   const int64_t n = (int64_t)gg.nx * gg.ny * gg.nz;
   const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (id >= n) return;
-  const int x = (int)(id % gg.nx), y = (int)((id / gg.nx) % gg.ny),
-            z = (int)(id / ((int64_t)gg.nx * gg.ny));
+  int x, y, z;
+  coords3(gg, id, x, y, z);
   const Consts<double> &K = dd->cd;
   Real *h = static_cast<Real *>(dd->h[dd->parity0]);
   Real *g = static_cast<Real *>(dd->g[dd->parity0]);
@@ -163,47 +174,84 @@ __device__ __forceinline__ Pull3 pull3(const Geo3 &g, int k, int x, int y, int z
   return p;
 }
 
-// phi (eq:N28 on the stored state), rho and c_k in FP64
-template <typename Real>
-__global__ void k3_macro_phi(const DomDesc *dd, int M, int parity, double *phi, double *rho,
-                             double *cout) {
+// phi of one node in FP64 (eq:N28 on the stored state)
+template <int M, typename Real>
+__device__ __forceinline__ void phi_node3(const DomDesc *dd, const Geo3 &g, const Real *h,
+                                          const Real *pv, int x, int y, int z, double (&ph)[M]) {
+#pragma unroll
+  for (int i = 0; i < M; ++i) ph[i] = (double)pv[at3(dd, 2, i, z, y, x)];
+#pragma unroll
+  for (int k = 0; k < 15; ++k) {
+    const Pull3 p = pull3(g, k, x, y, z);
+#pragma unroll
+    for (int i = 0; i < M; ++i) ph[i] += (double)h[at3(dd, 0, i * 15 + p.kk, p.zs, p.ys, p.xs)];
+  }
+}
+
+// phi, rho and c_k planes; phi and rho only for the callers that go on to
+// u and p (rho non-null)
+template <int M, typename Real>
+__global__ void __launch_bounds__(kT3) k3_macro_phi(const DomDesc *dd, int parity, double *phi,
+                                                    double *rho, double *cout) {
   const Geo3 g{dd->nx, dd->ny, dd->nz, dd->wall != 0};
   const int64_t n = (int64_t)g.nx * g.ny * g.nz;
   const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (id >= n) return;
-  const int x = (int)(id % g.nx), y = (int)((id / g.nx) % g.ny), z = (int)(id / ((int64_t)g.nx * g.ny));
+  int x, y, z;
+  coords3(g, id, x, y, z);
+  const Consts<double> &K = dd->cd;
+  double ph[M];
+  phi_node3<M, Real>(dd, g, static_cast<const Real *>(dd->h[parity]),
+                     static_cast<const Real *>(dd->prev[parity]), x, y, z, ph);
+  if (rho) {
+    double r = K.ra;
+#pragma unroll
+    for (int i = 0; i < M; ++i) {
+      phi[(int64_t)i * n + id] = ph[i];
+      r += K.rA[i] * ph[i];
+    }
+    rho[id] = r;
+  }
+  if (cout)
+#pragma unroll
+    for (int k = 0; k <= M; ++k) cout[(int64_t)k * n + id] = c_of<M>(K, k, ph);
+}
+
+// the diagnostics of a 3-D domain, as k_diag_partial in 2-D
+template <int M, typename Real>
+__global__ void __launch_bounds__(kReduceThreads) k3_diag_partial(const DomDesc *dd, int parity,
+                                                                  double *partials) {
+  constexpr int N = M + 1;
+  const Geo3 g{dd->nx, dd->ny, dd->nz, dd->wall != 0};
+  const int64_t n = (int64_t)g.nx * g.ny * g.nz;
   const Real *h = static_cast<const Real *>(dd->h[parity]);
   const Real *pv = static_cast<const Real *>(dd->prev[parity]);
   const Consts<double> &K = dd->cd;
-  double ph[kMaxM];
-  for (int i = 0; i < M; ++i) ph[i] = (double)pv[at3(dd, 2, i, z, y, x)];
-  for (int k = 0; k < 15; ++k) {
-    const Pull3 p = pull3(g, k, x, y, z);
-    for (int i = 0; i < M; ++i) ph[i] += (double)h[at3(dd, 0, i * 15 + p.kk, p.zs, p.ys, p.xs)];
+  double acc[N + 2];
+#pragma unroll
+  for (int q = 0; q < N + 2; ++q) acc[q] = 0.0;
+  for (int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; id < n;
+       id += (int64_t)gridDim.x * blockDim.x) {
+    int x, y, z;
+    coords3(g, id, x, y, z);
+    double ph[M];
+    phi_node3<M, Real>(dd, g, h, pv, x, y, z, ph);
+    diag_add<M>(K, ph, acc);
   }
-  double r = K.ra;
-  for (int i = 0; i < M; ++i) {
-    phi[(int64_t)i * n + id] = ph[i];
-    r += K.rA[i] * ph[i];
-  }
-  rho[id] = r;
-  if (cout)
-    for (int k = 0; k < M + 1; ++k) {
-      double ck = K.ca[k];
-      for (int i = 0; i < M; ++i) ck += K.cA[k][i] * ph[i];
-      cout[(int64_t)k * n + id] = ck;
-    }
+  block_record<N + 2>(acc, N, partials + (int64_t)blockIdx.x * (N + 2));
 }
 
 // u (eq:N22_1) and p (eq:N23 with the D3Q15 rest weight) in FP64
-template <typename Real>
-__global__ void k3_macro_up(const DomDesc *dd, int M, int parity, const double *phi,
-                            const double *rho, const double *C, double *uout, double *pout) {
+template <int M, typename Real>
+__global__ void __launch_bounds__(kT3) k3_macro_up(const DomDesc *dd, int parity,
+                                                   const double *phi, const double *rho,
+                                                   const double *C, double *uout, double *pout) {
   const Geo3 g{dd->nx, dd->ny, dd->nz, dd->wall != 0};
   const int64_t n = (int64_t)g.nx * g.ny * g.nz;
   const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (id >= n) return;
-  const int x = (int)(id % g.nx), y = (int)((id / g.nx) % g.ny), z = (int)(id / ((int64_t)g.nx * g.ny));
+  int x, y, z;
+  coords3(g, id, x, y, z);
   const Real *gp = static_cast<const Real *>(dd->g[parity]);
   const Consts<double> &K = dd->cd;
   double F[3] = {0.0, 0.0, 0.0}, gr[3] = {0.0, 0.0, 0.0};
@@ -240,6 +288,18 @@ __global__ void k3_macro_up(const DomDesc *dd, int M, int parity, const double *
   if (pout) pout[id] = 3.0 / 7.0 * (sg + 0.5 * udr - r * usq / 3.0);
 }
 
+// 3-D domains are built for N <= 5
+template <typename F>
+hipError_t for_phases3(int N, F f) {
+  return N > 5 ? hipErrorInvalidValue
+               : for_phases(N, [&](auto n) {
+                   if constexpr (decltype(n)::value <= 5)
+                     return f(n);
+                   else
+                     return hipErrorInvalidValue;
+                 });
+}
+
 int nb3blocks(int64_t n) { return (int)((n + kT3 - 1) / kT3); }
 
 }  // namespace
@@ -258,37 +318,50 @@ hipError_t launch_init3(const DomDesc *dd_dev, const DomDesc &dd, int precision,
   }
   const int nb = nb3blocks(n);
   hipLaunchKernelGGL(k3_init_phi, dim3(nb), dim3(kT3), 0, st, pm, M, c_dev, phi_tmp, n);
-  hipLaunchKernelGGL(k3_chem, dim3(nb), dim3(kT3), 0, st, dd_dev, M, phi_tmp, C_tmp);
-  if (precision == 64)
-    hipLaunchKernelGGL(k3_init_dist<double>, dim3(nb), dim3(kT3), 0, st, dd_dev, M, phi_tmp,
-                       C_tmp, u_dev);
-  else
-    hipLaunchKernelGGL(k3_init_dist<float>, dim3(nb), dim3(kT3), 0, st, dd_dev, M, phi_tmp,
-                       C_tmp, u_dev);
-  return hipGetLastError();
+  return for_phases3(dd.N, [&](auto n) {
+    constexpr int kM = decltype(n)::value - 1;
+    hipLaunchKernelGGL(k3_chem<kM>, dim3(nb), dim3(kT3), 0, st, dd_dev, phi_tmp, C_tmp);
+    if (precision == 64)
+      hipLaunchKernelGGL((k3_init_dist<kM, double>), dim3(nb), dim3(kT3), 0, st, dd_dev, phi_tmp,
+                         C_tmp, u_dev);
+    else
+      hipLaunchKernelGGL((k3_init_dist<kM, float>), dim3(nb), dim3(kT3), 0, st, dd_dev, phi_tmp,
+                         C_tmp, u_dev);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_macro3(const DomDesc *dd_dev, const DomDesc &dd, int precision, int parity,
                          double *phi, double *rho, double *C, double *c_out, double *u_out,
                          double *p_out, hipStream_t st) {
-  const int M = dd.N - 1;
-  const int64_t n = (int64_t)dd.nx * dd.ny * dd.nz;
-  const int nb = nb3blocks(n);
-  if (precision == 64)
-    hipLaunchKernelGGL(k3_macro_phi<double>, dim3(nb), dim3(kT3), 0, st, dd_dev, M, parity, phi,
-                       rho, c_out);
-  else
-    hipLaunchKernelGGL(k3_macro_phi<float>, dim3(nb), dim3(kT3), 0, st, dd_dev, M, parity, phi,
-                       rho, c_out);
-  if (!u_out && !p_out) return hipGetLastError();
-  hipLaunchKernelGGL(k3_chem, dim3(nb), dim3(kT3), 0, st, dd_dev, M, phi, C);
-  if (precision == 64)
-    hipLaunchKernelGGL(k3_macro_up<double>, dim3(nb), dim3(kT3), 0, st, dd_dev, M, parity, phi,
+  const int nb = nb3blocks((int64_t)dd.nx * dd.ny * dd.nz);
+  const bool up = u_out || p_out;
+  auto run = [&](auto n, auto real) {
+    constexpr int kM = decltype(n)::value - 1;
+    using Real = decltype(real);
+    hipLaunchKernelGGL((k3_macro_phi<kM, Real>), dim3(nb), dim3(kT3), 0, st, dd_dev, parity, phi,
+                       up ? rho : nullptr, c_out);
+    if (!up) return hipGetLastError();
+    hipLaunchKernelGGL(k3_chem<kM>, dim3(nb), dim3(kT3), 0, st, dd_dev, phi, C);
+    hipLaunchKernelGGL((k3_macro_up<kM, Real>), dim3(nb), dim3(kT3), 0, st, dd_dev, parity, phi,
                        rho, C, u_out, p_out);
-  else
-    hipLaunchKernelGGL(k3_macro_up<float>, dim3(nb), dim3(kT3), 0, st, dd_dev, M, parity, phi,
-                       rho, C, u_out, p_out);
-  return hipGetLastError();
+    return hipGetLastError();
+  };
+  return for_phases3(dd.N, [&](auto n) { return precision == 64 ? run(n, 0.0) : run(n, 0.0f); });
+}
+
+hipError_t launch_diag3(const DomDesc *dd_dev, const DomDesc &dd, int precision, int parity,
+                        double *partials, int nblk, double *out, hipStream_t st) {
+  return for_phases3(dd.N, [&](auto n) {
+    constexpr int N = decltype(n)::value;
+    if (precision == 64)
+      hipLaunchKernelGGL((k3_diag_partial<N - 1, double>), dim3(nblk), dim3(kReduceThreads), 0, st,
+                         dd_dev, parity, partials);
+    else
+      hipLaunchKernelGGL((k3_diag_partial<N - 1, float>), dim3(nblk), dim3(kReduceThreads), 0, st,
+                         dd_dev, parity, partials);
+    return launch_diag_final(N, partials, nblk, out, st);
+  });
 }
 
 }  // namespace nplbm

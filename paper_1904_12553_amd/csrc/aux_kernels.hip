@@ -7,6 +7,7 @@
 
 #include "lattice.h"
 #include "nplbm_internal.h"
+#include "reduce.h"
 
 namespace nplbm {
 
@@ -14,9 +15,9 @@ namespace {
 
 constexpr int kThreads = 256;
 
+// a in [-n, 2 n): the stencils step at most two nodes, and n >= 4
 __device__ __forceinline__ int wrapi(int a, int n) {
-  a %= n;
-  return a < 0 ? a + n : a;
+  return a < 0 ? a + n : (a >= n ? a - n : a);
 }
 
 // Neighbour (x + dx, y + dy) of a stencil: periodic in x; in y periodic or a
@@ -92,16 +93,17 @@ __global__ void k_init_phi(PhiMap pm, int M, const double *c, double *phi, int64
 }
 
 // C_i from phi (eq:N18 line 3 with eq:N17), dense planes
-__global__ void k_chem(const DomDesc *dd, int M, const double *phi, double *C) {
+template <int M>
+__global__ void __launch_bounds__(kThreads) k_chem(const DomDesc *dd, const double *phi, double *C) {
   const int nx = dd->nx, ny = dd->ny;
   const int64_t n = (int64_t)nx * ny;
   const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (id >= n) return;
-  const int x = (int)(id % nx), y = (int)(id / nx);
+  const int y = (int)((uint32_t)id / (uint32_t)nx), x = (int)id - y * nx;
   const bool wall = dd->wall != 0;
   const Consts<double> &K = dd->cd;
-  const int N = M + 1;
-  double ph[kMaxM], lp[kMaxM], wv[kMaxN];
+  constexpr int N = M + 1;
+  double ph[M], lp[M], wv[N];
   for (int i = 0; i < M; ++i) {
     ph[i] = phi[(int64_t)i * n + id];
     lp[i] = lap9(phi + (int64_t)i * n, x, y, nx, ny, wall);
@@ -124,14 +126,14 @@ __global__ void k_chem(const DomDesc *dd, int M, const double *phi, double *C) {
 // reads it, i.e. at x - c_k, or in the opposite direction at x itself when
 // x - c_k lies beyond a wall.  The k = 0 slot holds the deviation of h_0
 // from the stored phi (prev), as the step kernel expects.
-template <typename Real>
-__global__ void k_init_dist(const DomDesc *dd, int M, const double *phi, const double *C,
-                            const double *u) {
+template <int M, typename Real>
+__global__ void __launch_bounds__(kThreads) k_init_dist(const DomDesc *dd, const double *phi,
+                                                        const double *C, const double *u) {
   const int nx = dd->nx, ny = dd->ny, pitch = dd->pitch;
   const int64_t n = (int64_t)nx * ny;
   const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (id >= n) return;
-  const int x = (int)(id % nx), y = (int)(id / nx);
+  const int y = (int)((uint32_t)id / (uint32_t)nx), x = (int)id - y * nx;
   const bool wall = dd->wall != 0;
   const Consts<double> &K = dd->cd;
   Real *h = static_cast<Real *>(dd->h[dd->parity0]);
@@ -173,60 +175,72 @@ __global__ void k_init_dist(const DomDesc *dd, int M, const double *phi, const d
 }
 
 // --------------------------------------------------------------- macro ----
-// phi (pull + eq:N28), c_k, rho in FP64 from the stored populations
-template <typename Real>
-__global__ void k_macro_phi(const DomDesc *dd, int M, int parity, double *phi, double *rho,
-                            double *cout) {
-  const int nx = dd->nx, ny = dd->ny, pitch = dd->pitch;
-  const int64_t n = (int64_t)nx * ny;
-  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= n) return;
-  const int x = (int)(id % nx), y = (int)(id / nx);
+// phi of one node in FP64 from the stored populations (pull + eq:N28):
+// phi_i = phi_prev + (h_0 - phi_prev) + sum_{k>=1} h_k
+template <int M, typename Real>
+__device__ __forceinline__ void phi_node(const DomDesc *dd, const Real *h, const Real *pv, int x,
+                                         int y, double (&ph)[M]) {
+  const int nx = dd->nx, ny = dd->ny;
   const bool wall = dd->wall != 0;
-  const Real *h = static_cast<const Real *>(dd->h[parity]);
-  const Real *pv = static_cast<const Real *>(dd->prev[parity]);
-  const Consts<double> &K = dd->cd;
-  const int N = M + 1;
-  double ph[kMaxM];
-  // phi_i = phi_prev + (h_0 - phi_prev) + sum_{k>=1} h_k (eq:N28)
+#pragma unroll
   for (int i = 0; i < M; ++i) ph[i] = (double)pv[at(dd, 2, i, y, x)];
+#pragma unroll
   for (int k = 0; k < 9; ++k) {
     const int cx = cxk(k), cy = cyk(k);
-    int ys = y - cy, xs = wrapi(x - cx, nx);
+    int ys = y - cy, xs = x - cx;
     int kk = k;
     if (wall && (ys < 0 || ys >= ny)) {
       kk = oppk(k);
       ys = y;
       xs = x;
     } else {
-      ys = wrapi(ys, ny);
+      xs = xs < 0 ? xs + nx : (xs >= nx ? xs - nx : xs);
+      ys = ys < 0 ? ys + ny : (ys >= ny ? ys - ny : ys);
     }
+#pragma unroll
     for (int i = 0; i < M; ++i) ph[i] += (double)h[at(dd, 0, i * 9 + kk, ys, xs)];
   }
-  double r = K.ra;
-  for (int i = 0; i < M; ++i) {
-    phi[(int64_t)i * n + id] = ph[i];
-    r += K.rA[i] * ph[i];
-  }
-  rho[id] = r;
-  if (cout)
-    for (int k = 0; k < N; ++k) {
-      double ck = K.ca[k];
-      for (int i = 0; i < M; ++i) ck += K.cA[k][i] * ph[i];
-      cout[(int64_t)k * n + id] = ck;
+}
+
+// phi, rho and c_k planes; phi and rho only for the callers that go on to
+// u and p (rho non-null)
+template <int M, typename Real>
+__global__ void __launch_bounds__(kThreads) k_macro_phi(const DomDesc *dd, int parity, double *phi,
+                                                        double *rho, double *cout) {
+  const int nx = dd->nx;
+  const int64_t n = (int64_t)nx * dd->ny;
+  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (id >= n) return;
+  const int y = (int)((uint32_t)id / (uint32_t)nx), x = (int)id - y * nx;
+  const Consts<double> &K = dd->cd;
+  double ph[M];
+  phi_node<M, Real>(dd, static_cast<const Real *>(dd->h[parity]),
+                    static_cast<const Real *>(dd->prev[parity]), x, y, ph);
+  if (rho) {
+    double r = K.ra;
+#pragma unroll
+    for (int i = 0; i < M; ++i) {
+      phi[(int64_t)i * n + id] = ph[i];
+      r += K.rA[i] * ph[i];
     }
+    rho[id] = r;
+  }
+  if (cout)
+#pragma unroll
+    for (int k = 0; k <= M; ++k) cout[(int64_t)k * n + id] = c_of<M>(K, k, ph);
 }
 
 // Remark 1 (Sec. 3.1): the products J~_b u_a, J~ from the eq:N31a
 // gradients of C (eq:N18 line 4) and u the stored velocity of the previous
 // step; planes q[0..3] = J~_x u_x, J~_y u_x, J~_x u_y, J~_y u_y.
-template <typename Real>
-__global__ void k_macro_q(const DomDesc *dd, int M, int parity, const double *C, double *q) {
+template <int M, typename Real>
+__global__ void __launch_bounds__(kThreads) k_macro_q(const DomDesc *dd, int parity,
+                                                      const double *C, double *q) {
   const int nx = dd->nx, ny = dd->ny;
   const int64_t n = (int64_t)nx * ny;
   const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (id >= n) return;
-  const int x = (int)(id % nx), y = (int)(id / nx);
+  const int y = (int)((uint32_t)id / (uint32_t)nx), x = (int)id - y * nx;
   const bool wall = dd->wall != 0;
   const Real *pv = static_cast<const Real *>(dd->prev[parity]);
   const Consts<double> &K = dd->cd;
@@ -246,15 +260,16 @@ __global__ void k_macro_q(const DomDesc *dd, int M, int parity, const double *C,
 
 // u (eq:N22_1) and p (eq:N23) in FP64; with q non-null the force also
 // carries -div(J~ u) of Remark 1, component a = sum_b d_b q(b, a)
-template <typename Real>
-__global__ void k_macro_up(const DomDesc *dd, int M, int parity, const double *phi,
-                           const double *rho, const double *C, const double *q, double *uout,
-                           double *pout) {
+template <int M, typename Real>
+__global__ void __launch_bounds__(kThreads) k_macro_up(const DomDesc *dd, int parity,
+                                                       const double *phi, const double *rho,
+                                                       const double *C, const double *q,
+                                                       double *uout, double *pout) {
   const int nx = dd->nx, ny = dd->ny, pitch = dd->pitch;
   const int64_t n = (int64_t)nx * ny;
   const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (id >= n) return;
-  const int x = (int)(id % nx), y = (int)(id / nx);
+  const int y = (int)((uint32_t)id / (uint32_t)nx), x = (int)id - y * nx;
   const bool wall = dd->wall != 0;
   const Real *g = static_cast<const Real *>(dd->g[parity]);
   const Consts<double> &K = dd->cd;
@@ -313,72 +328,45 @@ __global__ void k_macro_up(const DomDesc *dd, int M, int parity, const double *p
 }
 
 // ---------------------------------------------------------- reductions ----
-__device__ __forceinline__ double wave_sum(double v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-__device__ __forceinline__ double wave_max(double v) {
-  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-  return v;
-}
 
-// Per-block partial sums of each c_k, max |sum_k c_k - 1| and non-finite
-// count; a block strides over the field so the result does not depend on
-// scheduling.  partials[b * (N + 2) + q].
-__global__ void k_diag_partial(const double *c, int N, int64_t n, double *partials) {
-  __shared__ double red[kThreads / 64][kMaxN + 2];
-  double acc[kMaxN + 2];
+// Conservation diagnostics straight from the populations: per-block partial
+// sums of each c_k, max |sum_k c_k - 1| and non-finite count; a block strides
+// over the field so the result does not depend on scheduling.
+// partials[b * (N + 2) + q].  Bound by reading 10 (N - 1) words a node once:
+// 117 us on 2048^2 N = 5 FP32, 5.7 TB/s (writing phi, rho and c planes and
+// reducing those took 335 + 52 us).
+template <int M, typename Real>
+__global__ void __launch_bounds__(kThreads) k_diag_partial(const DomDesc *dd, int parity,
+                                                           double *partials) {
+  constexpr int N = M + 1;
+  const int nx = dd->nx;
+  const int64_t n = (int64_t)nx * dd->ny;
+  const Real *h = static_cast<const Real *>(dd->h[parity]);
+  const Real *pv = static_cast<const Real *>(dd->prev[parity]);
+  const Consts<double> &K = dd->cd;
+  double acc[N + 2];
+#pragma unroll
   for (int q = 0; q < N + 2; ++q) acc[q] = 0.0;
   for (int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; id < n;
        id += (int64_t)gridDim.x * blockDim.x) {
-    double s = 0.0;
-    bool bad = false;
-    for (int k = 0; k < N; ++k) {
-      const double v = c[(int64_t)k * n + id];
-      bad |= !isfinite(v);
-      acc[k] += v;
-      s += v;
-    }
-    acc[N] = fmax(acc[N], fabs(s - 1.0));
-    acc[N + 1] += bad ? 1.0 : 0.0;
+    const int y = (int)((uint32_t)id / (uint32_t)nx), x = (int)id - y * nx;
+    double ph[M];
+    phi_node<M, Real>(dd, h, pv, x, y, ph);
+    diag_add<M>(K, ph, acc);
   }
-  const int wv = threadIdx.x / 64, ln = threadIdx.x & 63;
-  for (int q = 0; q < N + 2; ++q) {
-    const double r = (q == N) ? wave_max(acc[q]) : wave_sum(acc[q]);
-    if (ln == 0) red[wv][q] = r;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int q = 0; q < N + 2; ++q) {
-      double r = red[0][q];
-      for (int w = 1; w < kThreads / 64; ++w) r = (q == N) ? fmax(r, red[w][q]) : r + red[w][q];
-      partials[(int64_t)blockIdx.x * (N + 2) + q] = r;
-    }
-  }
-}
-
-// entry qmax of each partial record is a maximum, the others are sums
-__global__ void k_diag_final(const double *partials, int nq, int nblk, int qmax, double *out) {
-  const int q = threadIdx.x;
-  if (q >= nq) return;
-  double r = 0.0;
-  for (int b = 0; b < nblk; ++b) {
-    const double v = partials[(int64_t)b * nq + q];
-    r = q == qmax ? fmax(r, v) : r + v;
-  }
-  out[q] = r;
+  block_record<N + 2>(acc, N, partials + (int64_t)blockIdx.x * (N + 2));
 }
 
 // Laplace: sums and counts of p inside r <= r_in and outside r >= r_out
 __global__ void k_laplace_partial(const double *p, int nx, int ny, int nz, double xc, double yc,
                                   double zc, double r_in, double r_out, double *partials) {
-  __shared__ double red[kThreads / 64][4];
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   const int64_t n = (int64_t)nx * ny * nz;
   for (int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; id < n;
        id += (int64_t)gridDim.x * blockDim.x) {
-    const double x = (double)(id % nx), y = (double)((id / nx) % ny),
-                 z = (double)(id / ((int64_t)nx * ny));
+    const uint32_t row = (uint32_t)id / (uint32_t)nx, pl = row / (uint32_t)ny;
+    const double x = (double)((uint32_t)id - row * (uint32_t)nx),
+                 y = (double)(row - pl * (uint32_t)ny), z = (double)pl;
     const double r = sqrt((x - xc) * (x - xc) + (y - yc) * (y - yc) + (z - zc) * (z - zc));
     if (r <= r_in) {
       acc[0] += p[id];
@@ -388,26 +376,33 @@ __global__ void k_laplace_partial(const double *p, int nx, int ny, int nz, doubl
       acc[3] += 1.0;
     }
   }
-  const int wv = threadIdx.x / 64, ln = threadIdx.x & 63;
-  for (int q = 0; q < 4; ++q) {
-    const double r = wave_sum(acc[q]);
-    if (ln == 0) red[wv][q] = r;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0)
-    for (int q = 0; q < 4; ++q) {
-      double r = 0.0;
-      for (int w = 0; w < kThreads / 64; ++w) r += red[w][q];
-      partials[(int64_t)blockIdx.x * 4 + q] = r;
-    }
+  block_record<4>(acc, -1, partials + (int64_t)blockIdx.x * 4);
 }
 
 __global__ void k_laplace_final(const double *partials, int nblk, double *out) {
-  if (threadIdx.x != 0) return;
-  double a[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int b = 0; b < nblk; ++b)
-    for (int q = 0; q < 4; ++q) a[q] += partials[(int64_t)b * 4 + q];
-  out[0] = (a[1] > 0.0 && a[3] > 0.0) ? a[0] / a[1] - a[2] / a[3] : 0.0;
+  __shared__ double a[4];
+  const int q = threadIdx.x / 64, ln = threadIdx.x & 63;  // one wave per entry
+  double r = 0.0;
+  for (int b = ln; b < nblk; b += 64) r += partials[(int64_t)b * 4 + q];
+  r = wave_sum(r);
+  if (ln == 0) a[q] = r;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    out[0] = (a[1] > 0.0 && a[3] > 0.0) ? a[0] / a[1] - a[2] / a[3] : 0.0;
+}
+
+// entry qmax of each partial record is a maximum, the others are sums; one
+// wave per entry (one thread per entry, one record after the other, took
+// 141 us for 1024 records of N = 4; this 7 us)
+__global__ void k_diag_final(const double *partials, int nq, int nblk, int qmax, double *out) {
+  const int q = threadIdx.x / 64, ln = threadIdx.x & 63;
+  double r = 0.0;
+  for (int b = ln; b < nblk; b += 64) {
+    const double v = partials[(int64_t)b * nq + q];
+    r = q == qmax ? fmax(r, v) : r + v;
+  }
+  r = q == qmax ? wave_max(r) : wave_sum(r);
+  if (ln == 0) out[q] = r;
 }
 
 // one 16-byte element per thread and a grid covering the buffer: the
@@ -440,47 +435,44 @@ hipError_t launch_init(const DomDesc *dd_dev, const DomDesc &dd, int precision,
   }
   const int nb = blocks_for(n);
   hipLaunchKernelGGL(k_init_phi, dim3(nb), dim3(kThreads), 0, st, pm, M, c_dev, phi_tmp, n);
-  hipLaunchKernelGGL(k_chem, dim3(nb), dim3(kThreads), 0, st, dd_dev, M, phi_tmp, C_tmp);
-  if (precision == 64)
-    hipLaunchKernelGGL(k_init_dist<double>, dim3(nb), dim3(kThreads), 0, st, dd_dev, M,
-                       phi_tmp, C_tmp, u_dev);
-  else
-    hipLaunchKernelGGL(k_init_dist<float>, dim3(nb), dim3(kThreads), 0, st, dd_dev, M,
-                       phi_tmp, C_tmp, u_dev);
-  return hipGetLastError();
+  return for_phases(dd.N, [&](auto n) {
+    constexpr int kM = decltype(n)::value - 1;
+    hipLaunchKernelGGL(k_chem<kM>, dim3(nb), dim3(kThreads), 0, st, dd_dev, phi_tmp, C_tmp);
+    if (precision == 64)
+      hipLaunchKernelGGL((k_init_dist<kM, double>), dim3(nb), dim3(kThreads), 0, st, dd_dev,
+                         phi_tmp, C_tmp, u_dev);
+    else
+      hipLaunchKernelGGL((k_init_dist<kM, float>), dim3(nb), dim3(kThreads), 0, st, dd_dev,
+                         phi_tmp, C_tmp, u_dev);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_macro(const DomDesc *dd_dev, const DomDesc &dd, int precision, int parity,
                         double *phi, double *rho, double *C, double *c_out, double *u_out,
                         double *p_out, double *q, hipStream_t st) {
-  const int M = dd.N - 1;
-  const int64_t n = (int64_t)dd.nx * dd.ny;
-  const int nb = blocks_for(n);
-  if (precision == 64)
-    hipLaunchKernelGGL(k_macro_phi<double>, dim3(nb), dim3(kThreads), 0, st, dd_dev, M, parity,
-                       phi, rho, c_out);
-  else
-    hipLaunchKernelGGL(k_macro_phi<float>, dim3(nb), dim3(kThreads), 0, st, dd_dev, M, parity,
-                       phi, rho, c_out);
-  if (!u_out && !p_out) return hipGetLastError();
-  hipLaunchKernelGGL(k_chem, dim3(nb), dim3(kThreads), 0, st, dd_dev, M, phi, C);
-  const double *qq = dd.scheme == kSchemeRemark1 ? q : nullptr;
-  if (dd.scheme == kSchemeRemark1) {
-    if (!q) return hipErrorInvalidValue;
-    if (precision == 64)
-      hipLaunchKernelGGL(k_macro_q<double>, dim3(nb), dim3(kThreads), 0, st, dd_dev, M, parity,
+  const int64_t nodes = (int64_t)dd.nx * dd.ny;
+  const int nb = blocks_for(nodes);
+  const bool up = u_out || p_out;
+  if (up && dd.scheme == kSchemeRemark1 && !q) return hipErrorInvalidValue;
+  auto run = [&](auto n, auto real) {
+    constexpr int kM = decltype(n)::value - 1;
+    using Real = decltype(real);
+    hipLaunchKernelGGL((k_macro_phi<kM, Real>), dim3(nb), dim3(kThreads), 0, st, dd_dev, parity,
+                       phi, up ? rho : nullptr, c_out);
+    if (!up) return hipGetLastError();
+    hipLaunchKernelGGL(k_chem<kM>, dim3(nb), dim3(kThreads), 0, st, dd_dev, phi, C);
+    const double *qq = nullptr;
+    if (dd.scheme == kSchemeRemark1) {
+      hipLaunchKernelGGL((k_macro_q<kM, Real>), dim3(nb), dim3(kThreads), 0, st, dd_dev, parity,
                          C, q);
-    else
-      hipLaunchKernelGGL(k_macro_q<float>, dim3(nb), dim3(kThreads), 0, st, dd_dev, M, parity,
-                         C, q);
-  }
-  if (precision == 64)
-    hipLaunchKernelGGL(k_macro_up<double>, dim3(nb), dim3(kThreads), 0, st, dd_dev, M, parity,
+      qq = q;
+    }
+    hipLaunchKernelGGL((k_macro_up<kM, Real>), dim3(nb), dim3(kThreads), 0, st, dd_dev, parity,
                        phi, rho, C, qq, u_out, p_out);
-  else
-    hipLaunchKernelGGL(k_macro_up<float>, dim3(nb), dim3(kThreads), 0, st, dd_dev, M, parity,
-                       phi, rho, C, qq, u_out, p_out);
-  return hipGetLastError();
+    return hipGetLastError();
+  };
+  return for_phases(dd.N, [&](auto n) { return precision == 64 ? run(n, 0.0) : run(n, 0.0f); });
 }
 
 // ---- the static scratch of nplbm_diagnostics_noalloc ----
@@ -521,10 +513,24 @@ int diag_blocks(int64_t n) {
   return (int)(b < 1024 ? (b < 1 ? 1 : b) : 1024);
 }
 
-hipError_t launch_diag(const double *c, int N, int64_t n, double *partials, int nblk,
-                       double *out, hipStream_t st) {
-  hipLaunchKernelGGL(k_diag_partial, dim3(nblk), dim3(kThreads), 0, st, c, N, n, partials);
-  hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(64), 0, st, partials, N + 2, nblk, N, out);
+hipError_t launch_diag(const DomDesc *dd_dev, const DomDesc &dd, int precision, int parity,
+                       double *partials, int nblk, double *out, hipStream_t st) {
+  return for_phases(dd.N, [&](auto n) {
+    constexpr int N = decltype(n)::value;
+    if (precision == 64)
+      hipLaunchKernelGGL((k_diag_partial<N - 1, double>), dim3(nblk), dim3(kThreads), 0, st,
+                         dd_dev, parity, partials);
+    else
+      hipLaunchKernelGGL((k_diag_partial<N - 1, float>), dim3(nblk), dim3(kThreads), 0, st,
+                         dd_dev, parity, partials);
+    return launch_diag_final(N, partials, nblk, out, st);
+  });
+}
+
+hipError_t launch_diag_final(int N, const double *partials, int nblk, double *out,
+                             hipStream_t st) {
+  hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(64 * (N + 2)), 0, st, partials, N + 2, nblk, N,
+                     out);
   return hipGetLastError();
 }
 
@@ -533,7 +539,7 @@ hipError_t launch_laplace(const double *p, int nx, int ny, int nz, double xc, do
                           double *out, hipStream_t st) {
   hipLaunchKernelGGL(k_laplace_partial, dim3(nblk), dim3(kThreads), 0, st, p, nx, ny, nz, xc, yc,
                      zc, r_in, r_out, partials);
-  hipLaunchKernelGGL(k_laplace_final, dim3(1), dim3(64), 0, st, partials, nblk, out);
+  hipLaunchKernelGGL(k_laplace_final, dim3(1), dim3(256), 0, st, partials, nblk, out);
   return hipGetLastError();
 }
 

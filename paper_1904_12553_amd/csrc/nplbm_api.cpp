@@ -395,15 +395,13 @@ int nplbm_diagnostics(nplbm_domain *d, double *mass_out, double *max_sum_dev,
   clear_error();
   if (!check_domain(d)) return fail(NPLBM_EINVAL, "NULL domain");
   if (!d->initialised) return fail(NPLBM_ESTATE, "nplbm_set_fields was not called");
-  int rc = readback(d, false);
-  if (rc) return rc;
   const int N = d->p.N;
-  const int64_t n = (int64_t)nnodes(d);
-  hipError_t e = launch_diag(dptr(d, d->L.c), N, n, dptr(d, d->L.partials), d->L.nblk,
-                             dptr(d, d->L.out), d->stream);
+  hipError_t e = (d->d3 ? launch_diag3 : launch_diag)(
+      d->desc_dev, d->desc, d->p.precision, (int)(d->t & 1), dptr(d, d->L.partials), d->L.nblk,
+      dptr(d, d->L.out), d->stream);
   if (e != hipSuccess) return hip_fail(e, "diag launch");
   double out[kMaxN + 2];
-  rc = copy_out(d, out, d->L.out, (size_t)(N + 2) * 8);
+  int rc = copy_out(d, out, d->L.out, (size_t)(N + 2) * 8);
   if (rc) return rc;
   if (mass_out)
     for (int k = 0; k < N; ++k) mass_out[k] = out[k];
@@ -430,9 +428,8 @@ int nplbm_diagnostics_noalloc(nplbm_domain *d, double *out_dev) {
   double *scr = nullptr;
   e = static_diag_scratch(&scr);
   if (e != hipSuccess) return hip_fail(e, "static scratch address");
-  int rc = readback(d, false);
-  if (rc) return rc;
-  e = launch_diag(dptr(d, d->L.c), N, (int64_t)nnodes(d), scr, nblk, out_dev, d->stream);
+  e = (d->d3 ? launch_diag3 : launch_diag)(d->desc_dev, d->desc, d->p.precision, (int)(d->t & 1),
+                                           scr, nblk, out_dev, d->stream);
   if (e != hipSuccess) return hip_fail(e, "diag launch");
   return NPLBM_OK;
 }

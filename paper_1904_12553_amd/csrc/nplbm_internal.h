@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace nplbm {
 
 constexpr int kMaxN = 8;          // phases
@@ -160,6 +162,21 @@ struct TileArgs {
   uint32_t ntx, div, ntile, per;
 };
 
+// f(std::integral_constant<int, N>) for a validated number of phases
+template <typename F>
+hipError_t for_phases(int N, F f) {
+  switch (N) {
+    case 2: return f(std::integral_constant<int, 2>());
+    case 3: return f(std::integral_constant<int, 3>());
+    case 4: return f(std::integral_constant<int, 4>());
+    case 5: return f(std::integral_constant<int, 5>());
+    case 6: return f(std::integral_constant<int, 6>());
+    case 7: return f(std::integral_constant<int, 7>());
+    case 8: return f(std::integral_constant<int, 8>());
+    default: return hipErrorInvalidValue;
+  }
+}
+
 // Launchers (defined in the .hip files).  All are asynchronous on `st`.
 hipError_t launch_step(int N, int precision, int scheme, int bw, const StepArgs &a,
                        int nblocks, hipStream_t st);
@@ -224,8 +241,9 @@ hipError_t launch_macro(const DomDesc *dd_dev, const DomDesc &dd, int precision,
                         double *phi, double *rho, double *C, double *c_out, double *u_out,
                         double *p_out, double *q, hipStream_t st);
 
-// FP64 reductions over the c fields (N planes): per-phase sums, max
-// |sum c - 1|, non-finite count.  partials must hold nblk*(N+2) doubles.
+// FP64 reductions over the c of the current state (2-D and 3-D): per-phase
+// sums, max |sum c - 1|, non-finite count.  partials must hold nblk*(N+2)
+// doubles.
 int diag_blocks(int64_t n);
 // Doubles in the static device scratch of the allocation-free diagnostics:
 // the partial records of the most blocks diag_blocks() returns, plus the
@@ -235,8 +253,11 @@ constexpr int kStaticDiagDoubles = kStaticDiagPartials + 16;
 // Device address of that scratch on the current device (looked up once per
 // device with that device current).
 hipError_t static_diag_scratch(double **out);
-hipError_t launch_diag(const double *c, int N, int64_t n, double *partials, int nblk,
-                       double *out, hipStream_t st);
+hipError_t launch_diag(const DomDesc *dd_dev, const DomDesc &dd, int precision, int parity,
+                       double *partials, int nblk, double *out, hipStream_t st);
+hipError_t launch_diag3(const DomDesc *dd_dev, const DomDesc &dd, int precision, int parity,
+                        double *partials, int nblk, double *out, hipStream_t st);
+hipError_t launch_diag_final(int N, const double *partials, int nblk, double *out, hipStream_t st);
 // Laplace jump on a dense FP64 p field of nx * ny * nz nodes (nz = 1 in
 // 2-D): mean of p within distance r_in of (xc, yc, zc) minus the mean at
 // distance >= r_out.
