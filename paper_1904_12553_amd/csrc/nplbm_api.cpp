@@ -1,6 +1,7 @@
 // nplbm_api.cpp -- the single-domain part of the C ABI (include/nplbm.h).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <climits>
 #include <cmath>
 #include <cstdlib>
@@ -250,6 +251,7 @@ int nplbm_create(const nplbm_params *p, void *stream, void *device_mem, size_t d
   D.nz = dom_nz(p);
   if (is3d(p)) {
     D.phi3 = d->base + d->L.phi3;
+    D.c3 = d->L.c3 ? d->base + d->L.c3 : nullptr;
     D.rsf = (N - 1) * d->L.pitch;
   }
   D.pitch = d->L.pitch;
@@ -264,10 +266,14 @@ int nplbm_create(const nplbm_params *p, void *stream, void *device_mem, size_t d
   std::vector<StripDesc> strips;
   d->d3 = is3d(p);
   if (d->d3) {
-    d->ty = step3_ty(N, p->precision);
+    d->ty = step3_ty(N, p->precision, p->nx, p->ny, p->nz);
+    if (d->ty == 0 && !D.c3) {
+      nplbm_destroy(d);
+      return fail(NPLBM_ESTATE, "the step kernel's environment overrides changed during the call");
+    }
     int target = resident_step3_blocks(N, p->precision, d->ty);
     if (const char *env = std::getenv("NPLBM_TARGET_BLOCKS")) target = std::atoi(env);
-    build_tiles3(p->nx, p->ny, p->nz, 0, d->ty, target, strips);
+    build_tiles3(p->nx, p->ny, p->nz, 0, std::max(d->ty, 4), target, strips);
   } else {
     d->geom = domain_geom(p);
     build_strips(p->nx, p->ny, 0, d->geom, strips, single_domain_target(p));

@@ -433,6 +433,10 @@ Layout plan_layout(const nplbm_params *p) {
   L.p = take(n * 8);
   // 3-D: the phi array written by the phi pass of each step
   L.phi3 = d3 ? take((size_t)nrows * M * L.pitch * s) : 0;
+  // and the C array of the node kernels, where those step the domain
+  L.c3 = d3 && step3_ty(N, p->precision, p->nx, p->ny, p->nz) == 0
+             ? take((size_t)nrows * M * L.pitch * s)
+             : 0;
   // the products J~_b u_a of the Remark 1 force, for the read-back
   L.q = p->force_form == 1 ? take(4 * n * 8) : 0;
   L.nblk = diag_blocks((int64_t)n);
@@ -496,7 +500,6 @@ StepGeom step_geom(int N, int precision, int scheme) {
 // A set NPLBM_TX, NPLBM_BW, NPLBM_MIN_STRIP_H or NPLBM_TARGET_BLOCKS asks for
 // strips; NPLBM_TILE = 0 (strips), 4 or 8 overrides.
 StepGeom domain_geom(const nplbm_params *p) {
-  constexpr int64_t kCacheBytes = (int64_t)256 << 20;
   const int scheme = step_scheme(p);
   StepGeom g = step_geom(p->N, p->precision, scheme);
   for (const char *e : {"NPLBM_TX", "NPLBM_BW", "NPLBM_MIN_STRIP_H", "NPLBM_TARGET_BLOCKS"})

@@ -28,7 +28,8 @@ struct StepGeom {
 // per node.
 constexpr int kTileWidth = 32;
 constexpr int kTile4MaxN = 5;
-constexpr int kComputeUnits = 256;  // of the chip
+constexpr int kComputeUnits = 256;                    // of the chip
+constexpr int64_t kCacheBytes = (int64_t)256 << 20;  // of its Infinity Cache
 // Gradient schemes (nplbm_params.grad_scheme): central isotropic (eq:N31a)
 // or the isotropic mixed scheme of eq:N40 (sign of its two-hop term read as
 // negative).
@@ -110,6 +111,7 @@ struct DomDesc {
   // the phi pass and read by the step pass of the same time step
   int32_t rsf;
   void *phi3;
+  void *c3;  // 3-D: the C_i of the node kernels, laid out as phi3
   Consts<double> cd;
   Consts<float> cf;
 };
@@ -207,9 +209,12 @@ int step_blocks_per_cu_central(int N, int precision, int bw);
 int step_blocks_per_cu_mixed(int N, int precision, int bw);
 int step_blocks_per_cu_remark1(int N, int precision, int bw);
 
-// The 3-D (D3Q15) step kernel: tiles of (64 - 4) x (ty - 4) interior nodes,
-// ty rows of one 64-lane wave each (ty = 8 or 16).
-int step3_ty(int N, int precision);
+// How a 3-D (D3Q15) domain is stepped: rows of the marching kernel's tiles
+// (4 or 8, one 64-lane wave each), or 0 for the node kernels.
+int step3_ty(int N, int precision, int nx, int ny, int nz);
+// One 3-D time step by node kernels after the phi pass (step3n_kernel.hip).
+hipError_t launch_step3n(int N, int precision, const StepArgs &s, int nx, int ny, int nz,
+                         hipStream_t st);
 // One 3-D time step: the phi pass over all nx * ny * nz nodes of domain 0
 // of a.doms, then the tiled step pass over nblocks tiles.
 hipError_t launch_step3(int N, int precision, int ty, const StepArgs &a, int nblocks, int nx,

@@ -27,20 +27,13 @@
 // population reads, and no population is read twice by the step pass.
 // D3Q15 stencils reach the six faces and eight corners of a node, so the
 // halo is two nodes for phi and one for C, as in 2-D.
-//
-// Stencils on D3Q15 (eq:N31 with the weights 1/9 and 1/72, c_s^2 = 1/3):
-//   lap   = (8 sum_faces + sum_corners - 56 zeta) / 12
-//   d/dx  = (8 (E - W) + sum_corners c_x zeta) / 24     (likewise y, z)
+#include <algorithm>
 #include <cstdlib>
 #include <type_traits>
 
-#include "buffer_io.h"
-#include "lattice3.h"
-#include "nplbm_internal.h"
+#include "node_math3.h"
 
 namespace nplbm {
-
-#define NPL_CONST __attribute__((address_space(4)))
 
 namespace {
 
@@ -48,19 +41,6 @@ constexpr int k3W = 64;   // threads per tile row (one wave) = interior columns 
 constexpr int k3L = 68;   // LDS row: the 64 columns plus 2 halo columns each side
 constexpr int k3PR = 5;   // phi ring planes
 constexpr int k3CR = 4;   // C ring planes
-
-template <typename Real>
-__device__ __forceinline__ const NPL_CONST Consts<Real> *consts3(const NPL_CONST DomDesc *d);
-template <>
-__device__ __forceinline__ const NPL_CONST Consts<double> *consts3<double>(
-    const NPL_CONST DomDesc *d) {
-  return &d->cd;
-}
-template <>
-__device__ __forceinline__ const NPL_CONST Consts<float> *consts3<float>(
-    const NPL_CONST DomDesc *d) {
-  return &d->cf;
-}
 
 // what the collision of one node reads: CH populations pulled (k = 0: the
 // stored deviation), stored previous phi, NS populations k = 1..14 pulled,
@@ -103,12 +83,8 @@ __global__ void __launch_bounds__(k3W * TY) k_step3(StepArgs a) {
   const void *hs = D->h[par], *hd = D->h[par ^ 1];
   const void *gs = D->g[par], *gd = D->g[par ^ 1];
   const void *pvs = D->prev[par], *pvd = D->prev[par ^ 1];
-  const NPL_CONST Consts<Real> &K = *consts3<Real>(D);
-  // the NS part of the collision in FP64 arithmetic in both modes (FP32
-  // populations stay FP32): FP32 rounding there biases each node's momentum
-  // in the same direction wherever the flow state repeats
-  using Acc = double;
-  const NPL_CONST Consts<double> &KD = *consts3<double>(D);
+  const NPL_CONST Consts<Real> &K = *consts_of<Real>(D);
+  const NPL_CONST Consts<double> &KD = *consts_of<double>(D);
   const int nx = D->nx, ny = D->ny, nz = D->nz;
   const bool wall = D->wall != 0;
   constexpr uint32_t SZ = sizeof(Real);
@@ -297,38 +273,12 @@ __global__ void __launch_bounds__(k3W * TY) k_step3(StepArgs a) {
   constexpr bool kOneCopy = N >= 5 || kLean;
   auto chem_at = [&](int q, int c, int s0, int sU, int sD, int sc) {
     const int ty = q + 1;  // phi ring row of C ring row q
-    Real phi[M], lap[M];
-#pragma unroll
-    for (int i = 0; i < M; ++i) {
-      const Real v = sphi[s0][i][ty][c];
-      const Real faces = (sphi[s0][i][ty][c + 1] + sphi[s0][i][ty][c - 1]) +
-                         (sphi[s0][i][ty + 1][c] + sphi[s0][i][ty - 1][c]) +
-                         (sphi[sU][i][ty][c] + sphi[sD][i][ty][c]);
-      const Real corners =
-          ((sphi[sU][i][ty + 1][c + 1] + sphi[sU][i][ty + 1][c - 1]) +
-           (sphi[sU][i][ty - 1][c + 1] + sphi[sU][i][ty - 1][c - 1])) +
-          ((sphi[sD][i][ty + 1][c + 1] + sphi[sD][i][ty + 1][c - 1]) +
-           (sphi[sD][i][ty - 1][c + 1] + sphi[sD][i][ty - 1][c - 1]));
-      lap[i] = (Real(8) * faces + corners - Real(56) * v) * (Real(1) / Real(12));  // eq:N31b
-      phi[i] = v;
-    }
-    Real wv[N];
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-      Real ck = K.ca[k];
-#pragma unroll
-      for (int i = 0; i < M; ++i) ck += K.cA[k][i] * phi[i];
-      wv[k] = ck * (Real(1) - ck) * (Real(1) - Real(2) * ck);
-    }
-#pragma unroll
-    for (int i = 0; i < M; ++i) {
-      Real Ci = Real(0);
-#pragma unroll
-      for (int j = 0; j < M; ++j) Ci -= K.lam[i][j] * lap[j];
-#pragma unroll
-      for (int k = 0; k < N; ++k) Ci += K.KH[k][i] * wv[k];
-      sC[sc][i][q][c] = Ci;
-    }
+    chem_node3<N, Real>(
+        K,
+        [&](int i, int dx, int dy, int dz) {
+          return sphi[dz == 0 ? s0 : (dz > 0 ? sU : sD)][i][ty + dy][c + dx];
+        },
+        [&](int i, Real v) { sC[sc][i][q][c] = v; });
   };
   // the C ring rows of a wave: its own (row y0 + w) while w <= nyi, and for
   // waves 0 / 1 rows y0 - 1 / y0 + TY
@@ -372,22 +322,6 @@ __global__ void __launch_bounds__(k3W * TY) k_step3(StepArgs a) {
     }
   };
 
-  // eq:N31a on D3Q15 from an LDS ring: planes s0 (own), sU (z + 1), sD (z - 1)
-  // around LDS column `lane` (2 .. 65)
-  auto grad3 = [&](auto f, int ty, int lane, int s0, int sU, int sD, int i, Real &gx, Real &gy,
-                   Real &gz) {
-    const Real upp = f[sU][i][ty + 1][lane + 1], upm = f[sU][i][ty + 1][lane - 1];
-    const Real ump = f[sU][i][ty - 1][lane + 1], umm = f[sU][i][ty - 1][lane - 1];
-    const Real dpp = f[sD][i][ty + 1][lane + 1], dpm = f[sD][i][ty + 1][lane - 1];
-    const Real dmp = f[sD][i][ty - 1][lane + 1], dmm = f[sD][i][ty - 1][lane - 1];
-    const Real cx = ((upp - upm) + (ump - umm)) + ((dpp - dpm) + (dmp - dmm));
-    const Real cy = ((upp + upm) - (ump + umm)) + ((dpp + dpm) - (dmp + dmm));
-    const Real cz = ((upp + upm) + (ump + umm)) - ((dpp + dpm) + (dmp + dmm));
-    gx = (Real(8) * (f[s0][i][ty][lane + 1] - f[s0][i][ty][lane - 1]) + cx) * (Real(1) / Real(24));
-    gy = (Real(8) * (f[s0][i][ty + 1][lane] - f[s0][i][ty - 1][lane]) + cy) * (Real(1) / Real(24));
-    gz = (Real(8) * (f[sU][i][ty][lane] - f[sD][i][ty][lane]) + cz) * (Real(1) / Real(24));
-  };
-
   // ---- stage C: collide march index mC (interior rows) ----
   // With kLate the NS pulls are issued here and the CH populations of each
   // phase right before its collision, behind a compiler barrier, so only one
@@ -403,145 +337,49 @@ __global__ void __launch_bounds__(k3W * TY) k_step3(StepArgs a) {
     const int cU = gU ? c0 : ring4(mC + dir), cD = gD ? c0 : ring4(mC - dir);
     // lanes past a ragged tile end compute on their (valid) columns and do
     // not store
-    const int ln = col;
+    int ln = col;
     Real phi[M], Cv[M];
-    // (the sums over phases of the gradient terms stay in the state type)
-    Acc rho = KD.ra;
-    Real grs[3] = {Real(0), Real(0), Real(0)}, Fs[3] = {Real(0), Real(0), Real(0)},
-         Js[3] = {Real(0), Real(0), Real(0)};
+    Sums3<Real> S = sums3_begin<N, Real>(KD);
 #pragma unroll
     for (int i = 0; i < M; ++i) {
+      sums3_order(ln, S);
       phi[i] = sphi[s0][i][pr][ln];
       Cv[i] = sC[c0][i][cr][ln];
       Real gp[3], gc[3];
-      grad3(sphi, pr, ln, s0, sU, sD, i, gp[0], gp[1], gp[2]);
-      grad3(sC, cr, ln, c0, cU, cD, i, gc[0], gc[1], gc[2]);
-      rho += KD.rA[i] * phi[i];
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        grs[d] += K.rA[i] * gp[d];
-        Fs[d] += Cv[i] * gp[d];
-        Js[d] += K.Jc[i] * gc[d];
-      }
+      grad_node3<Real>(
+          [&](int dx, int dy, int dz) {
+            return sphi[dz == 0 ? s0 : (dz > 0 ? sU : sD)][i][pr + dy][ln + dx];
+          },
+          gp);
+      grad_node3<Real>(
+          [&](int dx, int dy, int dz) {
+            return sC[dz == 0 ? c0 : (dz > 0 ? cU : cD)][i][cr + dy][ln + dx];
+          },
+          gc);
+      sums3_add<Real>(K, KD, i, phi[i], Cv[i], gp, gc, S);
     }
-    const Acc gr[3] = {grs[0], grs[1], grs[2]}, J[3] = {Js[0], Js[1], Js[2]};
-    Acc F[3] = {Fs[0], Fs[1], Fs[2]};
-    F[0] += rho * KD.gx;
-    F[1] += rho * KD.gy;
-    F[2] += rho * KD.gz;
-    Acc itau, srcg, theta;
-    if (KD.const_tau) {
-      itau = KD.itau_g;
-      srcg = KD.src_g;
-      theta = KD.theta_g;
-    } else {
-      Acc mu = KD.ma;
-#pragma unroll
-      for (int i = 0; i < M; ++i) mu += KD.mA[i] * phi[i];
-      const Acc tm = Acc(3) * mu / rho;  // tau_g - 1/2 (eq:N21_1)
-      itau = Acc(1) / (Acc(0.5) + tm);
-      srcg = Acc(1) - Acc(0.5) * itau;
-      theta = Acc(1) / tm;
-    }
-    const Real(&g)[15] = P.g;  // every use below is promoted to Acc
-    Acc m[3] = {Acc(0), Acc(0), Acc(0)}, sumg = Acc(0);
-#pragma unroll
-    for (int k = 1; k < 15; ++k) {
-      if (ex3(k)) m[0] += Acc(ex3(k)) * g[k];
-      if (ey3(k)) m[1] += Acc(ey3(k)) * g[k];
-      if (ez3(k)) m[2] += Acc(ez3(k)) * g[k];
-      sumg += g[k];
-    }
-    const Acc irho = Acc(1) / rho;
-    Acc u[3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) u[d] = (m[d] + Acc(0.5) * F[d]) * irho;  // eq:N22_1
-    const Acc usq = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
-    const Acc udr = u[0] * gr[0] + u[1] * gr[1] + u[2] * gr[2];
-    // eq:N23 with w_0 = 2/9: c_s^2 / (1 - w_0) = 3/7, rho s_0 = -(1/3) rho |u|^2
-    const Acc p = Acc(3) / Acc(7) * (sumg + Acc(0.5) * udr - Acc(1) / Acc(3) * rho * usq);
-    const Acc uF = u[0] * F[0] + u[1] * F[1] + u[2] * F[2];
-    const Acc Ju = J[0] * u[0] + J[1] * u[1] + J[2] * u[2];
-    // isotropic part of eq:N20_1: u.grad(rho) - tr(T) / (2 c_s^2)
-    const Acc gbase = udr - Acc(1.5) * (Acc(2) * uF + Acc(2) / Acc(3) * udr + theta * Ju);
     if (!lane_int) return;
     const Rsrc wh = row_rsrc(hd, plh, zp), wg = row_rsrc(gd, plg, zp),
                wp = row_rsrc(pvd, plp, zp);
-    // eq:24 with g^eq and G split into the parts even and odd in c_k, each
-    // pair of opposite directions evaluated once
-    const Acc keep = Acc(1) - itau;
-    const Acc e0 = Acc(3) * p - Acc(1.5) * rho * usq;
-#pragma unroll
-    for (int k = 1; k < 15; ++k) {
-      if (opp3(k) < k) continue;
-      const int ko = opp3(k);
-      const Acc cx = Acc(ex3(k)), cy = Acc(ey3(k)), cz = Acc(ez3(k));
-      const Acc w = w3<Acc>(k);
-      const Acc cu = cx * u[0] + cy * u[1] + cz * u[2];
-      const Acc cF = cx * F[0] + cy * F[1] + cz * F[2];
-      const Acc cr = cx * gr[0] + cy * gr[1] + cz * gr[2];
-      const Acc cJ = cx * J[0] + cy * J[1] + cz * J[2];
-      const Acc ev =
-          w * (itau * (e0 + Acc(4.5) * rho * cu * cu) +
-               srcg * (gbase + Acc(4.5) * cu * (Acc(2) * cF + Acc(2) / Acc(3) * cr + theta * cJ)));
-      const Acc od = w * Acc(3) * (itau * rho * cu + srcg * cF);
-      bst<Real, true>(wg, xcu, ybg[1] + (uint32_t)(k - 1) * pb, keep * g[k] + ev + od);
-      bst<Real, true>(wg, xcu, ybg[1] + (uint32_t)(ko - 1) * pb, keep * g[ko] + ev - od);
-    }
-#pragma unroll
-    for (int i = 0; i < M; ++i) {
-      Real phii = phi[i], Cvi = Cv[i];
-      if constexpr (decltype(kLate)::value) {
-        asm volatile("" ::: "memory");
-        pull_phase(mC, i, P);
-        // plane mC's slots of the phi and C rings are rewritten only two
-        // iterations later, so these are the values read above
-        if constexpr (kLean) {
-          phii = sphi[s0][i][pr][ln];
-          Cvi = sC[c0][i][cr][ln];
-        }
-      }
-      const Real pp = P.hi[i];
-      Real ps[3], dd[3];
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        ps[d] = phii * u[d];
-        dd[d] = ps[d] - pp * P.pu[d];  // eq:N27
-      }
-      const Real ec = K.eta_i[i] * Cvi;
-      const Real it = K.itau_i[i], sr = K.src_i[i];
-      // eq:N24 with h^eq (eq:N25) and R_k (eq:N26) split into the parts
-      // even and odd in c_k, per pair of opposite directions
-      const Real keep = Real(1) - it;
-      Real hsum = Real(0);
-#pragma unroll
-      for (int k = 1; k < 15; ++k) {
-        if (opp3(k) < k) continue;
-        const int ko = opp3(k);
-        const Real cx = Real(ex3(k)), cy = Real(ey3(k)), cz = Real(ez3(k));
-        const Real w = w3<Real>(k);
-        const Real ev = it * w * ec;
-        const Real od = w * Real(3) *
-                        (it * (cx * ps[0] + cy * ps[1] + cz * ps[2]) +
-                         sr * (cx * dd[0] + cy * dd[1] + cz * dd[2]));
-        const Real hn = keep * P.h[i][k] + ev + od;
-        const Real ho = keep * P.h[i][ko] + ev - od;
-        hsum += hn + ho;
-        bst<Real, true>(wh, xcu, ybh[1] + (uint32_t)(i * 15 + k) * pb, hn);
-        bst<Real, true>(wh, xcu, ybh[1] + (uint32_t)(i * 15 + ko) * pb, ho);
-      }
-      // phi_i = pp + lo exactly; fl(phi_i) is stored as the new previous
-      // phi and the k = 0 slot keeps (pp + lo - fl(phi_i)) - sum h_k
-      Real lo = P.h[i][0];
-#pragma unroll
-      for (int k = 1; k < 15; ++k) lo += P.h[i][k];
-      const Real bb = phii - pp;
-      const Real err = (pp - (phii - bb)) + (lo - bb);
-      bst<Real, true>(wh, xcu, ybh[1] + (uint32_t)(i * 15) * pb, err - hsum);
-      bst<Real, true>(wp, xcu, ybp + (uint32_t)i * pb, phii);
-    }
-#pragma unroll
-    for (int d = 0; d < 3; ++d) bst<Real, true>(wp, xcu, ybp + (uint32_t)(M + d) * pb, u[d]);
+    collide_node3<N, Real>(
+        K, KD, S, P.g, P.pu,
+        [&](int i, auto collide) {
+          Real phii = phi[i], Cvi = Cv[i];
+          if constexpr (decltype(kLate)::value) {
+            asm volatile("" ::: "memory");
+            pull_phase(mC, i, P);
+            // plane mC's slots of the phi and C rings are rewritten only two
+            // iterations later, so these are the values read above
+            if constexpr (kLean) {
+              phii = sphi[s0][i][pr][ln];
+              Cvi = sC[c0][i][cr][ln];
+            }
+          }
+          collide(P.h[i], P.hi[i], phii, Cvi);
+        },
+        [&](int plane, Real v) { bst<Real, true>(wg, xcu, ybg[1] + (uint32_t)plane * pb, v); },
+        [&](int plane, Real v) { bst<Real, true>(wh, xcu, ybh[1] + (uint32_t)plane * pb, v); },
+        [&](int plane, Real v) { bst<Real, true>(wp, xcu, ybp + (uint32_t)plane * pb, v); });
   };
 
   // March: iteration j pulls plane mA = j - 2, computes C of mA - 1 and
@@ -651,6 +489,16 @@ hipError_t launch_phi3(int precision, const StepArgs &a, dim3 grid, hipStream_t 
   return hipGetLastError();
 }
 
+// LDS asked for beyond the rings of an FP32 workgroup so that two of them
+// fill a compute unit: three (at N <= 3 registers and rings would allow
+// them) march more tiles at once, each over fewer planes (256^3 N = 2 996 us
+// a step against 1131, 192^3 446 against 485; N = 3 256^3 1584 against 1787,
+// 192^3 710 against 767).
+template <int N, int TY>
+constexpr int pad3_bytes() {
+  return std::max(0, 56 * 1024 - lds3_bytes<N, TY>(4));
+}
+
 template <int N, int TY>
 hipError_t launch3(int precision, const StepArgs &a, int nblocks, hipStream_t st) {
   if (precision == 64) {
@@ -660,7 +508,8 @@ hipError_t launch3(int precision, const StepArgs &a, int nblocks, hipStream_t st
       return hipErrorInvalidValue;
   } else {
     if constexpr (lds3_bytes<N, TY>(4) <= 160 * 1024)
-      hipLaunchKernelGGL((k_step3<N, float, TY>), dim3(nblocks), dim3(k3W * TY), 0, st, a);
+      hipLaunchKernelGGL((k_step3<N, float, TY>), dim3(nblocks), dim3(k3W * TY),
+                         (pad3_bytes<N, TY>()), st, a);
     else
       return hipErrorInvalidValue;
   }
@@ -676,26 +525,41 @@ int occ3(int precision) {
       e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_step3<N, double, TY>, k3W * TY, 0);
   } else {
     if constexpr (lds3_bytes<N, TY>(4) <= 160 * 1024)
-      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_step3<N, float, TY>, k3W * TY, 0);
+      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_step3<N, float, TY>, k3W * TY,
+                                                       (pad3_bytes<N, TY>()));
   }
   return e == hipSuccess ? nb : 0;
 }
 
 }  // namespace
 
-// Interior rows of a tile = waves of a workgroup: 4 in FP32, where two or
+// The node kernels (0) take lattices of up to 900 000 nodes, where the
+// marching tiles leave compute units idle, and those whose rows fill less
+// than 77% of the marching kernel's 64-column tiles; the marching kernel the
+// others, where it moves 2 (N - 1) words a node less.  A step, node /
+// marching: 64^3 FP32 N = 3 32 / 69 us, FP64 N = 4 84 / 182; 100 x 84 x 60
+// FP64 N = 4 187 / 246; 96^3 FP32 N = 3 106 / 120; 72 x 160^2 FP64 N = 3
+// 488 / 537; 96 x 200^2 FP64 N = 3 886 / 914; 112^3 FP32 N = 3 176 / 166;
+// 128^3 237 / 217; 200^3 (78%) FP32 N = 3 1016 / 952.
+// Interior rows of a marching tile = waves of a workgroup: 4 in FP32, where two or
 // more 4-row workgroups per CU measured faster than one of 8 (256^3: N = 3
 // 48.3% against 44.9% of the HBM roofline, N = 5 38.2% against 35.6%); in
 // FP64 8 for N <= 4 (N = 3: 44.9% against 43.9%; N = 4, with the leaner
 // register use of that variant: 45.0% against 40.7%) and 4 for N = 5, where
-// FP64 rings of 8 rows would not fit in LDS.  NPLBM_TY3 = 4 or 8 overrides.
-int step3_ty(int N, int precision) {
+// FP64 rings of 8 rows would not fit in LDS.  NPLBM_TY3 = 0, 4 or 8
+// overrides; NPLBM_TARGET_BLOCKS asks for the marching kernel.
+int step3_ty(int N, int precision, int nx, int ny, int nz) {
   if (const char *e = std::getenv("NPLBM_TY3")) {
     const int t = std::atoi(e);
+    if (t == 0) return 0;
     const int bytes = precision == 64 ? 8 : 4;
     const int lds = (k3PR * (t + 4) + k3CR * (t + 2)) * (N - 1) * k3L * bytes;
     if (t == 4 || (t == 8 && lds <= 160 * 1024)) return t;
   }
+  const int tiles = (nx + k3W - 1) / k3W * k3W;
+  if (std::getenv("NPLBM_TARGET_BLOCKS") == nullptr &&
+      ((int64_t)nx * ny * nz <= 900000 || nx * 100 < tiles * 77))
+    return 0;
   return precision == 64 && N <= 4 ? 8 : 4;
 }
 
@@ -716,6 +580,7 @@ hipError_t launch_step3(int N, int precision, int ty, const StepArgs &a, int nbl
     default: return hipErrorInvalidValue;
   }
   if (e != hipSuccess) return e;
+  if (ty == 0) return launch_step3n(N, precision, a, nx, ny, nz, st);
   if (ty == 4) {
     switch (N) {
       case 2: return launch3<2, 4>(precision, a, nblocks, st);
