@@ -405,6 +405,14 @@ __global__ void k_diag_final(const double *partials, int nq, int nblk, int qmax,
   if (ln == 0) out[q] = r;
 }
 
+// one thread per slot
+__global__ void k_progress(DomDesc *descs, Progress p) {
+  const int j = threadIdx.x;
+  if (p.left[j] < 0) return;
+  descs[p.base + j].parity0 = (p.odd[j / 32] >> (j % 32)) & 1;
+  descs[p.base + j].steps_left = p.left[j];
+}
+
 // one 16-byte element per thread and a grid covering the buffer: the
 // fastest plain copy pattern measured on gfx950 (~6.2 TB/s read + write)
 __global__ void k_copy16(uint4 *__restrict__ dst, const uint4 *__restrict__ src, int64_t n16) {
@@ -540,6 +548,11 @@ hipError_t launch_laplace(const double *p, int nx, int ny, int nz, double xc, do
   hipLaunchKernelGGL(k_laplace_partial, dim3(nblk), dim3(kThreads), 0, st, p, nx, ny, nz, xc, yc,
                      zc, r_in, r_out, partials);
   hipLaunchKernelGGL(k_laplace_final, dim3(1), dim3(256), 0, st, partials, nblk, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_progress(DomDesc *descs, const Progress &p, hipStream_t st) {
+  hipLaunchKernelGGL(k_progress, dim3(1), dim3(kProgressSlots), 0, st, descs, p);
   return hipGetLastError();
 }
 

@@ -230,6 +230,17 @@ hipError_t launch_macro3(const DomDesc *dd_dev, const DomDesc &dd, int precision
                          double *phi, double *rho, double *C, double *c_out, double *u_out,
                          double *p_out, hipStream_t st);
 
+// Serving: where each resident domain of up to kProgressSlots slots stands at
+// the start of a quantum (by value: no copy from host memory).  left[j] < 0:
+// slot base + j is free.
+constexpr int kProgressSlots = 256;
+struct Progress {
+  int32_t base;
+  int32_t left[kProgressSlots];          // steps left
+  uint32_t odd[kProgressSlots / 32];     // bit j: an odd number of steps is done
+};
+hipError_t launch_progress(DomDesc *descs, const Progress &p, hipStream_t st);
+
 // Initialisation: phi (double, (N-1) planes of nx*ny) is computed from c,
 // then C from phi, then h^eq / g^eq written in pull layout.
 // phi_i = P1[i] c_i + PN[i] c_N + P0[i] (eq:N12 inverted).
