@@ -21,7 +21,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 SOURCES = ["step_kernel.hip", "step_kernel_mixed.hip", "step_kernel_remark1.hip",
            "tile_kernel.hip", "tile_kernel_mixed.hip", "tile_kernel_remark1.hip",
-           "step3d_kernel.hip", "step3n_kernel.hip", "aux_kernels.hip", "aux3d_kernels.hip", "nplbm_host.cpp",
+           "step3d_kernel.hip", "step3n_kernel.hip", "aux_kernels.hip", "aux3d_kernels.hip", "nplbm_host.cpp", "host_copy.cpp",
            "nplbm_api.cpp", "nplbm_server.cpp"]
 
 COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

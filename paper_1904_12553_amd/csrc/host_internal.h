@@ -47,6 +47,16 @@ struct Layout {
 Layout plan_layout(const nplbm_params *p);
 int single_domain_target(const nplbm_params *p);
 
+// Copy device memory to a host array behind the work enqueued on st, and wait
+// for it (host_copy.cpp).
+hipError_t copy_to_host(void *dst, const void *src, size_t bytes, hipStream_t st);
+// Domains and servers count themselves (+1 / -1) as users of the pinned
+// buffers behind copy_to_host.
+void copy_users(int change);
+// first node whose N fractions do not sum to 1 within 1e-9 (n if none)
+size_t first_bad_sum(const double *c, int N, size_t n);
+bool all_finite(const double *v, size_t n);
+
 // default padding of every population plane (64 elements of 4 bytes)
 constexpr size_t kPlanePadBytes = 256;
 int64_t plane_pad(size_t elem);

@@ -36,6 +36,8 @@ struct nplbm_domain {
   // graphs of 2^j consecutive steps (j = 0..kGraphLevels-1) starting at an
   // even (index 0) or odd (index 1) time step
   hipGraphExec_t graph[2][7] = {{nullptr}};
+  nplbm_domain() { copy_users(1); }
+  ~nplbm_domain() { copy_users(-1); }
 };
 
 namespace {
@@ -139,11 +141,8 @@ int readback(nplbm_domain *d, bool want_up) {
 }
 
 int copy_out(nplbm_domain *d, void *dst, size_t off, size_t bytes) {
-  hipError_t e = hipMemcpyAsync(dst, d->base + off, bytes, hipMemcpyDeviceToHost, d->stream);
-  if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync D2H");
-  e = hipStreamSynchronize(d->stream);
-  if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-  return NPLBM_OK;
+  const hipError_t e = copy_to_host(dst, d->base + off, bytes, d->stream);
+  return e == hipSuccess ? NPLBM_OK : hip_fail(e, "device to host copy");
 }
 
 bool check_domain(const nplbm_domain *d) { return d != nullptr && d->base != nullptr; }
@@ -305,19 +304,17 @@ int nplbm_set_fields(nplbm_domain *d, const double *c, const double *u) {
   const int N = d->p.N;
   const size_t n = nnodes(d);
   const int nu = d->d3 ? 3 : 2;
-  for (size_t id = 0; id < n; ++id) {
+  const size_t id = first_bad_sum(c, N, n);
+  if (id < n) {
     double s = 0.0;
     for (int k = 0; k < N; ++k) {
       const double v = c[(size_t)k * n + id];
       if (!std::isfinite(v)) return fail(NPLBM_EINVAL, "c is not finite at node %zu", id);
       s += v;
     }
-    if (std::fabs(s - 1.0) > 1e-9)
-      return fail(NPLBM_EINVAL, "sum_k c_k = %.17g at node %zu (must be 1)", s, id);
+    return fail(NPLBM_EINVAL, "sum_k c_k = %.17g at node %zu (must be 1)", s, id);
   }
-  if (u)
-    for (size_t id = 0; id < nu * n; ++id)
-      if (!std::isfinite(u[id])) return fail(NPLBM_EINVAL, "u is not finite");
+  if (u && !all_finite(u, nu * n)) return fail(NPLBM_EINVAL, "u is not finite");
   hipError_t e = hipMemcpyAsync(dptr(d, d->L.c), c, (size_t)N * n * 8, hipMemcpyHostToDevice,
                                 d->stream);
   if (e == hipSuccess && u)
@@ -510,13 +507,9 @@ int nplbm_get_state(nplbm_domain *d, void *host, int64_t *time_out) {
   (void)s;
   (void)M;
   unsigned char *o = static_cast<unsigned char *>(host);
-  hipError_t e = hipMemcpyAsync(o, d->base + d->L.h[par], hb, hipMemcpyDeviceToHost, d->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(o + hb, d->base + d->L.g[par], gb, hipMemcpyDeviceToHost, d->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(o + hb + gb, d->base + d->L.prev[par], pb, hipMemcpyDeviceToHost,
-                       d->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(d->stream);
+  hipError_t e = copy_to_host(o, d->base + d->L.h[par], hb, d->stream);
+  if (e == hipSuccess) e = copy_to_host(o + hb, d->base + d->L.g[par], gb, d->stream);
+  if (e == hipSuccess) e = copy_to_host(o + hb + gb, d->base + d->L.prev[par], pb, d->stream);
   if (e != hipSuccess) return hip_fail(e, "state copy");
   if (time_out) *time_out = d->t;
   return NPLBM_OK;

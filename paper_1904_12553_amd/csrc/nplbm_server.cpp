@@ -21,7 +21,9 @@
 #include <cstring>
 #include <deque>
 #include <map>
+#include <memory>
 #include <mutex>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -62,8 +64,9 @@ struct Req {
   unsigned char *base = nullptr;
   int slot = -1;
   DomDesc desc{};
-  // results
-  std::vector<double> c_out, u_out, p_out;
+  // results: the device planes c, u and p as they lie, from L.c on (not
+  // cleared first)
+  std::unique_ptr<double[]> out;
 };
 
 }  // namespace
@@ -102,6 +105,8 @@ struct nplbm_server {
   // the first submission / last completion times (under the mutex)
   std::vector<double> lat;
   double t_first = -1.0, t_last = 0.0;
+  nplbm_server() { copy_users(1); }
+  ~nplbm_server() { copy_users(-1); }
 };
 
 namespace {
@@ -351,23 +356,19 @@ int retire(nplbm_server *s, Req *r) {
   const size_t n = (size_t)r->p.nx * r->p.ny;
   const int par = (int)(r->done_steps & 1);
   DomDesc D = r->desc;
-  r->c_out.resize((size_t)r->p.N * n);
-  r->u_out.resize(2 * n);
-  r->p_out.resize(n);
+  const size_t bytes = r->L.p + n * 8 - r->L.c;
+  r->out.reset(new (std::nothrow) double[bytes / 8]);
+  if (!r->out) {
+    release(s, r);
+    s->dirty = true;
+    return fail(NPLBM_ENOMEM, "host memory for the results of %zu nodes", n);
+  }
   auto dp = [&](size_t off) { return reinterpret_cast<double *>(r->base + off); };
   hipError_t e = launch_macro(s->descs_dev + r->slot, D, r->p.precision, par, dp(r->L.phi),
                               dp(r->L.rho), dp(r->L.C), dp(r->L.c), dp(r->L.u), dp(r->L.p),
                               r->L.q ? dp(r->L.q) : nullptr, s->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(r->c_out.data(), dp(r->L.c), r->c_out.size() * 8, hipMemcpyDeviceToHost,
-                       s->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(r->u_out.data(), dp(r->L.u), r->u_out.size() * 8, hipMemcpyDeviceToHost,
-                       s->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(r->p_out.data(), dp(r->L.p), r->p_out.size() * 8, hipMemcpyDeviceToHost,
-                       s->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
+  if (e == hipSuccess) e = copy_to_host(r->out.get(), dp(r->L.c), bytes, s->stream);
+  if (e != hipSuccess) (void)hipStreamSynchronize(s->stream);
   release(s, r);
   s->dirty = true;
   if (e != hipSuccess) return hip_fail(e, "retire");
@@ -435,13 +436,10 @@ int nplbm_submit(nplbm_server *s, const nplbm_params *p, const double *c, const 
     return fail(NPLBM_ETOOBIG, "request needs %zu bytes, budget is %zu", b, s->budget);
   }
   const size_t n = (size_t)p->nx * p->ny;
-  for (size_t id = 0; id < n; ++id) {
-    double sum = 0.0;
-    for (int k = 0; k < N; ++k) sum += c[(size_t)k * n + id];
-    if (!(std::fabs(sum - 1.0) <= 1e-9)) {
-      delete r;
-      return fail(NPLBM_EINVAL, "sum_k c_k != 1 at node %zu", id);
-    }
+  const size_t id = first_bad_sum(c, N, n);
+  if (id < n) {
+    delete r;
+    return fail(NPLBM_EINVAL, "sum_k c_k != 1 at node %zu", id);
   }
   r->c.assign(c, c + (size_t)N * n);
   if (u) {
@@ -572,9 +570,11 @@ int nplbm_result(nplbm_server *s, uint64_t ticket, double *c, double *u, double 
     if (r->state != 2) return fail(NPLBM_ESTATE, "request not finished (state %d)", r->state);
     s->reqs.erase(it);
   }
-  if (c) std::memcpy(c, r->c_out.data(), r->c_out.size() * 8);
-  if (u) std::memcpy(u, r->u_out.data(), r->u_out.size() * 8);
-  if (p) std::memcpy(p, r->p_out.data(), r->p_out.size() * 8);
+  const size_t n = (size_t)r->p.nx * r->p.ny;
+  auto plane = [&](size_t off) { return r->out.get() + (off - r->L.c) / 8; };
+  if (c) std::memcpy(c, plane(r->L.c), (size_t)r->p.N * n * 8);
+  if (u) std::memcpy(u, plane(r->L.u), 2 * n * 8);
+  if (p) std::memcpy(p, plane(r->L.p), n * 8);
   if (admit_s) *admit_s = r->t_admit - r->t_submit;
   if (done_s) *done_s = r->t_done - r->t_submit;
   delete r;
