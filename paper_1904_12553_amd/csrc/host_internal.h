@@ -70,7 +70,8 @@ int64_t state_pitch(const nplbm_params *p);
 int step_scheme(const nplbm_params *p);
 // geometry of one 2-D domain: step_geom, and the tile kernel where its rule
 // picks it
-StepGeom domain_geom(const nplbm_params *p);
+// (shared: its launches hold the tiles of other domains too)
+StepGeom domain_geom(const nplbm_params *p, bool shared);
 int resident_step_blocks(int N, int precision, int scheme);
 void build_strips(int nx, int ny, int dom, const StepGeom &geom, std::vector<StripDesc> &out,
                   int target = 0);

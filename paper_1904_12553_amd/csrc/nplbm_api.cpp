@@ -274,7 +274,7 @@ int nplbm_create(const nplbm_params *p, void *stream, void *device_mem, size_t d
     if (const char *env = std::getenv("NPLBM_TARGET_BLOCKS")) target = std::atoi(env);
     build_tiles3(p->nx, p->ny, p->nz, 0, std::max(d->ty, 4), target, strips);
   } else {
-    d->geom = domain_geom(p);
+    d->geom = domain_geom(p, false);
     build_strips(p->nx, p->ny, 0, d->geom, strips, single_domain_target(p));
   }
   xcd_order(strips);

@@ -496,10 +496,16 @@ StepGeom step_geom(int N, int precision, int scheme) {
 // Tiles have 8 rows; 4 in FP64 with few phases while that still gives each
 // compute unit at most one tile (160^2 N = 3: 6.1 against 7.1 us; two tiles
 // on some units at 180^2 were slower, as was mixed N = 5; FP32 measures the
-// same or slower with 4).
+// same or slower with 4).  A domain alone in its launches takes 12 rows where
+// that gives each compute unit one tile and 8 rows would give some two: a
+// unit with two tiles takes longer than one with a taller tile, though the
+// others have less to do (256 x 300, 304 against 200 tiles: N = 2 FP32 5.9
+// against 5.7 us, N = 5 FP32 12.4 against 11.1, N = 8 FP32 20.8 against 17.4,
+// N = 3 FP64 11.5 against 10.1; with 12 rows on 320 x 320, 270 tiles, N = 5
+// FP32 takes 18.6 us against 13.3).
 // A set NPLBM_TX, NPLBM_BW, NPLBM_MIN_STRIP_H or NPLBM_TARGET_BLOCKS asks for
 // strips; NPLBM_TILE = 0 (strips), 4 or 8 overrides.
-StepGeom domain_geom(const nplbm_params *p) {
+StepGeom domain_geom(const nplbm_params *p, bool shared) {
   const int scheme = step_scheme(p);
   StepGeom g = step_geom(p->N, p->precision, scheme);
   for (const char *e : {"NPLBM_TX", "NPLBM_BW", "NPLBM_MIN_STRIP_H", "NPLBM_TARGET_BLOCKS"})
@@ -507,9 +513,12 @@ StepGeom domain_geom(const nplbm_params *p) {
   const int64_t rows = p->ny;
   const int64_t state = 2 * 10 * (int64_t)p->N * (p->precision / 8) * state_pitch(p) * rows;
   if (state <= kCacheBytes) {
-    const int64_t tiles4 = (int64_t)((p->nx + kTileWidth - 1) / kTileWidth) * ((rows + 3) / 4);
+    const int64_t cols = (p->nx + kTileWidth - 1) / kTileWidth;
+    auto one_each = [&](int ty) { return cols * ((rows + ty - 1) / ty) <= kComputeUnits; };
     const bool few = p->precision == 64 && p->N <= (scheme == kSchemeCentral ? 5 : 3);
-    g.ty = few && tiles4 <= kComputeUnits ? 4 : 8;
+    g.ty = few && one_each(4) ? 4 : 8;
+    if (!shared && !one_each(8) && one_each(12) && tile12_built(p->N, p->precision / 8, scheme))
+      g.ty = 12;
   }
   if (const char *e = std::getenv("NPLBM_TILE")) {
     const int t = std::atoi(e);

@@ -24,8 +24,8 @@ struct StepGeom {
   int ty = 0;  // > 0: the domain is stepped by the tile kernel, tiles of this many rows
 };
 // Tiles of the tile kernel are kTileWidth columns (one 128-byte line in FP32)
-// by ty = 8 rows, or 4 (built for FP64 up to kTile4MaxN phases), one thread
-// per node.
+// by ty = 8 rows, 4 (built for FP64 up to kTile4MaxN phases) or 12
+// (tile12_built), one thread per node.
 constexpr int kTileWidth = 32;
 constexpr int kTile4MaxN = 5;
 constexpr int kComputeUnits = 256;                    // of the chip
@@ -40,6 +40,13 @@ constexpr int kGradMixed = 1;
 constexpr int kSchemeCentral = 0;
 constexpr int kSchemeMixed = 1;
 constexpr int kSchemeRemark1 = 2;
+// Whether the tile kernel is built with 12 rows: its 24 waves, helpers
+// included, leave 168 registers a thread, which more phases spill (FP64 N = 4
+// with the mixed scheme already by 84 bytes: 16.4 us a step on 256 x 300, no
+// faster than with 8 rows).
+constexpr bool tile12_built(int N, int bytes, int scheme) {
+  return N * bytes <= 32 && !(N * bytes == 32 && bytes == 8 && scheme == kSchemeMixed);
+}
 // Whether every lane of a step-kernel row owns an interior column (the
 // x-halo phi then comes from lanes that each pull one population of a halo
 // node): the central scheme in FP32 for N <= 5 and in FP64 for N <= 3, the

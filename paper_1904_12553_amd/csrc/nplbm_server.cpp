@@ -211,7 +211,7 @@ int rebuild(nplbm_server *s) {
           for (int slot = 0; slot < s->max_slots; ++slot) {
             Req *r = s->slots[slot];
             if (!r || r->p.N != N || r->p.precision != prec || step_scheme(&r->p) != sch) continue;
-            const StepGeom rg = domain_geom(&r->p);
+            const StepGeom rg = domain_geom(&r->p, true);
             if (rg.ty != ty) continue;
             const int64_t b = 2 * (int64_t)(r->L.gbytes[0] + r->L.gbytes[1] + r->L.gbytes[2]);
             if (bytes + b > kCacheBytes) close();

@@ -436,6 +436,19 @@ hipError_t launch_t(const TileArgs &a, int nblocks, hipStream_t st) {
   return hipGetLastError();
 }
 
+// 12-row tiles are launched alone on their compute units, so always with
+// helper threads.
+template <int N, typename Real>
+hipError_t launch_12(const TileArgs &a, int nblocks, hipStream_t st) {
+  if constexpr (tile12_built(N, (int)sizeof(Real), NPL_GS)) {
+    hipLaunchKernelGGL((k_tile<N, Real, 12, NPL_GS, true>), dim3(nblocks), dim3(kTW * 12 * 2), 0,
+                       st, a);
+    return hipGetLastError();
+  } else {
+    return hipErrorInvalidValue;
+  }
+}
+
 template <int N>
 hipError_t launch_n(int precision, int ty, const TileArgs &a, int nblocks, hipStream_t st) {
   if (ty == 4) {
@@ -443,6 +456,9 @@ hipError_t launch_n(int precision, int ty, const TileArgs &a, int nblocks, hipSt
       if (precision == 64) return launch_t<N, double, 4>(a, nblocks, st);
     return hipErrorInvalidValue;
   }
+  if (ty == 12)
+    return precision == 64 ? launch_12<N, double>(a, nblocks, st)
+                           : launch_12<N, float>(a, nblocks, st);
   if (ty != 8) return hipErrorInvalidValue;
   return precision == 64 ? launch_t<N, double, 8>(a, nblocks, st)
                          : launch_t<N, float, 8>(a, nblocks, st);

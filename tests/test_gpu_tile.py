@@ -55,3 +55,22 @@ def test_tiles_equal_strips_and_oracle(N, scheme, nx, ny):
                 assert all(np.array_equal(a, b) for a, b in zip(got, strips)), (precision, tile)
             if precision == 64:
                 assert max(maxabs(a, b) for a, b in zip(got, o)) < 1e-10
+
+
+@pytest.mark.parametrize("nx,ny", [(250, 261), (400, 193), (512, 192), (20, 3001)])
+@pytest.mark.parametrize("scheme", list(SCHEMES))
+@pytest.mark.parametrize("N", [2, 4, 5, 8])
+def test_twelve_row_tiles_equal_strips(N, scheme, nx, ny):
+    """Lattices that 8-row tiles give more than one tile per compute unit and
+    12-row tiles at most one (the largest exactly 256): last tiles of 9, 1,
+    12 and 1 rows, ragged and whole columns, one column.  Bitwise, as above."""
+    steps = 6
+    sig = {"sigma_range": (0.95e-3, 1.05e-3)} if N > 5 else {}
+    for wall in (False, True):
+        w = W.random_smooth(N, nx, ny, seed=900 + N + nx + wall, wall_y=wall,
+                            accept=oracle_accepts, **sig)
+        print(f"case tall tile N={N} {scheme} {nx}x{ny} wall={wall}", flush=True)
+        for precision in (64, 32):
+            strips = _macro(w, precision, steps, "0", **SCHEMES[scheme])
+            got = _macro(w, precision, steps, None, **SCHEMES[scheme])
+            assert all(np.array_equal(a, b) for a, b in zip(got, strips)), precision
