@@ -161,31 +161,48 @@ struct GradSums {
   Real grs, gys, Fxs, Fys, Jxs, Jys;
 };
 
-// Both collisions of one node.  phi, Cv: order parameters and chemical
-// potentials; G: the sums above; divx, divy: -div(J~ u) of Remark 1 (0
-// otherwise); hphase(i) names phase i's pulled CH populations (element 0 the
-// stored deviation of h_0), hi the previous phi, g[1..8] and pu the pulled NS
-// populations and previous u.  sg(plane, v), sh(plane, v), sp(plane, v)
-// store into the NS, CH and previous-step groups.
-template <int N, typename Real, bool kR1, typename HP, typename SG, typename SH, typename SP>
-__device__ __forceinline__ void collide_node(
-    const NPL_CONST Consts<Real> &K, const NPL_CONST Consts<double> &KD,
-    const Real (&phi)[N - 1], const Real (&Cv)[N - 1], const GradSums<Real> &G, Acc divx,
-    Acc divy, HP hphase, const Real (&hi)[N - 1], const Real (&gin)[9],
-    const Real (&pu)[2], SG sg, SH sh, SP sp) {
-  constexpr int M = N - 1;
-  Acc rho = KD.ra;
+// Density, force and velocity of a node.
+struct NodeFlow {
+  Acc rho, irho, Fx, Fy, ux, uy;
+};
+
+// phi: order parameters; G: the sums above; divx, divy: -div(J~ u) of
+// Remark 1 (0 otherwise); gin[1..8] the pulled NS populations.
+template <int N, typename Real, bool kR1>
+__device__ __forceinline__ NodeFlow flow_node(const NPL_CONST Consts<double> &KD,
+                                              const Real (&phi)[N - 1], const GradSums<Real> &G,
+                                              Acc divx, Acc divy, const Real (&gin)[9]) {
+  NodeFlow f;
+  f.rho = KD.ra;
 #pragma unroll
-  for (int i = 0; i < M; ++i) rho += KD.rA[i] * phi[i];
-  const Acc grx = G.grs, gry = G.gys, Jx = G.Jxs, Jy = G.Jys;
-  Acc Fx = G.Fxs, Fy = G.Fys;
-  Fx += rho * KD.gx;
-  Fy += rho * KD.gy;
+  for (int i = 0; i < N - 1; ++i) f.rho += KD.rA[i] * phi[i];
+  f.Fx = G.Fxs;
+  f.Fy = G.Fys;
+  f.Fx += f.rho * KD.gx;
+  f.Fy += f.rho * KD.gy;
   if constexpr (kR1) {
-    Fx -= divx;
-    Fy -= divy;
+    f.Fx -= divx;
+    f.Fy -= divy;
   }
-  const Acc irho = Acc(1) / rho;
+  f.irho = Acc(1) / f.rho;
+  Acc g[9];
+#pragma unroll
+  for (int k = 1; k < 9; ++k) g[k] = gin[k];
+  const Acc mx = (g[1] - g[3]) + (g[5] - g[6]) + (g[8] - g[7]);
+  const Acc my = (g[2] - g[4]) + (g[5] + g[6]) - (g[7] + g[8]);
+  f.ux = (mx + Acc(0.5) * f.Fx) * f.irho;  // eq:N22_1
+  f.uy = (my + Acc(0.5) * f.Fy) * f.irho;
+  return f;
+}
+
+// NS collision of a node; sg(plane, v) stores into the NS group.
+template <int N, typename Real, bool kR1, typename SG>
+__device__ __forceinline__ void collide_ns(const NPL_CONST Consts<double> &KD,
+                                           const Real (&phi)[N - 1], const GradSums<Real> &G,
+                                           const NodeFlow &f, const Real (&gin)[9], SG sg) {
+  constexpr int M = N - 1;
+  const Acc rho = f.rho, irho = f.irho, Fx = f.Fx, Fy = f.Fy, ux = f.ux, uy = f.uy;
+  const Acc grx = G.grs, gry = G.gys, Jx = G.Jxs, Jy = G.Jys;
   Acc itau, srcg, theta;
   if (KD.const_tau) {
     itau = KD.itau_g;
@@ -207,10 +224,6 @@ __device__ __forceinline__ void collide_node(
   Acc g[9];
 #pragma unroll
   for (int k = 1; k < 9; ++k) g[k] = gin[k];
-  const Acc mx = (g[1] - g[3]) + (g[5] - g[6]) + (g[8] - g[7]);
-  const Acc my = (g[2] - g[4]) + (g[5] + g[6]) - (g[7] + g[8]);
-  const Acc ux = (mx + Acc(0.5) * Fx) * irho;  // eq:N22_1
-  const Acc uy = (my + Acc(0.5) * Fy) * irho;
   Acc sumg = g[1];
 #pragma unroll
   for (int k = 2; k < 9; ++k) sumg += g[k];
@@ -244,44 +257,64 @@ __device__ __forceinline__ void collide_node(
     sg(k - 1, (Real)(keep * g[k] + ev + od));
     sg(ko - 1, (Real)(keep * g[ko] + ev - od));
   }
-  // CH collisions
+}
+
+// CH collision of one phase of a node: phi, C its order parameter and chemical
+// potential, pp its previous order parameter, h its pulled populations
+// (element 0 the stored deviation of h_0), ux, uy the velocity and pu the
+// previous one.  sh(plane, v) stores into the CH group, sp(i, v) into the
+// previous-step group.
+template <typename Real, typename SH, typename SP>
+__device__ __forceinline__ void collide_ch(const NPL_CONST Consts<Real> &K, int i, Real phi,
+                                           Real C, Acc ux, Acc uy, Real pp, const Real (&pu)[2],
+                                           const Real (&h)[9], SH sh, SP sp) {
+  const Real psx = phi * ux, psy = phi * uy;
+  const Real dx = psx - pp * pu[0], dy = psy - pp * pu[1];  // eq:N27
+  const Real ec = K.eta_i[i] * C;
+  const Real it = K.itau_i[i], sr = K.src_i[i];
+  // h* = (1 - 1/tau_i) h + h^eq / tau_i + R_k with h^eq (eq:N25) and R_k
+  // (eq:N26) split into the parts even and odd in c_k, per pair of
+  // opposite directions
+  const Real kp = Real(1) - it;
+  Real hsum = Real(0);
 #pragma unroll
-  for (int i = 0; i < M; ++i) {
-    const Real(&h)[9] = hphase(i);
-    const Real pp = hi[i];  // phi_i of the previous step (stored)
-    const Real psx = phi[i] * ux, psy = phi[i] * uy;
-    const Real dx = psx - pp * pu[0], dy = psy - pp * pu[1];  // eq:N27
-    const Real ec = K.eta_i[i] * Cv[i];
-    const Real it = K.itau_i[i], sr = K.src_i[i];
-    // h* = (1 - 1/tau_i) h + h^eq / tau_i + R_k with h^eq (eq:N25) and R_k
-    // (eq:N26) split into the parts even and odd in c_k, per pair of
-    // opposite directions
-    const Real kp = Real(1) - it;
-    Real hsum = Real(0);
-#pragma unroll
-    for (int k = 1; k < 9; ++k) {
-      if (oppk(k) < k) continue;
-      const int ko = oppk(k);
-      const Real w = wk<Real>(k);
-      const Real ev = it * w * ec;
-      const Real od = w * Real(3) * (it * cdot(k, psx, psy) + sr * cdot(k, dx, dy));
-      const Real hn = kp * h[k] + ev + od;
-      const Real ho = kp * h[ko] + ev - od;
-      hsum += hn + ho;
-      sh(i * 9 + k, hn);
-      sh(i * 9 + ko, ho);
-    }
-    // phi_i = hi + lo exactly; phi[i] = fl(hi + lo) is stored as the new
-    // previous phi and the k = 0 slot keeps (hi + lo - phi[i]) - sum h_k
-    // (error-free two-sum for the rounding part).
-    const Real lo = lo_sum(h);
-    const Real bb = phi[i] - pp;
-    const Real err = (pp - (phi[i] - bb)) + (lo - bb);
-    sh(i * 9, err - hsum);
-    sp(i, phi[i]);
+  for (int k = 1; k < 9; ++k) {
+    if (oppk(k) < k) continue;
+    const int ko = oppk(k);
+    const Real w = wk<Real>(k);
+    const Real ev = it * w * ec;
+    const Real od = w * Real(3) * (it * cdot(k, psx, psy) + sr * cdot(k, dx, dy));
+    const Real hn = kp * h[k] + ev + od;
+    const Real ho = kp * h[ko] + ev - od;
+    hsum += hn + ho;
+    sh(i * 9 + k, hn);
+    sh(i * 9 + ko, ho);
   }
-  sp(M, (Real)ux);
-  sp(M + 1, (Real)uy);
+  // phi_i = pp + lo exactly; phi = fl(pp + lo) is stored as the new
+  // previous phi and the k = 0 slot keeps (pp + lo - phi) - sum h_k
+  // (error-free two-sum for the rounding part).
+  const Real lo = lo_sum(h);
+  const Real bb = phi - pp;
+  const Real err = (pp - (phi - bb)) + (lo - bb);
+  sh(i * 9, err - hsum);
+  sp(i, phi);
+}
+
+// Both collisions of one node: hphase(i) names phase i's pulled CH
+// populations, hi the previous phi.
+template <int N, typename Real, bool kR1, typename HP, typename SG, typename SH, typename SP>
+__device__ __forceinline__ void collide_node(
+    const NPL_CONST Consts<Real> &K, const NPL_CONST Consts<double> &KD,
+    const Real (&phi)[N - 1], const Real (&Cv)[N - 1], const GradSums<Real> &G, Acc divx,
+    Acc divy, HP hphase, const Real (&hi)[N - 1], const Real (&gin)[9],
+    const Real (&pu)[2], SG sg, SH sh, SP sp) {
+  const NodeFlow f = flow_node<N, Real, kR1>(KD, phi, G, divx, divy, gin);
+  collide_ns<N, Real, kR1>(KD, phi, G, f, gin, sg);
+#pragma unroll
+  for (int i = 0; i < N - 1; ++i)
+    collide_ch<Real>(K, i, phi[i], Cv[i], f.ux, f.uy, hi[i], pu, hphase(i), sh, sp);
+  sp(N - 1, (Real)f.ux);
+  sp(N, (Real)f.uy);
 }
 
 }  // namespace nplbm

@@ -493,16 +493,18 @@ StepGeom step_geom(int N, int precision, int scheme) {
 // kernel, which reads every population once, is faster (768^2 N = 3 FP64,
 // 283 MB, 64 against 76, but 1024^2 N = 3 FP64 116 against 100, N = 5 FP32
 // 119 against 100, 768^2 N = 4 FP64 96 against 87).
-// Tiles have 8 rows; 4 in FP64 with few phases while that still gives each
-// compute unit at most one tile (160^2 N = 3: 6.1 against 7.1 us; two tiles
-// on some units at 180^2 were slower, as was mixed N = 5; FP32 measures the
-// same or slower with 4).  A domain alone in its launches takes 12 rows where
-// that gives each compute unit one tile and 8 rows would give some two: a
-// unit with two tiles takes longer than one with a taller tile, though the
-// others have less to do (256 x 300, 304 against 200 tiles: N = 2 FP32 5.9
-// against 5.7 us, N = 5 FP32 12.4 against 11.1, N = 8 FP32 20.8 against 17.4,
-// N = 3 FP64 11.5 against 10.1; with 12 rows on 320 x 320, 270 tiles, N = 5
-// FP32 takes 18.6 us against 13.3).
+// Tiles have 8 rows; 4 while that gives each compute unit at most one tile
+// (160 x 200, 250 tiles: N = 2 FP32 4.6 against 5.0 us with 8, N = 5 FP32 7.7
+// against 8.7, N = 8 FP32 10.9 against 12.6, N = 3 FP64 6.4 against 7.5; 256 x
+// 256, 512 tiles: N = 5 FP32 10.2 against 9.7).  A domain alone in its launches
+// takes 12 rows where that gives each compute unit one tile and 8 rows would
+// give some two: a unit with two tiles takes longer than one with a taller
+// tile, though the others have less to do (264 x 260, 297 against 198 tiles:
+// N = 2 FP32 6.0 against 6.0 us, N = 5 FP32 12.6 against 11.3, N = 8 FP32 19.0
+// against 16.7, N = 3 FP64 11.3 against 9.9, N = 5 FP64 17.8 against 15.6; with
+// 12 rows on 320 x 320, 270 tiles, N = 5 FP32 takes 18.6 us against 13.3).
+// Domains that share their launches (the server) keep to 8 rows, except in
+// FP64 with few phases, so that those of one phase count stay in one launch.
 // A set NPLBM_TX, NPLBM_BW, NPLBM_MIN_STRIP_H or NPLBM_TARGET_BLOCKS asks for
 // strips; NPLBM_TILE = 0 (strips), 4 or 8 overrides.
 StepGeom domain_geom(const nplbm_params *p, bool shared) {
@@ -516,15 +518,15 @@ StepGeom domain_geom(const nplbm_params *p, bool shared) {
     const int64_t cols = (p->nx + kTileWidth - 1) / kTileWidth;
     auto one_each = [&](int ty) { return cols * ((rows + ty - 1) / ty) <= kComputeUnits; };
     const bool few = p->precision == 64 && p->N <= (scheme == kSchemeCentral ? 5 : 3);
-    g.ty = few && one_each(4) ? 4 : 8;
-    if (!shared && !one_each(8) && one_each(12) && tile12_built(p->N, p->precision / 8, scheme))
+    g.ty = one_each(4) && (few || !shared) ? 4 : 8;
+    if (!shared && !one_each(8) && one_each(12) && tile12_built(p->N, p->precision / 8))
       g.ty = 12;
   }
   if (const char *e = std::getenv("NPLBM_TILE")) {
     const int t = std::atoi(e);
     if (t == 0) g.ty = 0;
     if (g.ty && t == 8) g.ty = 8;
-    if (g.ty && t == 4 && p->precision == 64 && p->N <= kTile4MaxN) g.ty = 4;
+    if (g.ty && t == 4) g.ty = 4;
   }
   return g;
 }

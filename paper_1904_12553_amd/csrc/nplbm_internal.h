@@ -24,10 +24,8 @@ struct StepGeom {
   int ty = 0;  // > 0: the domain is stepped by the tile kernel, tiles of this many rows
 };
 // Tiles of the tile kernel are kTileWidth columns (one 128-byte line in FP32)
-// by ty = 8 rows, 4 (built for FP64 up to kTile4MaxN phases) or 12
-// (tile12_built), one thread per node.
+// by ty = 8, 4 or 12 (tile12_built) rows, one or two threads per node.
 constexpr int kTileWidth = 32;
-constexpr int kTile4MaxN = 5;
 constexpr int kComputeUnits = 256;                    // of the chip
 constexpr int64_t kCacheBytes = (int64_t)256 << 20;  // of its Infinity Cache
 // Gradient schemes (nplbm_params.grad_scheme): central isotropic (eq:N31a)
@@ -40,13 +38,20 @@ constexpr int kGradMixed = 1;
 constexpr int kSchemeCentral = 0;
 constexpr int kSchemeMixed = 1;
 constexpr int kSchemeRemark1 = 2;
-// Whether the tile kernel is built with 12 rows: its 24 waves, helpers
-// included, leave 168 registers a thread, which more phases spill (FP64 N = 4
-// with the mixed scheme already by 84 bytes: 16.4 us a step on 256 x 300, no
-// faster than with 8 rows).
-constexpr bool tile12_built(int N, int bytes, int scheme) {
-  return N * bytes <= 32 && !(N * bytes == 32 && bytes == 8 && scheme == kSchemeMixed);
+// Whether the two threads that a node has while all tiles are resident share
+// its collision (tile_kernel.hip): always with 4 rows (128^2, one thread
+// against two: N = 2 FP32 4.51 / 4.43 us a step, N = 5 FP32 7.75 / 6.99, N = 8
+// FP32 11.5 / 10.0, N = 3 FP64 5.98 / 5.72, N = 8 FP64 14.7 / 11.9), with 8
+// and 12 from the phase count on where it gains (N = 8 FP32 256^2 15.6 /
+// 14.5, mixed 17.4 / 16.2, N = 8 FP64 24.1 / 21.2; but 12 rows on 250 x 380
+// N = 3 FP32 7.8 / 8.4, N = 3 FP64 11.5 / 11.8): the exchange through LDS and
+// its barrier cost 0.3 us.
+constexpr bool tile_split(int N, int bytes, int scheme, int ty) {
+  return ty == 4 || N >= (bytes == 8 ? 3 : 5) + (scheme == kSchemeCentral);
 }
+// Whether the tile kernel is built with 12 rows: its 24 waves, helpers
+// included, leave 168 registers a thread, which more phases spill.
+constexpr bool tile12_built(int N, int bytes) { return N * bytes <= 40; }
 // Whether every lane of a step-kernel row owns an interior column (the
 // x-halo phi then comes from lanes that each pull one population of a halo
 // node): the central scheme in FP32 for N <= 5 and in FP64 for N <= 3, the

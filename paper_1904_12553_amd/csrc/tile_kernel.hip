@@ -6,9 +6,10 @@
 // loads, LDS stages and two barriers (about 4 us with few workgroups on the
 // chip), so a small lattice -- a few strips of 16 rows and more -- leaves
 // most compute units idle and is bound by that chain: 44 us a step on the
-// 100 x 100 N = 3 FP64 droplet, seven workgroups.  Here one launch gives
-// every node a thread of its own and goes through the chain once: a
-// workgroup owns a tile of 32 x TY nodes (one cache line of FP32 wide) and
+// 100 x 100 N = 3 FP64 droplet, seven workgroups; 5.5 us here.  One launch
+// gives every node a thread of its own, or two, and goes through the chain
+// once: a workgroup owns a tile of 32 x TY nodes (one cache line of FP32
+// wide) and
 //
 //   stage A: each thread pulls the CH populations of its node (kept in
 //            registers for the collision) and the workgroup shares out the
@@ -23,10 +24,17 @@
 //
 // The halo populations are pulled again by the neighbouring tiles (1.7 times
 // the CH reads at TY = 8, 2.3 at TY = 4), from L2 or MALL at the sizes this
-// kernel runs at.  Every node's arithmetic is that of node_math.h, as in the
+// kernel runs at.  What bounds it: with a tile or less per compute unit the
+// chain of latencies, half of it in stage A (N = 8 FP32 on 128^2: 10 of 21
+// thousand cycles, 3 in B, 7 in C) on top of 1.6 us a launch; with many, the
+// traffic of L2 and MALL (512^2 N = 4 FP32: 106 MB in 18.9 us, 5.6 TB/s).
+// Wider tiles (64 x 4, 64 x 8, 128 x 4) were slower, but for FP32 with N <= 5
+// at 512^2 (64 x 8: 5 - 7%).  Every node's arithmetic is that of node_math.h, as in the
 // marching kernel, and a halo phi is summed in the order its own tile sums
 // it, so the state does not depend on which kernel or tile advanced a node.
 #include "node_math.h"
+
+#include <climits>
 
 namespace nplbm {
 
@@ -77,21 +85,29 @@ __device__ __forceinline__ void touch_consts(const NPL_CONST Consts<Real> &K) {
   asm volatile("" ::"v"(s));
 }
 
-// kHelp: the workgroup has a second set of kTW x TY threads that takes the
-// halo items of stage A and the rings of stages B and J, so that a node's own
-// thread goes through its own part only.
-template <int N, typename Real, int TY, int kGS, bool kHelp>
+// kHelp: the workgroup has a second set of kTW x TY threads (helpers) that
+// takes the rings of stages B and J and the halo items of stage A, so that a
+// node's own thread goes through its own part only.  kSplit: the sets share
+// the halo items, and a node's collision too: the first set takes the NS
+// populations and the CH phases below kOwn (the NS collision weighs as two
+// phases), the helpers the other phases and the gradients of C.
+template <int N, typename Real, int TY, int kGS, bool kHelp,
+          bool kSplit = kHelp && tile_split(N, (int)sizeof(Real), kGS, TY)>
 __global__ void __launch_bounds__(kTW * TY * (kHelp ? 2 : 1)) k_tile(TileArgs a) {
   constexpr int M = N - 1;
   constexpr bool kTwoHop = kGS == kSchemeMixed;  // eq:N40 first derivatives
   constexpr bool kR1 = kGS == kSchemeRemark1;    // Remark 1 force distribution
   constexpr int kNT = kTW * TY;
-  // Many phases in FP64: the own populations, three and more rounds of halo
-  // items and the NS ones together exceed the registers of two waves per
-  // SIMD.  These variants finish the own phi before the halo and take the
-  // halo three items at a time (512^2 FP64 Remark 1 N = 6: 63 us a step
-  // against 78; up to N = 5 it costs a few percent).
-  constexpr bool kGrouped = sizeof(Real) == 8 && M * 8 + (kGS == kSchemeRemark1 ? 8 : 0) >= 48;
+  constexpr int kHT = kNT * (kSplit ? 2 : 1);  // threads that bring the halo
+  constexpr int kOwn = kSplit ? (M > 2 ? (M - 2) / 2 : 0) : M;
+  constexpr int kPh = M - kOwn > kOwn ? M - kOwn : kOwn;  // most phases of a thread
+  // Many phases in FP64 on one thread: the own populations, three and more
+  // rounds of halo items and the NS ones together exceed the registers of two
+  // waves per SIMD.  These variants finish the own phi before the halo and
+  // take the halo three items at a time (512^2 FP64 Remark 1 N = 6: 63 us a
+  // step against 78, 360^2 mixed N = 6: 39 against 46; up to N = 5 it costs a
+  // few percent).
+  constexpr bool kGrouped = !kSplit && sizeof(Real) == 8 && M * 8 + (kGS ? 8 : 0) >= 48;
   // phi is needed kHalo nodes around a node that collides, C kHalo - 1
   constexpr int kHalo = kGS ? 3 : 2, kRing = kHalo - 1;
   constexpr int kPW = kTW + 2 * kHalo, kPR = TY + 2 * kHalo;
@@ -99,6 +115,8 @@ __global__ void __launch_bounds__(kTW * TY * (kHelp ? 2 : 1)) k_tile(TileArgs a)
   constexpr int kQW = kTW + 2, kQR = TY + 2;
   __shared__ Real sphi[M][kPR][kPW];
   __shared__ Real sC[M][kCR][kCW];
+  __shared__ Acc sU[kSplit ? 2 : 1][kSplit ? kNT : 1];  // new velocity
+  __shared__ Real sJ[kSplit && !kR1 ? 2 : 1][kSplit && !kR1 ? kNT : 1];  // G.Jxs, G.Jys
   __shared__ Real sQ[kR1 ? 4 : 1][kR1 ? kQR : 1][kQW];  // J~_x u_x, J~_y u_x, J~_x u_y, J~_y u_y
 
   // The tile and its domain: by value for a launch over one domain (block b
@@ -151,10 +169,12 @@ __global__ void __launch_bounds__(kTW * TY * (kHelp ? 2 : 1)) k_tile(TileArgs a)
              rp = row_rsrc(d.src[2], rbp * (uint32_t)ny, 0);
 
   const int tid = threadIdx.x;
-  // helpers hold no node (uniform over a wave)
+  // (uniform over a wave)
   const bool helper = kHelp && __builtin_amdgcn_readfirstlane(tid / kNT) != 0;
-  const int ht = tid % kNT;  // thread number among the halo's threads
+  const int ht = tid % kNT;
   const int lx = ht % kTW, ly = ht / kTW;
+  // the thread's phases: ph0 + j, j < nph
+  const int ph0 = helper ? kOwn : 0, nph = helper ? M - kOwn : kOwn;
   // Lattice node of tile position (px, py), px, py >= -kHalo: periodic in
   // x; periodic or mirrored at the walls in y.  Positions more than kHalo
   // beyond a ragged edge are never asked for.
@@ -194,30 +214,33 @@ __global__ void __launch_bounds__(kTW * TY * (kHelp ? 2 : 1)) k_tile(TileArgs a)
 
   // ---- stage A: all loads of the step ----
   // own node; threads up to kHalo beyond a ragged edge bring halo nodes
-  const bool own = !helper && lx < ncol + kHalo && ly < nrow + kHalo;
-  const bool interior = !helper && lx < ncol && ly < nrow;
+  const bool active = kSplit || !helper;  // has part in a node's collision
+  const bool own = active && lx < ncol + kHalo && ly < nrow + kHalo;
+  const bool interior = active && lx < ncol && ly < nrow;
   // Columns past a ragged right end are stored too: they fall into the
   // padding of the row pitch, which nothing reads, and whole lines store
   // faster than parts of one (100 x 96 N = 2 FP32: 5.5 us against 6.5 us).
-  const bool storing = !helper && ly < nrow;
+  const bool storing = active && ly < nrow;
   const int x = own ? col_of(lx) : 0, y = own ? row_of(ly) : 0;
-  Real h[M][9], hi[M], g[9], pu[2];
+  Real h[kPh][9], hi[kPh], g[9], pu[2];
   if (own) {
     uint32_t o[9];
     sources(x, y, rbh, o);
 #pragma unroll
-    for (int i = 0; i < M; ++i)
+    for (int j = 0; j < kPh; ++j)
+      if (j < nph)
 #pragma unroll
-      for (int k = 0; k < 9; ++k) h[i][k] = bld<Real>(rh, o[k], (uint32_t)(i * 9) * pb);
+        for (int k = 0; k < 9; ++k) h[j][k] = bld<Real>(rh, o[k], (uint32_t)((ph0 + j) * 9) * pb);
     const uint32_t op = (uint32_t)y * rbp + (uint32_t)x * SZ;
 #pragma unroll
-    for (int i = 0; i < M; ++i) hi[i] = bld<Real>(rp, op, (uint32_t)i * pb);
+    for (int j = 0; j < kPh; ++j)
+      if (j < nph) hi[j] = bld<Real>(rp, op, (uint32_t)(ph0 + j) * pb);
   }
   // halo nodes: position q of the frame around the tile, one phase each
   constexpr int kHN = 2 * kHalo * (kPW + TY);         // nodes of the frame
-  constexpr int kRounds = (kHN * M + kNT - 1) / kNT;  // items per thread
+  constexpr int kRounds = (kHN * M + kHT - 1) / kHT;  // items per thread
   auto load_item = [&](int r, Real (&v)[10]) {
-    const int it = ht + r * kNT;
+    const int it = (kSplit ? tid : ht) + r * kHT;
     const int i = it / kHN;
     int px, py;
     frame_at<kHalo, TY>(it % kHN, px, py);
@@ -234,7 +257,7 @@ __global__ void __launch_bounds__(kTW * TY * (kHelp ? 2 : 1)) k_tile(TileArgs a)
     }
   };
   auto store_item = [&](int r, const Real (&v)[10]) {
-    const int it = ht + r * kNT;
+    const int it = (kSplit ? tid : ht) + r * kHT;
     const int i = it / kHN;
     int px, py;
     frame_at<kHalo, TY>(it % kHN, px, py);
@@ -250,24 +273,26 @@ __global__ void __launch_bounds__(kTW * TY * (kHelp ? 2 : 1)) k_tile(TileArgs a)
   auto store_own = [&]() {
     if (own)
 #pragma unroll
-      for (int i = 0; i < M; ++i)
-        sphi[i][ly + kHalo][lx + kHalo] = hi[i] + lo_sum(h[i]);  // eq:N28
+      for (int j = 0; j < kPh; ++j)
+        if (j < nph) sphi[ph0 + j][ly + kHalo][lx + kHalo] = hi[j] + lo_sum(h[j]);  // eq:N28
   };
   constexpr int kGroup = kGrouped ? 3 : kRounds;
   if constexpr (kGrouped) {
     store_own();
     __builtin_amdgcn_sched_barrier(0);
   }
-  const bool halo = !kHelp || helper;  // who brings the halo
   Real hv[kGroup][10];
+  const bool halo = !kHelp || kSplit || helper;  // has part in bringing the halo
   if (halo)
 #pragma unroll
     for (int r = 0; r < kGroup; ++r) load_item(r, hv[r]);
   if (interior) {
-    uint32_t o[9];
-    sources(x, y, rbg, o);
+    if (!helper) {
+      uint32_t o[9];
+      sources(x, y, rbg, o);
 #pragma unroll
-    for (int k = 1; k < 9; ++k) g[k] = bld<Real>(rg, o[k] - pb, 0u);
+      for (int k = 1; k < 9; ++k) g[k] = bld<Real>(rg, o[k] - pb, 0u);
+    }
     const uint32_t op = (uint32_t)y * rbp + (uint32_t)x * SZ;
     pu[0] = bld<Real>(rp, op, (uint32_t)M * pb);
     pu[1] = bld<Real>(rp, op, (uint32_t)(M + 1) * pb);
@@ -353,51 +378,95 @@ __global__ void __launch_bounds__(kTW * TY * (kHelp ? 2 : 1)) k_tile(TileArgs a)
   }
 
   // ---- stage C: gradients and collisions ----
-  if (!storing) return;
-  Real phi[M], Cv[M];
+  if constexpr (!kSplit)
+    if (!storing) return;
+  // phi and C stay in registers from here where these suffice, and are read
+  // again by each CH collision where they would spill (N = 8 FP64 on 250 x
+  // 380: 29.6 against 40.7 us a step)
+  constexpr bool kKeep = !kSplit && N * sizeof(Real) <= 32;
+  Real phi[M], Cv[kKeep ? M : 1];
   GradSums<Real> G{};
+  NodeFlow f;
   int lc = lx;
-#pragma unroll
-  for (int i = 0; i < M; ++i) {
-    phi[i] = sphi[i][ly + kHalo][lx + kHalo];
-    Cv[i] = sC[i][ly + kRing][lx + kRing];
-    // The next phase's LDS reads wait for this phase's sums (their index
-    // passes through an empty asm that takes them).  Left alone the compiler
-    // issues the reads of all phases first and holds them: 216 against 108
-    // registers for FP32 mixed N = 5 (512^2: 29.9 against 25.0 us a step),
-    // and spills for FP64 mixed N >= 7 (N = 8, 512^2: 288 against 111 us).
-    asm("" : "+v"(lc) : "v"(G.grs), "v"(G.gys), "v"(G.Fxs), "v"(G.Fys), "v"(G.Jxs), "v"(G.Jys));
-    auto fp = [&](int dx, int dy) { return sphi[i][ly + kHalo + dy][lc + kHalo + dx]; };
-    auto fc = [&](int dx, int dy) { return sC[i][ly + kRing + dy][lc + kRing + dx]; };
-    Real gx, gy;
+  auto grad = [&](auto at, Real &gx, Real &gy) {
     if constexpr (kTwoHop)
-      grad_two_hop<Real>(fp, gx, gy);
+      grad_two_hop<Real>(at, gx, gy);
     else
-      grad_central<Real>(fp, gx, gy);
+      grad_central<Real>(at, gx, gy);
+  };
+  // The next phase's LDS reads wait for this phase's sums (their index
+  // passes through an empty asm that takes them).  Left alone the compiler
+  // issues the reads of all phases first and holds them: 216 against 108
+  // registers for FP32 mixed N = 5 (512^2: 29.9 against 25.0 us a step),
+  // and spills for FP64 mixed N >= 7 (N = 8, 512^2: 288 against 111 us).
+  auto in_turn = [&]() {
+    asm("" : "+v"(lc) : "v"(G.grs), "v"(G.gys), "v"(G.Fxs), "v"(G.Fys), "v"(G.Jxs), "v"(G.Jys));
+  };
+  auto phi_grads = [&](int i, Real C) {
+    Real gx, gy;
+    grad([&](int dx, int dy) { return sphi[i][ly + kHalo + dy][lc + kHalo + dx]; }, gx, gy);
     G.grs += K.rA[i] * gx;
     G.gys += K.rA[i] * gy;
-    G.Fxs += Cv[i] * gx;
-    G.Fys += Cv[i] * gy;
-    if constexpr (!kR1) {
-      if constexpr (kTwoHop)
-        grad_two_hop<Real>(fc, gx, gy);
-      else
-        grad_central<Real>(fc, gx, gy);
-      G.Jxs += K.Jc[i] * gx;
-      G.Jys += K.Jc[i] * gy;
+    G.Fxs += C * gx;
+    G.Fys += C * gy;
+  };
+  auto c_grads = [&](int i) {
+    Real gx, gy;
+    grad([&](int dx, int dy) { return sC[i][ly + kRing + dy][lc + kRing + dx]; }, gx, gy);
+    G.Jxs += K.Jc[i] * gx;
+    G.Jys += K.Jc[i] * gy;
+  };
+  if (!kSplit || (!helper && storing)) {
+#pragma unroll
+    for (int i = 0; i < M; ++i) {
+      phi[i] = sphi[i][ly + kHalo][lx + kHalo];
+      const Real C = sC[i][ly + kRing][lx + kRing];
+      if constexpr (kKeep) Cv[i] = C;
+      in_turn();
+      phi_grads(i, C);
+      if constexpr (!kR1 && !kSplit) c_grads(i);
     }
-  }
-  Acc divx = Acc(0), divy = Acc(0);
-  if constexpr (kR1) {
-    const int s0 = ly + 1;
-    const int sN = wall && y0 + ly == ny - 1 ? s0 : s0 + 1, sS = wall && y0 + ly == 0 ? s0 : s0 - 1;
-    auto q = [&](int c) {
-      return [&, c](int dx, int dy) {
-        return sQ[c][dy == 0 ? s0 : (dy > 0 ? sN : sS)][lx + 1 + dx];
+    Acc divx = Acc(0), divy = Acc(0);
+    if constexpr (kR1) {
+      const int s0 = ly + 1;
+      const int sN = wall && y0 + ly == ny - 1 ? s0 : s0 + 1,
+                sS = wall && y0 + ly == 0 ? s0 : s0 - 1;
+      auto q = [&](int c) {
+        return [&, c](int dx, int dy) {
+          return sQ[c][dy == 0 ? s0 : (dy > 0 ? sN : sS)][lx + 1 + dx];
+        };
       };
-    };
-    divx = ddx_central(q(0)) + ddy_central(q(1));
-    divy = ddx_central(q(2)) + ddy_central(q(3));
+      divx = ddx_central(q(0)) + ddy_central(q(1));
+      divy = ddx_central(q(2)) + ddy_central(q(3));
+    }
+    f = flow_node<N, Real, kR1>(KD, phi, G, divx, divy, g);
+  }
+  if constexpr (kSplit) {
+    if (helper) {
+      if constexpr (!kR1) {
+        if (storing) {
+#pragma unroll
+          for (int i = 0; i < M; ++i) {
+            in_turn();
+            c_grads(i);
+          }
+          sJ[0][ht] = G.Jxs;
+          sJ[1][ht] = G.Jys;
+        }
+      }
+    } else if (storing) {
+      sU[0][ht] = f.ux;
+      sU[1][ht] = f.uy;
+    }
+    __syncthreads();
+    if (!storing) return;
+    if (helper) {
+      f.ux = sU[0][ht];
+      f.uy = sU[1][ht];
+    } else if constexpr (!kR1) {
+      G.Jxs = sJ[0][ht];
+      G.Jys = sJ[1][ht];
+    }
   }
   const Rsrc wh = row_rsrc(d.dst[0], rbh * (uint32_t)ny, 0),
              wg = row_rsrc(d.dst[1], rbg * (uint32_t)ny, 0),
@@ -405,63 +474,70 @@ __global__ void __launch_bounds__(kTW * TY * (kHelp ? 2 : 1)) k_tile(TileArgs a)
   const uint32_t oc = (uint32_t)(x0 + lx) * SZ, yr = (uint32_t)(y0 + ly);
   const uint32_t oh = yr * rbh + oc, og = yr * rbg + oc, op = yr * rbp + oc;
   // plain stores: the state is read back by the next launch from L2 or MALL
-  collide_node<N, Real, kR1>(
-      K, KD, phi, Cv, G, divx, divy,
-      [&](int i) -> const Real(&)[9] { return h[i]; },
-      hi, g, pu,
-      [&](int plane, Real v) { bst<Real, false>(wg, og, (uint32_t)plane * pb, v); },
-      [&](int plane, Real v) { bst<Real, false>(wh, oh, (uint32_t)plane * pb, v); },
-      [&](int plane, Real v) { bst<Real, false>(wp, op, (uint32_t)plane * pb, v); });
+  auto sg = [&](int plane, Real v) { bst<Real, false>(wg, og, (uint32_t)plane * pb, v); };
+  auto sh = [&](int plane, Real v) { bst<Real, false>(wh, oh, (uint32_t)plane * pb, v); };
+  auto sp = [&](int plane, Real v) { bst<Real, false>(wp, op, (uint32_t)plane * pb, v); };
+  if (!kSplit || !helper) {
+    collide_ns<N, Real, kR1>(KD, phi, G, f, g, sg);
+    sp(M, (Real)f.ux);
+    sp(M + 1, (Real)f.uy);
+  }
+#pragma unroll
+  for (int j = 0; j < kPh; ++j)
+    if (j < nph) {
+      Real pj, Cj;
+      if constexpr (kKeep) {
+        pj = phi[j];
+        Cj = Cv[j];
+      } else {
+        pj = sphi[ph0 + j][ly + kHalo][lx + kHalo];
+        Cj = sC[ph0 + j][ly + kRing][lx + kRing];
+      }
+      collide_ch<Real>(K, ph0 + j, pj, Cj, f.ux, f.uy, hi[j], pu, h[j], sh, sp);
+    }
 }
 
-// Whether a launch of nblocks tiles gets the helper threads: while every
+// The most 8-row tiles of a launch with two threads per node: while every
 // workgroup is resident at once, one per compute unit, or two where the
-// registers allow four waves per SIMD (N x bytes <= 20: at most 128).  A step
-// with and without them: 64^2 FP32 N = 5 7.4 / 8.9 us, 256 x 256 9.4 / 10.9;
-// 256 x 416 (416 tiles) 13.6 / 14.5, FP64 N = 3 there 13.5 / 12.1; 512^2
-// FP32 N = 5 (1024 tiles) 25.0 / 23.0.
+// registers allow four waves per SIMD (FP32, N = 2 FP64).  A step with and
+// without: 256 x 256 (256 tiles) FP32 N = 5 9.4 / 10.9 us; 385 x 257 (429
+// tiles) FP32 N = 5 13.8 / 14.8, N = 6 16.4 / 17.3, N = 8 20.0 / 22.2, FP64
+// N = 3 12.4 / 12.5, N = 5 24.0 / 19.3; 512 x 512 (1024 tiles) FP32 N = 5
+// 25.5 / 23.5.  With the most phases one thread holds so many registers that
+// two per node are faster at any count (620 x 620, 1560 tiles: FP32 N = 8
+// 58.4 / 61.7, mixed 63.6 / 80.9; FP64 mixed N = 8 on 448 x 448 78 / 96).
 template <int N, typename Real>
 constexpr int help_limit() {
-  return kComputeUnits * (N * (int)sizeof(Real) <= 20 ? 2 : 1);
+  constexpr bool f32 = sizeof(Real) == 4;
+  constexpr bool big = f32 && N == 8 && NPL_GS == kSchemeRemark1;  // 129 registers
+  if (f32 ? N >= 7 && !big : N == 8 && NPL_GS != kSchemeCentral) return INT_MAX;
+  return kComputeUnits * ((f32 && !big) || N == 2 ? 2 : 1);
 }
 
-template <int N, typename Real, int TY>
-hipError_t launch_t(const TileArgs &a, int nblocks, hipStream_t st) {
-  if (nblocks <= help_limit<N, Real>())
-    hipLaunchKernelGGL((k_tile<N, Real, TY, NPL_GS, true>), dim3(nblocks), dim3(kTW * TY * 2), 0,
-                       st, a);
-  else
-    hipLaunchKernelGGL((k_tile<N, Real, TY, NPL_GS, false>), dim3(nblocks), dim3(kTW * TY), 0, st,
-                       a);
+template <int N, typename Real, int TY, bool kHelp>
+hipError_t launch_k(const TileArgs &a, int nblocks, hipStream_t st) {
+  hipLaunchKernelGGL((k_tile<N, Real, TY, NPL_GS, kHelp>), dim3(nblocks),
+                     dim3(kTW * TY * (kHelp ? 2 : 1)), 0, st, a);
   return hipGetLastError();
 }
 
-// 12-row tiles are launched alone on their compute units, so always with
-// helper threads.
 template <int N, typename Real>
-hipError_t launch_12(const TileArgs &a, int nblocks, hipStream_t st) {
-  if constexpr (tile12_built(N, (int)sizeof(Real), NPL_GS)) {
-    hipLaunchKernelGGL((k_tile<N, Real, 12, NPL_GS, true>), dim3(nblocks), dim3(kTW * 12 * 2), 0,
-                       st, a);
-    return hipGetLastError();
-  } else {
-    return hipErrorInvalidValue;
-  }
+hipError_t launch_ty(int ty, const TileArgs &a, int nblocks, hipStream_t st) {
+  // 4 rows: two threads per node at any count (FP64 N = 3 on 512 x 512, 2048
+  // tiles, 23.2 us a step against 25.0)
+  if (ty == 4) return launch_k<N, Real, 4, true>(a, nblocks, st);
+  if constexpr (tile12_built(N, (int)sizeof(Real)))
+    if (ty == 12) return launch_k<N, Real, 12, true>(a, nblocks, st);
+  if (ty != 8) return hipErrorInvalidValue;
+  if constexpr (help_limit<N, Real>() < INT_MAX)
+    if (nblocks > help_limit<N, Real>()) return launch_k<N, Real, 8, false>(a, nblocks, st);
+  return launch_k<N, Real, 8, true>(a, nblocks, st);
 }
 
 template <int N>
 hipError_t launch_n(int precision, int ty, const TileArgs &a, int nblocks, hipStream_t st) {
-  if (ty == 4) {
-    if constexpr (N <= kTile4MaxN)
-      if (precision == 64) return launch_t<N, double, 4>(a, nblocks, st);
-    return hipErrorInvalidValue;
-  }
-  if (ty == 12)
-    return precision == 64 ? launch_12<N, double>(a, nblocks, st)
-                           : launch_12<N, float>(a, nblocks, st);
-  if (ty != 8) return hipErrorInvalidValue;
-  return precision == 64 ? launch_t<N, double, 8>(a, nblocks, st)
-                         : launch_t<N, float, 8>(a, nblocks, st);
+  return precision == 64 ? launch_ty<N, double>(ty, a, nblocks, st)
+                         : launch_ty<N, float>(ty, a, nblocks, st);
 }
 
 }  // namespace

@@ -74,3 +74,19 @@ def test_twelve_row_tiles_equal_strips(N, scheme, nx, ny):
             strips = _macro(w, precision, steps, "0", **SCHEMES[scheme])
             got = _macro(w, precision, steps, None, **SCHEMES[scheme])
             assert all(np.array_equal(a, b) for a, b in zip(got, strips)), precision
+
+
+@pytest.mark.parametrize("scheme", list(SCHEMES))
+@pytest.mark.parametrize("N", [6, 7, 8])
+def test_shared_collisions_equal_strips(N, scheme):
+    """Many phases, whose two threads per node share the collision: one 8-row
+    tile per compute unit, two, and more than are resident (256, 506 and 546
+    tiles); and 4-row tiles, 255 of them.  Bitwise, as above."""
+    for nx, ny in ((256, 253), (352, 366), (416, 333), (480, 68)):
+        w = W.random_smooth(N, nx, ny, seed=960 + N + nx, wall_y=True, accept=oracle_accepts,
+                            sigma_range=(0.95e-3, 1.05e-3))
+        print(f"case shared N={N} {scheme} {nx}x{ny}", flush=True)
+        for precision in (64, 32):
+            strips = _macro(w, precision, 5, "0", **SCHEMES[scheme])
+            got = _macro(w, precision, 5, None, **SCHEMES[scheme])
+            assert all(np.array_equal(a, b) for a, b in zip(got, strips)), (nx, precision)
