@@ -537,10 +537,10 @@ int occ3(int precision) {
 // marching tiles leave compute units idle, and those whose rows fill less
 // than 77% of the marching kernel's 64-column tiles; the marching kernel the
 // others, where it moves 2 (N - 1) words a node less.  A step, node /
-// marching: 64^3 FP32 N = 3 32 / 69 us, FP64 N = 4 84 / 182; 100 x 84 x 60
-// FP64 N = 4 187 / 246; 96^3 FP32 N = 3 106 / 120; 72 x 160^2 FP64 N = 3
-// 488 / 537; 96 x 200^2 FP64 N = 3 886 / 914; 112^3 FP32 N = 3 176 / 166;
-// 128^3 237 / 217; 200^3 (78%) FP32 N = 3 1016 / 952.
+// marching: 64^3 FP32 N = 3 30 / 69 us, FP64 N = 4 76 / 182; 100 x 84 x 60
+// FP64 N = 4 171 / 246; 96^3 FP32 N = 3 100 / 117; 72 x 160^2 FP64 N = 3
+// 461 / 500; 96 x 200^2 FP64 N = 3 836 / 895; 112^3 FP32 N = 3 171 / 166;
+// 128^3 230 / 213; 200^3 (78%) FP32 N = 3 1016 / 952.
 // Interior rows of a marching tile = waves of a workgroup: 4 in FP32, where two or
 // more 4-row workgroups per CU measured faster than one of 8 (256^3: N = 3
 // 48.3% against 44.9% of the HBM roofline, N = 5 38.2% against 35.6%); in

@@ -14,13 +14,29 @@
 // phi and C the same way and collides.  Against the marching kernel this
 // moves 2 (N - 1) words a node more (C written and read), and keeps no LDS
 // rings: registers alone set the occupancy.
+//
+// The 15 reads of a stencil come from the same few rows, and read singly they
+// cost more than their bytes (100 x 84 x 60 FP64 N = 4: with the centre read
+// in their place the two kernels took 112 us a step, not 141).  While a
+// workgroup holds two rows and more (W <= 128) it therefore copies the rows
+// it needs into LDS, 3 (R + 2) / R reads a node and field, and forms the
+// stencils from there (k_chem3r, kRows): that lattice 187 -> 171 us a step,
+// FP64 N = 3 64^3 54 -> 51, FP32 N = 3 64^3 31.6 -> 29.8, FP32 N = 5 40 x 64 x 50
+// 50 -> 44.  With one row a workgroup (180 x 60 x 60, 130 x 70 x 70) the copy is
+// as long as the reads it saves, and LDS leaves fewer workgroups: FP64 N = 4
+// 228 -> 239 us, N = 5 FP32 172 -> 187.
+// What bounds them: HBM where the state exceeds the Infinity Cache (that
+// lattice: 0.73 GB a step in three passes, 4.3 TB/s), else latency.
 #include "node_math3.h"
+
+#include <algorithm>
 
 namespace nplbm {
 
 namespace {
 
 constexpr int kT3n = 256;  // threads of a workgroup
+constexpr int kT3r = 512;  // and of one of k_chem3r
 
 // The node of a thread and how to reach its neighbours.  Blocks are numbered
 // for the 8 XCDs as in the phi pass: XCD x takes the x-th contiguous eighth
@@ -67,11 +83,100 @@ __device__ __forceinline__ Node3<Real> node3(const NPL_CONST DomDesc *D, int W, 
   return n;
 }
 
+// The node of a thread where a workgroup owns R whole rows of a plane (R W
+// threads in use), and its place in their LDS copy.  Blocks are numbered for
+// the XCDs as above.
+template <typename Real>
+struct Rows3 {
+  Node3<Real> n;
+  bool use;     // holds a column of the rows
+  int ly, col;  // row and column within the workgroup
+  int cx[3];    // LDS columns x - 1, x, x + 1
+};
+
+template <typename Real>
+__device__ __forceinline__ Rows3<Real> rows3(const NPL_CONST DomDesc *D, int W, int R,
+                                             uint32_t nblk, uint32_t per_plane) {
+  Rows3<Real> q;
+  constexpr uint32_t SZ = sizeof(Real);
+  const int nx = D->nx, ny = D->ny, nz = D->nz;
+  const bool wall = D->wall != 0;
+  const uint32_t per = (nblk + 7) / 8;
+  const uint32_t t = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  Node3<Real> &n = q.n;
+  n.live = t < nblk;
+  if (!n.live) return q;
+  n.z = (int)(t / per_plane);
+  const int y0 = (int)(t - (uint32_t)n.z * per_plane) * R;
+  q.ly = (int)threadIdx.x / W;
+  q.col = (int)threadIdx.x - q.ly * W;
+  q.use = q.ly < R;
+  n.x = q.col;
+  n.y = y0 + q.ly;
+  const int xs = n.x < nx ? n.x : nx - 1;
+  q.cx[0] = xs == 0 ? nx - 1 : xs - 1;
+  q.cx[1] = xs;
+  q.cx[2] = xs == nx - 1 ? 0 : xs + 1;
+  n.own = (uint32_t)n.x * SZ;
+  for (int c = 0; c < 3; ++c) n.cx[c] = (uint32_t)q.cx[c] * SZ;
+  n.ry[0] = n.y == 0 ? ny - 1 : n.y - 1;
+  n.ry[1] = n.y;
+  n.ry[2] = n.y == ny - 1 ? 0 : n.y + 1;
+  n.pz[0] = n.z == 0 ? (wall ? 0 : nz - 1) : n.z - 1;
+  n.pz[1] = n.z;
+  n.pz[2] = n.z == nz - 1 ? (wall ? nz - 1 : 0) : n.z + 1;
+  return q;
+}
+
+// Copies M dense fields' rows into s[(i * 3 + plane) * (R + 2) + row][W].
+template <int M, typename Real>
+__device__ __forceinline__ void copy_rows3(const Rows3<Real> &q, const Rsrc (&r)[3], uint32_t rbf,
+                                           uint32_t pb, int ny, int W, int R, Real *s) {
+  if (!q.use) return;
+  for (int rr = q.ly; rr < R + 2; rr += R) {
+    int y = q.n.y - q.ly - 1 + rr;
+    y = y < 0 ? y + ny : (y >= ny ? y - ny : y);  // R <= ny: one turn suffices
+    const uint32_t o = (uint32_t)y * rbf + q.n.own;
+#pragma unroll
+    for (int i = 0; i < M; ++i)
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+        s[((i * 3 + p) * (R + 2) + rr) * W + q.col] = bld<Real>(r[p], o, (uint32_t)i * pb);
+  }
+}
+
 struct Step3nArgs {
   StepArgs s;
-  int32_t W;
+  int32_t W, R;
   uint32_t nblk, per_plane;
 };
+
+template <int N, typename Real>
+__global__ void __launch_bounds__(kT3r) k_chem3r(Step3nArgs a) {
+  constexpr uint32_t SZ = sizeof(Real);
+  extern __shared__ __align__(16) char lds3[];
+  Real *s = (Real *)lds3;
+  const NPL_CONST DomDesc *D = (const NPL_CONST DomDesc *)a.s.doms;
+  const int W = a.W, R = a.R, ny = D->ny;
+  const Rows3<Real> q = rows3<Real>(D, W, R, a.nblk, a.per_plane);
+  if (!q.n.live) return;
+  const NPL_CONST Consts<Real> &K = *consts_of<Real>(D);
+  const uint32_t pb = (uint32_t)D->ps[0] * SZ, rbf = (uint32_t)D->rsf * SZ,
+                 plf = (uint32_t)ny * rbf;
+  const Rsrc r[3] = {row_rsrc(D->phi3, plf, q.n.pz[0]), row_rsrc(D->phi3, plf, q.n.pz[1]),
+                     row_rsrc(D->phi3, plf, q.n.pz[2])};
+  copy_rows3<N - 1, Real>(q, r, rbf, pb, ny, W, R, s);
+  __syncthreads();
+  if (!q.use || q.n.y >= ny) return;
+  const Rsrc w = row_rsrc(D->c3, plf, q.n.z);
+  const uint32_t ow = (uint32_t)q.n.y * rbf + q.n.own;
+  chem_node3<N, Real>(
+      K,
+      [&](int i, int dx, int dy, int dz) {
+        return s[((i * 3 + dz + 1) * (R + 2) + q.ly + 1 + dy) * W + q.cx[dx + 1]];
+      },
+      [&](int i, Real v) { bst<Real, false>(w, ow, (uint32_t)i * pb, v); });
+}
 
 template <int N, typename Real>
 __global__ void __launch_bounds__(kT3n) k_chem3n(Step3nArgs a) {
@@ -100,15 +205,23 @@ __global__ void __launch_bounds__(kT3n) k_chem3n(Step3nArgs a) {
 }
 
 // kNT: nontemporal stores of the new state, for states that do not fit the
-// Infinity Cache (112^3 FP32 N = 5 326 us a step against 346 with plain
-// stores); states that do are read back from it (64^3 FP32 N = 5 53 us with
-// plain stores against 57, FP64 N = 3 55 against 62).
-template <int N, typename Real, bool kNT>
+// Infinity Cache (112^3 FP32 N = 5, stencils not yet read through LDS: 326 us a
+// step against 346 with plain stores); states that do are read back from it
+// (likewise 64^3 FP32 N = 5 53 us with plain stores against 57, FP64 N = 3 55
+// against 62).
+template <int N, typename Real, bool kNT, bool kRows>
 __global__ void __launch_bounds__(kT3n) k_step3n(Step3nArgs a) {
   constexpr int M = N - 1;
   constexpr uint32_t SZ = sizeof(Real);
   const NPL_CONST DomDesc *D = (const NPL_CONST DomDesc *)a.s.doms;
-  const Node3<Real> n = node3<Real>(D, a.W, a.nblk, a.per_plane);
+  extern __shared__ __align__(16) char lds3[];
+  Real *sf = (Real *)lds3, *sc = sf + M * 3 * (a.R + 2) * a.W;
+  Rows3<Real> q;
+  if constexpr (kRows)
+    q = rows3<Real>(D, a.W, a.R, a.nblk, a.per_plane);
+  else
+    q.n = node3<Real>(D, a.W, a.nblk, a.per_plane);
+  const Node3<Real> &n = q.n;
   if (!n.live) return;
   const NPL_CONST Consts<Real> &K = *consts_of<Real>(D);
   const NPL_CONST Consts<double> &KD = *consts_of<double>(D);
@@ -124,6 +237,16 @@ __global__ void __launch_bounds__(kT3n) k_step3n(Step3nArgs a) {
   // node's own opposite ones (uniform over the workgroup)
   const bool bS = wall && n.z == 0, bN = wall && n.z == nz - 1;
 
+  if constexpr (kRows) {
+    const Rsrc rf[3] = {row_rsrc(D->phi3, plf, n.pz[0]), row_rsrc(D->phi3, plf, n.pz[1]),
+                        row_rsrc(D->phi3, plf, n.pz[2])};
+    const Rsrc rc[3] = {row_rsrc(D->c3, plf, n.pz[0]), row_rsrc(D->c3, plf, n.pz[1]),
+                        row_rsrc(D->c3, plf, n.pz[2])};
+    copy_rows3<M, Real>(q, rf, rbf, pb, ny, a.W, a.R, sf);
+    copy_rows3<M, Real>(q, rc, rbf, pb, ny, a.W, a.R, sc);
+    __syncthreads();
+    if (!q.use || n.y >= ny) return;
+  }
   // NS populations and previous u
   Real g[15], pu[3];
   const uint32_t op = (uint32_t)n.y * rbp + n.cx[1];
@@ -160,9 +283,20 @@ __global__ void __launch_bounds__(kT3n) k_step3n(Step3nArgs a) {
       for (int c = 0; c < 3; ++c) o[j][c] = (uint32_t)n.ry[j] * rbf + n.cx[c];
 #pragma unroll
     for (int i = 0; i < M; ++i) {
+      Real gp[3], gc[3];
+      if constexpr (kRows) {
+        auto at = [&](const Real *f, int dx, int dy, int dz) {
+          return f[((i * 3 + dz + 1) * (a.R + 2) + q.ly + 1 + dy) * a.W + q.cx[dx + 1]];
+        };
+        phi[i] = at(sf, 0, 0, 0);
+        Cv[i] = at(sc, 0, 0, 0);
+        grad_node3<Real>([&](int dx, int dy, int dz) { return at(sf, dx, dy, dz); }, gp);
+        grad_node3<Real>([&](int dx, int dy, int dz) { return at(sc, dx, dy, dz); }, gc);
+        sums3_add<Real>(K, KD, i, phi[i], Cv[i], gp, gc, S);
+        continue;
+      }
       phi[i] = bld<Real>(rf[1], o[1][1], (uint32_t)i * pb);
       Cv[i] = bld<Real>(rc[1], o[1][1], (uint32_t)i * pb);
-      Real gp[3], gc[3];
       grad_node3<Real>(
           [&](int dx, int dy, int dz) {
             return bld<Real>(rf[dz + 1], o[dy + 1][dx + 1], (uint32_t)i * pb);
@@ -197,14 +331,37 @@ __global__ void __launch_bounds__(kT3n) k_step3n(Step3nArgs a) {
       [&](int plane, Real v) { bst<Real, kNT>(wp, ow, (uint32_t)plane * pb, v); });
 }
 
-template <int N, typename Real>
-hipError_t launch3n(const Step3nArgs &a, bool cached, hipStream_t st) {
+template <int N, typename Real, bool kRows>
+void launch_step3_nodes(const Step3nArgs &a, bool cached, int threads, size_t lds,
+                        hipStream_t st) {
   const dim3 grid((a.nblk + 7) / 8 * 8);
-  hipLaunchKernelGGL((k_chem3n<N, Real>), grid, dim3(kT3n), 0, st, a);
   if (cached)
-    hipLaunchKernelGGL((k_step3n<N, Real, false>), grid, dim3(kT3n), 0, st, a);
+    hipLaunchKernelGGL((k_step3n<N, Real, false, kRows>), grid, dim3(threads), lds, st, a);
   else
-    hipLaunchKernelGGL((k_step3n<N, Real, true>), grid, dim3(kT3n), 0, st, a);
+    hipLaunchKernelGGL((k_step3n<N, Real, true, kRows>), grid, dim3(threads), lds, st, a);
+}
+
+template <int N, typename Real>
+hipError_t launch3n(Step3nArgs a, bool cached, int ny, int nz, hipStream_t st) {
+  const size_t row = (size_t)a.W * sizeof(Real) * 3 * (N - 1);
+  Step3nArgs b = a;
+  auto rows = [&](int T) {
+    b.R = std::min(T / b.W, ny);
+    b.per_plane = (uint32_t)((ny + b.R - 1) / b.R);
+    b.nblk = b.per_plane * (uint32_t)nz;
+    return (b.R * b.W + 63) / 64 * 64;
+  };
+  // whole rows while two and more of them are a workgroup of kT3n threads
+  if (a.W <= kT3n / 2) {
+    const int tc = rows(kT3r);
+    hipLaunchKernelGGL((k_chem3r<N, Real>), dim3((b.nblk + 7) / 8 * 8), dim3(tc),
+                       row * (b.R + 2), st, b);
+    const int ts = rows(kT3n);
+    launch_step3_nodes<N, Real, true>(b, cached, ts, 2 * row * (b.R + 2), st);
+  } else {
+    hipLaunchKernelGGL((k_chem3n<N, Real>), dim3((a.nblk + 7) / 8 * 8), dim3(kT3n), 0, st, a);
+    launch_step3_nodes<N, Real, false>(a, cached, kT3n, 0, st);
+  }
   return hipGetLastError();
 }
 
@@ -224,13 +381,13 @@ hipError_t launch_step3n(int N, int precision, const StepArgs &s, int nx, int ny
   const bool cached = 2 * (int64_t)(16 * N + 1) * (precision / 8) * nx * ny * nz <= kCacheBytes;
   switch (N) {
     case 2:
-      return precision == 64 ? launch3n<2, double>(a, cached, st) : launch3n<2, float>(a, cached, st);
+      return precision == 64 ? launch3n<2, double>(a, cached, ny, nz, st) : launch3n<2, float>(a, cached, ny, nz, st);
     case 3:
-      return precision == 64 ? launch3n<3, double>(a, cached, st) : launch3n<3, float>(a, cached, st);
+      return precision == 64 ? launch3n<3, double>(a, cached, ny, nz, st) : launch3n<3, float>(a, cached, ny, nz, st);
     case 4:
-      return precision == 64 ? launch3n<4, double>(a, cached, st) : launch3n<4, float>(a, cached, st);
+      return precision == 64 ? launch3n<4, double>(a, cached, ny, nz, st) : launch3n<4, float>(a, cached, ny, nz, st);
     case 5:
-      return precision == 64 ? launch3n<5, double>(a, cached, st) : launch3n<5, float>(a, cached, st);
+      return precision == 64 ? launch3n<5, double>(a, cached, ny, nz, st) : launch3n<5, float>(a, cached, ny, nz, st);
     default: return hipErrorInvalidValue;
   }
 }

@@ -58,3 +58,17 @@ def test_node_kernels_equal_march_beyond_the_cache():
     print("case node kernels N=5 110x60x50 fp64 steps=6", flush=True)
     got, march = _macro(w, 64, 6, "0"), _macro(w, 64, 6, "4")
     assert all(np.array_equal(a, b) for a, b in zip(got, march))
+
+
+@pytest.mark.parametrize("N,nx,ny,nz", [(2, 128, 7, 4), (3, 129, 5, 4), (4, 16, 5, 6), (5, 113, 9, 4),
+                                        (3, 112, 13, 5), (2, 48, 4, 9)])
+@pytest.mark.parametrize("wall", [False, True])
+def test_row_copies_equal_march(N, nx, ny, nz, wall):
+    """Stencils formed from rows copied to LDS: the longest rows that are
+    copied and the first that are not, fewer rows than a workgroup holds, a
+    last workgroup of one row.  Bitwise, as above."""
+    w = W.random_smooth3d(N, nx, ny, nz, seed=840 + nx + wall, wall_z=wall, accept=oracle_accepts)
+    print(f"case row copies N={N} {nx}x{ny}x{nz} wall={wall}", flush=True)
+    for precision in (64, 32):
+        got, march = _macro(w, precision, 7, "0"), _macro(w, precision, 7, "4")
+        assert all(np.array_equal(a, b) for a, b in zip(got, march)), precision
