@@ -487,12 +487,18 @@ StepGeom step_geom(int N, int precision, int scheme) {
 // state, 2 x 10 N words per node, fit the 256 MB Infinity Cache: it reads the
 // halo of each tile again, which is cheap from there, and has a thread for
 // every node where marching strips leave compute units idle (100^2 N = 3 FP64
-// 5.7 against 45 us a step; 512^2: N = 3 FP64 23 against 67, N = 4 FP32 19
-// against 61, N = 8 FP32 41 against 64; at the edge, 768^2 N = 5 FP32, 236
+// 5.5 against 45 us a step; 512^2: N = 3 FP64 23 against 67, N = 4 FP32 19
+// against 61, N = 8 FP32 38 against 64; at the edge, 768^2 N = 5 FP32, 236
 // MB, 46 against 78).  Beyond it the second read goes to HBM and the marching
 // kernel, which reads every population once, is faster (768^2 N = 3 FP64,
 // 283 MB, 64 against 76, but 1024^2 N = 3 FP64 116 against 100, N = 5 FP32
-// 119 against 100, 768^2 N = 4 FP64 96 against 87).
+// 119 against 100, 768^2 N = 4 FP64 96 against 87).  With many phases the
+// marching kernel runs out of registers and the line lies at twice the cache
+// (1000^2, tile against strips: FP32 N = 6 143 / 127, mixed 157 / 161, N = 7
+// 174 / 174, mixed 187 / 191, N = 8 mixed 216 / 227; 700^2 FP64: N = 6 124 /
+// 117, mixed 130 / 149, Remark 1 135 / 155, N = 8 mixed 200 / 208), with the
+// most further out (1500^2: FP64 N = 8 746 / 866, Remark 1 931 / 1051, FP32
+// Remark 1 483 / 523); eight times keeps every group below 2^31 bytes.
 // Tiles have 8 rows; 4 while that gives each compute unit at most one tile
 // (160 x 200, 250 tiles: N = 2 FP32 4.6 against 5.0 us with 8, N = 5 FP32 7.7
 // against 8.7, N = 8 FP32 10.9 against 12.6, N = 3 FP64 6.4 against 7.5; 256 x
@@ -514,10 +520,13 @@ StepGeom domain_geom(const nplbm_params *p, bool shared) {
     if (std::getenv(e)) return g;
   const int64_t rows = p->ny;
   const int64_t state = 2 * 10 * (int64_t)p->N * (p->precision / 8) * state_pitch(p) * rows;
-  if (state <= kCacheBytes) {
+  const bool central = scheme == kSchemeCentral, f32 = p->precision == 32;
+  const bool most = p->N == 8 && (scheme == kSchemeRemark1 || (central && !f32));
+  const bool many = p->N >= (f32 && central ? 7 : 6) && (f32 || !central);
+  if (state <= kCacheBytes * (most ? 8 : many ? 2 : 1)) {
     const int64_t cols = (p->nx + kTileWidth - 1) / kTileWidth;
     auto one_each = [&](int ty) { return cols * ((rows + ty - 1) / ty) <= kComputeUnits; };
-    const bool few = p->precision == 64 && p->N <= (scheme == kSchemeCentral ? 5 : 3);
+    const bool few = p->precision == 64 && p->N <= (central ? 5 : 3);
     g.ty = one_each(4) && (few || !shared) ? 4 : 8;
     if (!shared && !one_each(8) && one_each(12) && tile12_built(p->N, p->precision / 8))
       g.ty = 12;

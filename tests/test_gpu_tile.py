@@ -90,3 +90,17 @@ def test_shared_collisions_equal_strips(N, scheme):
             strips = _macro(w, precision, 5, "0", **SCHEMES[scheme])
             got = _macro(w, precision, 5, None, **SCHEMES[scheme])
             assert all(np.array_equal(a, b) for a, b in zip(got, strips)), (nx, precision)
+
+
+@pytest.mark.parametrize("N,scheme,precision,nx,ny", [
+    (7, "central", 32, 800, 640), (6, "mixed", 32, 901, 650), (8, "remark1", 32, 900, 980),
+    (6, "remark1", 64, 560, 520), (8, "central", 64, 777, 700)])
+def test_tiles_beyond_the_cache_equal_strips(N, scheme, precision, nx, ny):
+    """Many phases, which are stepped by tiles beyond 256 MB of state (287 to
+    713 MB).  Bitwise, as above."""
+    w = W.random_smooth(N, nx, ny, seed=980 + N + nx, accept=oracle_accepts,
+                        sigma_range=(0.95e-3, 1.05e-3))
+    print(f"case big tile N={N} {scheme} fp{precision} {nx}x{ny}", flush=True)
+    strips = _macro(w, precision, 3, "0", **SCHEMES[scheme])
+    got = _macro(w, precision, 3, None, **SCHEMES[scheme])
+    assert all(np.array_equal(a, b) for a, b in zip(got, strips))
