@@ -25,9 +25,14 @@ namespace nplbm {
 namespace {
 
 constexpr size_t kChunk = (size_t)1 << 20;  // bytes of one chunk
-// Copies below this go the plain way: starting the threads costs about what
-// they save at 8 MB (22 MB in three copies 1.2 ms against 1.55).
-constexpr size_t kLarge = 8 * kChunk;
+// Copies below this go the plain way.  The threads save time from about 10 MB
+// on (c, u and p in 24 + 10 + 5 MB 1.8 ms against 2.4, 52 + 21 + 10 MB 3.5
+// against 7.3), but afterwards a caller with as many threads of its own as
+// there are cores now and then finds one of them pushed aside: 16 OpenMP
+// threads that convert the frame on 16 cores took 20 ms more in one pass of
+// four, so a 606 000-node solve of 12 ms took 32.  With 168 + 67 + 34 MB the
+// copies take 10.5 against 29 ms and the conversion 8 against 6.7 on average.
+constexpr size_t kLarge = 56 * kChunk;
 constexpr int kMaxThreads = 8;
 
 // The pinned buffers, shared by every domain and server of the process: at

@@ -85,3 +85,27 @@ def test_first_node_in_error(nx, ny):
         d.set_fields(good, u)
     assert np.array_equal(d.get_c(), ref)
     d.close()
+
+
+def test_chunked_readbacks_from_two_threads():
+    """Arrays that several threads move in chunks (c of 59 MiB, the last chunk
+    not full), read by two domains at once, against the initial fields."""
+    bad = []
+
+    def work(i):
+        try:
+            c = _fields(1603, 1600 + i, 3, 20 + i)
+            d = _domain(1603, 1600 + i)
+            d.set_fields(c)
+            for _ in range(3):
+                assert np.max(np.abs(d.get_c() - c)) < 1e-13
+            d.close()
+        except Exception as e:  # surfaced below
+            bad.append(e)
+
+    th = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in th:
+        t.start()
+    for t in th:
+        t.join()
+    assert not bad, bad
