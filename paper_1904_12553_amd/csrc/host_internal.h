@@ -57,10 +57,7 @@ void copy_users(int change);
 size_t first_bad_sum(const double *c, int N, size_t n);
 bool all_finite(const double *v, size_t n);
 
-// default padding of every population plane (64 elements of 4 bytes)
-constexpr size_t kPlanePadBytes = 256;
-int64_t plane_pad(size_t elem);
-// default padding of every row block of the row-interleaved layout
+// default padding of every row block
 constexpr size_t kRowPadBytes = 0;
 int64_t row_pad(size_t elem);
 // elements between the planes of one lattice row (the padded row pitch)

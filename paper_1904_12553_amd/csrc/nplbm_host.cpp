@@ -322,16 +322,7 @@ int derive(const nplbm_params *p, Derived &d) {
 // ------------------------------------------------------------ memory plan
 static size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-// Padding (in elements) appended to every population plane.  Without it the
-// ~10N planes a node touches are a power of two apart for power-of-two
-// lattices and fall onto the same HBM channels.
-int64_t plane_pad(size_t elem) {
-  if (const char *e = std::getenv("NPLBM_PLANE_PAD")) return std::atoll(e);
-  return (int64_t)(kPlanePadBytes / elem);
-}
-
-// Padding (in elements) appended to every row block of the row-interleaved
-// layout.
+// Padding (in elements) appended to every row block.
 int64_t row_pad(size_t elem) {
   if (const char *e = std::getenv("NPLBM_ROW_PAD")) return std::atoll(e);
   return (int64_t)(kRowPadBytes / elem);
@@ -396,18 +387,12 @@ Layout plan_layout(const nplbm_params *p) {
   const size_t n = (size_t)p->nx * nrows;
   // planes per group: CH populations, NS populations k >= 1, previous phi and u
   const int np[3] = {M * (d3 ? 15 : 9), d3 ? 14 : 8, M + (d3 ? 3 : 2)};
-  const char *lay = std::getenv("NPLBM_LAYOUT");
-  const bool soa = lay && std::strcmp(lay, "soa") == 0;
+  // Planes interleaved by row, the one layout the step kernels address: their
+  // buffer resources span row blocks, and a plane beyond the resource reads 0.
   for (int G = 0; G < 3; ++G) {
-    if (soa) {
-      L.ps[G] = (int64_t)L.pitch * nrows + plane_pad(s);
-      L.rs[G] = L.pitch;
-      L.gbytes[G] = (size_t)np[G] * L.ps[G] * s;
-    } else {
-      L.ps[G] = L.pitch;
-      L.rs[G] = (int64_t)np[G] * L.pitch + row_pad(s);
-      L.gbytes[G] = (size_t)nrows * L.rs[G] * s;
-    }
+    L.ps[G] = L.pitch;
+    L.rs[G] = (int64_t)np[G] * L.pitch + row_pad(s);
+    L.gbytes[G] = (size_t)nrows * L.rs[G] * s;
   }
   size_t off = 0;
   auto take = [&](size_t bytes) {

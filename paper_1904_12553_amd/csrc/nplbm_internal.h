@@ -104,8 +104,8 @@ struct DomDesc {
   void *g[2];        // NS populations k = 1..8, [8][ny][pitch], ping-pong
   void *prev[2];     // previous-step phi_i (N-1 planes) and u (2 planes), ping-pong
   // Element (plane p, row y, column x) of group G (0: h, 1: g, 2: prev) is at
-  // base + p * ps[G] + y * rs[G] + x.  The default layout interleaves planes
-  // by row (ps = row pitch, rs = planes x pitch), so the populations one row
+  // base + p * ps[G] + y * rs[G] + x.  Planes are interleaved by
+  // row (ps = row pitch, rs = planes x pitch), so the populations one row
   // of nodes needs are one contiguous block.
   int64_t ps[3], rs[3];
   int32_t nx, ny, pitch, wall;

@@ -1,0 +1,57 @@
+// The part of the HIP runtime's interface that the library's host sources
+// use, declared for a CPU build of them (double.cpp holds the bodies).
+#pragma once
+
+#include <stddef.h>
+#include <stdint.h>
+
+enum hipError_t {
+  hipSuccess = 0,
+  hipErrorInvalidValue = 1,
+  hipErrorOutOfMemory = 2,
+  hipErrorLaunchFailure = 719
+};
+struct ihipStream;
+struct ihipEvent;
+struct ihipGraph;
+typedef ihipStream *hipStream_t;
+typedef ihipEvent *hipEvent_t;
+typedef ihipGraph *hipGraph_t;
+typedef ihipGraph *hipGraphExec_t;
+struct hipDeviceProp_t {
+  int multiProcessorCount;
+};
+enum hipMemcpyKind { hipMemcpyHostToDevice = 1, hipMemcpyDeviceToHost = 2 };
+enum hipStreamCaptureMode { hipStreamCaptureModeThreadLocal = 1 };
+constexpr unsigned hipEventDisableTiming = 2, hipStreamNonBlocking = 1, hipHostMallocPortable = 1;
+
+const char *hipGetErrorString(hipError_t e);
+hipError_t hipGetLastError();
+hipError_t hipGetDevice(int *dev);
+hipError_t hipSetDevice(int dev);
+hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int dev);
+hipError_t hipDeviceSynchronize();
+hipError_t hipMalloc(void **p, size_t bytes);
+template <typename T>
+hipError_t hipMalloc(T **p, size_t bytes) {
+  return hipMalloc(reinterpret_cast<void **>(p), bytes);
+}
+hipError_t hipFree(void *p);
+hipError_t hipHostMalloc(void **p, size_t bytes, unsigned flags);
+hipError_t hipHostFree(void *p);
+hipError_t hipMemcpyAsync(void *dst, const void *src, size_t bytes, hipMemcpyKind kind,
+                          hipStream_t st);
+hipError_t hipStreamCreateWithFlags(hipStream_t *st, unsigned flags);
+hipError_t hipStreamDestroy(hipStream_t st);
+hipError_t hipStreamSynchronize(hipStream_t st);
+hipError_t hipStreamWaitEvent(hipStream_t st, hipEvent_t ev, unsigned flags);
+hipError_t hipEventCreateWithFlags(hipEvent_t *ev, unsigned flags);
+hipError_t hipEventDestroy(hipEvent_t ev);
+hipError_t hipEventRecord(hipEvent_t ev, hipStream_t st);
+hipError_t hipEventSynchronize(hipEvent_t ev);
+hipError_t hipStreamBeginCapture(hipStream_t st, hipStreamCaptureMode mode);
+hipError_t hipStreamEndCapture(hipStream_t st, hipGraph_t *g);
+hipError_t hipGraphInstantiate(hipGraphExec_t *x, hipGraph_t g, void *, char *, size_t);
+hipError_t hipGraphLaunch(hipGraphExec_t x, hipStream_t st);
+hipError_t hipGraphDestroy(hipGraph_t g);
+hipError_t hipGraphExecDestroy(hipGraphExec_t x);
