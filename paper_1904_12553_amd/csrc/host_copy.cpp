@@ -44,6 +44,11 @@ std::mutex g_mu;
 std::vector<void *> g_free;
 int g_made = 0, g_users = 0;
 
+void free_buffer(void *p) {
+  if (hipHostFree(p) != hipSuccess) forget_hip_error();
+  --g_made;
+}
+
 int take_buffers(void **buf, int want) {
   std::lock_guard<std::mutex> lk(g_mu);
   int n = 0;
@@ -53,7 +58,10 @@ int take_buffers(void **buf, int want) {
   }
   while (n < want && g_made < kMaxBuffers) {
     void *p = nullptr;
-    if (hipHostMalloc(&p, kChunk, hipHostMallocPortable) != hipSuccess) break;
+    if (hipHostMalloc(&p, kChunk, hipHostMallocPortable) != hipSuccess) {
+      forget_hip_error();  // fewer buffers, or none, will do
+      break;
+    }
     ++g_made;
     buf[n++] = p;
   }
@@ -63,12 +71,10 @@ int take_buffers(void **buf, int want) {
 void give_buffers(void **buf, int n) {
   std::lock_guard<std::mutex> lk(g_mu);
   for (int i = 0; i < n; ++i)
-    if (g_users > 0) {
+    if (g_users > 0)
       g_free.push_back(buf[i]);
-    } else {
-      (void)hipHostFree(buf[i]);
-      --g_made;
-    }
+    else
+      free_buffer(buf[i]);
 }
 
 // f(thread number) on up to n threads, the caller's among them; fewer where
@@ -96,8 +102,7 @@ void copy_users(int change) {
   std::lock_guard<std::mutex> lk(g_mu);
   g_users += change;
   if (g_users > 0) return;
-  for (void *p : g_free) (void)hipHostFree(p);
-  g_made -= (int)g_free.size();
+  for (void *p : g_free) free_buffer(p);
   g_free.clear();
 }
 

@@ -12,6 +12,7 @@ namespace nplbm {
 
 int fail(int code, const char *fmt, ...);
 int hip_fail(hipError_t e, const char *what);
+void forget_hip_error();
 void clear_error();
 const char *last_error();
 

@@ -225,6 +225,7 @@ int nplbm_create(const nplbm_params *p, void *stream, void *device_mem, size_t d
     void *m = nullptr;
     e = hipMalloc(&m, d->L.total);
     if (e != hipSuccess) {
+      forget_hip_error();
       size_t need = d->L.total;
       delete d;
       return fail(NPLBM_ENOMEM, "hipMalloc(%zu): %s", need, hipGetErrorString(e));

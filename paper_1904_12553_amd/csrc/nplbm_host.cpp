@@ -35,7 +35,13 @@ int fail(int code, const char *fmt, ...) {
 void clear_error() { g_err.clear(); }
 const char *last_error() { return g_err.c_str(); }
 
+// The runtime keeps the error of a failed call until the thread asks for its
+// last error, which every kernel launch does: an error that is reported, or
+// that the library gets by without, must not be found by the next launch.
+void forget_hip_error() { (void)hipGetLastError(); }
+
 int hip_fail(hipError_t e, const char *what) {
+  forget_hip_error();
   return fail(NPLBM_EDEVICE, "%s: %s", what, hipGetErrorString(e));
 }
 

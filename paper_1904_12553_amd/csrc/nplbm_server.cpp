@@ -122,8 +122,10 @@ void release(nplbm_server *s, Req *r) {
 int admit(nplbm_server *s, Req *r) {
   void *m = nullptr;
   hipError_t e = hipMalloc(&m, r->bytes);
-  if (e != hipSuccess)
+  if (e != hipSuccess) {
+    forget_hip_error();
     return fail(NPLBM_ENOMEM, "hipMalloc(%zu): %s", r->bytes, hipGetErrorString(e));
+  }
   r->base = static_cast<unsigned char *>(m);
   s->used += r->bytes;
   int slot = -1;
@@ -397,6 +399,7 @@ int nplbm_server_create(size_t hbm_budget, int32_t max_slots, int32_t quantum, v
   s->slots.assign(max_slots, nullptr);
   hipError_t e = hipMalloc(&s->descs_dev, sizeof(DomDesc) * (size_t)max_slots);
   if (e != hipSuccess) {
+    forget_hip_error();
     delete s;
     return fail(NPLBM_ENOMEM, "descriptor table allocation: %s", hipGetErrorString(e));
   }

@@ -344,6 +344,8 @@ void double_reset() {
   g_threads.clear();
   g_launches.clear();
   g_unsafe = 0;
+  t_last = hipSuccess;
+  (void)hipDeviceSynchronize();
 }
 void *double_stream() {
   hipStream_t st;
