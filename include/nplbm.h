@@ -276,7 +276,10 @@ int nplbm_submit(nplbm_server *s, const nplbm_params *p, const double *c,
                  const double *u, int64_t nsteps, uint64_t *ticket);
 
 /* Admit what fits, run one quantum, retire finished requests.
- * *active_out (may be NULL) = resident domains after the pump. */
+ * *active_out (may be NULL) = resident domains after the pump.  An error
+ * while a quantum is enqueued or runs fails every resident request (state 3),
+ * since some of its steps may have been taken; after an error before that the
+ * requests stay as they were and the next pump goes on. */
 int nplbm_server_pump(nplbm_server *s, int32_t *active_out);
 
 /* *state: 0 queued, 1 resident, 2 done, 3 failed. Thread-safe. */

@@ -379,6 +379,20 @@ int retire(nplbm_server *s, Req *r) {
   return NPLBM_OK;
 }
 
+// Fail every resident request with the error of a quantum that broke off: what
+// was enqueued of it has advanced some domains by an unknown part of the
+// quantum, so none can be continued.  Waits for that work first.
+void abandon(nplbm_server *s, int rc) {
+  for (hipStream_t st : s->side) (void)hipStreamSynchronize(st);
+  (void)hipStreamSynchronize(s->stream);
+  for (size_t i = 0; i < s->slots.size(); ++i)
+    if (Req *r = s->slots[i]) {
+      release(s, r);
+      finish(s, r, rc);
+    }
+  s->dirty = true;
+}
+
 }  // namespace
 
 extern "C" {
@@ -521,10 +535,21 @@ int nplbm_server_pump(nplbm_server *s, int32_t *active_out) {
       if (any) e = launch_progress(s->descs_dev, pr, s->stream);
     }
     if (e != hipSuccess) return hip_fail(e, "progress upload");
-    e = s->graph ? hipGraphLaunch(s->graph, s->stream) : enqueue_quantum(s);
-    if (e != hipSuccess) return hip_fail(e, s->graph ? "hipGraphLaunch" : "step launch");
-    e = hipStreamSynchronize(s->stream);
-    if (e != hipSuccess) return hip_fail(e, "quantum");
+    if (s->graph) {
+      // a graph that was not launched left the state as it was: the next pump
+      // tries again
+      e = hipGraphLaunch(s->graph, s->stream);
+      if (e != hipSuccess) return hip_fail(e, "hipGraphLaunch");
+    } else {
+      e = enqueue_quantum(s);
+    }
+    const char *what = e == hipSuccess ? "quantum" : "step launch";
+    if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
+    if (e != hipSuccess) {
+      const int rc = hip_fail(e, what);
+      abandon(s, rc);
+      return rc;
+    }
     s->node_updates += nodes;
     for (int slot = 0; slot < s->max_slots; ++slot) {
       Req *r = s->slots[slot];
@@ -616,6 +641,7 @@ int nplbm_server_stats(nplbm_server *s, double *p50_s, double *p99_s, double *ml
 
 void nplbm_server_destroy(nplbm_server *s) {
   if (!s) return;
+  for (hipStream_t st : s->side) (void)hipStreamSynchronize(st);
   (void)hipStreamSynchronize(s->stream);
   for (Req *r : s->slots)
     if (r) release(s, r);
