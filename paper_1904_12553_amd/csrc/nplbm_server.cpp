@@ -6,7 +6,8 @@
 // quantum of Q steps in which every resident domain of a given (N,
 // precision, scheme, kernel) group is advanced by the same step kernel launch,
 // driven by a packed strip table over all the group's domains.  Groups that
-// fit the Infinity Cache together run side by side, the others in turn.  The
+// fit the Infinity Cache together run side by side, one such set after the
+// other, and last those of the domains beyond it.  The
 // launches of a quantum are captured into a HIP graph and replayed once a
 // resident set outlasts its first quantum; per-domain progress (which
 // ping-pong buffer is current, how many of the Q sub-steps it still needs) is
@@ -199,30 +200,34 @@ int rebuild(nplbm_server *s) {
     for (int prec : {32, 64})
       for (int N = 2; N <= kMaxN; ++N)
         // one table per kernel: strips (ty = 0) and tiles of each height
-        for (int ty : {0, 4, 8}) {
-          StepGeom geom{};
-          int64_t bytes = 0;
-          auto close = [&]() {
-            if (g.empty()) return;
-            xcd_order(g);
-            s->groups.push_back({N, prec, sch, geom, all.size(), g.size(), bytes, 0});
-            all.insert(all.end(), g.begin(), g.end());
-            g.clear();
-            bytes = 0;
-          };
-          for (int slot = 0; slot < s->max_slots; ++slot) {
-            Req *r = s->slots[slot];
-            if (!r || r->p.N != N || r->p.precision != prec || step_scheme(&r->p) != sch) continue;
-            const StepGeom rg = domain_geom(&r->p, true);
-            if (rg.ty != ty) continue;
-            const int64_t b = 2 * (int64_t)(r->L.gbytes[0] + r->L.gbytes[1] + r->L.gbytes[2]);
-            if (bytes + b > kCacheBytes) close();
-            geom = rg;
-            bytes += b;
-            build_strips(r->p.nx, r->p.ny, slot, rg, g);
+        // of domains whose own state fits the cache, in tables that fit it,
+        // and of all those beyond it, which read HBM whatever runs beside them
+        for (int ty : {0, 4, 8})
+          for (bool fits : {true, false}) {
+            StepGeom geom{};
+            int64_t bytes = 0;
+            auto close = [&]() {
+              if (g.empty()) return;
+              xcd_order(g);
+              s->groups.push_back({N, prec, sch, geom, all.size(), g.size(), bytes, 0});
+              all.insert(all.end(), g.begin(), g.end());
+              g.clear();
+              bytes = 0;
+            };
+            for (int slot = 0; slot < s->max_slots; ++slot) {
+              Req *r = s->slots[slot];
+              if (!r || r->p.N != N || r->p.precision != prec || step_scheme(&r->p) != sch)
+                continue;
+              const StepGeom rg = domain_geom(&r->p, true);
+              const int64_t b = 2 * (int64_t)(r->L.gbytes[0] + r->L.gbytes[1] + r->L.gbytes[2]);
+              if (rg.ty != ty || (b <= kCacheBytes) != fits) continue;
+              if (fits && bytes + b > kCacheBytes) close();
+              geom = rg;
+              bytes += b;
+              build_strips(r->p.nx, r->p.ny, slot, rg, g);
+            }
+            close();
           }
-          close();
-        }
   // the resident set is marked clean only once its tables are on the device:
   // a failed rebuild leaves it dirty, so the next pump tries again
   if (all.empty()) {
@@ -233,9 +238,14 @@ int rebuild(nplbm_server *s) {
   // Infinity Cache together, so the steps of a quantum read them from there;
   // the waves of a quantum run one after the other, each for all its steps
   // (20 FP32 requests of 64..432 a side, 1.0 M nodes and 330 MB: 70 us a
-  // step against 85 with all groups side by side).
+  // step against 85 with all groups side by side).  The groups beyond the
+  // cache run side by side in a last wave, all domains of one kind in one
+  // launch: in launches of their own each domain pays for a last round that
+  // is partly empty (50 steps of six 1152 x 1200 N = 3 FP64 39.2 ms against
+  // 48.1, of three with twelve FP32 of 200 a side 22.9 against 25.9).
   std::vector<int64_t> load;
   for (auto &gr : s->groups) {
+    if (gr.bytes > kCacheBytes) continue;
     size_t w = 0;
     while (w < load.size() && load[w] + gr.bytes > kCacheBytes) ++w;
     if (w == load.size()) load.push_back(0);
@@ -243,6 +253,11 @@ int rebuild(nplbm_server *s) {
     gr.wave = (int)w;
   }
   s->waves = (int)load.size();
+  for (auto &gr : s->groups)
+    if (gr.bytes > kCacheBytes) {
+      gr.wave = (int)load.size();
+      s->waves = gr.wave + 1;
+    }
   if (all.size() > s->strips_cap) {
     if (s->strips_dev) (void)hipFree(s->strips_dev);
     s->strips_dev = nullptr;

@@ -61,3 +61,36 @@ def test_destroyed_with_work_in_flight():
     assert s.pump() == (0, 3) and s.pump() == (0, 3)
     s.close()
     assert s.L.double_unsafe() == 0
+
+
+def test_domains_beyond_the_cache_share_their_launches():
+    """Domains whose state alone exceeds the 256 MB cache (three of 288 MB of
+    one kind, one of another) run in one wave, those of one kind in one
+    launch; those that fit are packed into launches that fit, in waves."""
+    s = H.Server(quantum=2)
+    big = [s.submit(5, 600, 600, 5, 64) for _ in range(3)] + [s.submit(3, 800, 800, 4, 64)]
+    fit = [s.submit(4, 400, 400, 3, 64) for _ in range(3)] + [s.submit(2, 64, 64, 6, 32)]
+    assert s.pump() == (0, 8)
+    rows = [(N, ty, domains) for N, prec, ty, domains, graph, stream in H.launches()]
+    assert rows.count((5, 0, 3)) == 2 and rows.count((3, 0, 1)) == 2
+    assert (5, 0, 1) not in rows
+    # 102 MB each: two in one launch, the third in another
+    assert rows.count((4, 8, 2)) == 2 and rows.count((4, 8, 1)) == 2
+    # the launches beyond the cache come last, on two streams
+    last = H.launches()[-4:]
+    assert {r[0] for r in last} == {3, 5} and len({r[5] for r in last}) == 2
+    _drain(s)
+    assert [s.result(t) for t in big + fit] == [5, 5, 5, 4, 3, 3, 3, 6]
+    s.close()
+    assert s.L.double_unsafe() == 0
+
+
+def test_more_slots_than_one_progress_launch():
+    """Resident requests on both sides of slot 256, of different step counts:
+    each takes its own, over quanta that end in odd and even steps."""
+    s = H.Server(slots=600, quantum=3)
+    steps = [1 + (7 * i) % 11 for i in range(530)]
+    ts = [s.submit(2 + i % 2, 4 + i % 5, 8, n) for i, n in enumerate(steps)]
+    _drain(s)
+    assert [s.result(t) for t in ts] == steps
+    s.close()
