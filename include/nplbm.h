@@ -236,7 +236,9 @@ void nplbm_destroy(nplbm_domain *d);
  * Raw state in the library's storage order, for checkpoint / resume:
  * nplbm_state_bytes gives the size; get copies device -> host, set copies
  * host -> device and restores the time step.  Resuming from a saved state
- * is bitwise identical to an uninterrupted run.  Synchronous.
+ * is bitwise identical to an uninterrupted run, and the bytes depend on the
+ * state alone (rows are padded to 32 values, the padding is zeros).
+ * Synchronous.
  */
 size_t nplbm_state_bytes(const nplbm_domain *d);
 int nplbm_get_state(nplbm_domain *d, void *host, int64_t *time_out);

@@ -34,6 +34,7 @@ inline int dom_nz(const nplbm_params *p) { return p->nz > 1 ? p->nz : 1; }
 struct Layout {
   int pitch = 0;
   int64_t ps[3] = {0, 0, 0}, rs[3] = {0, 0, 0};  // element strides (see DomDesc)
+  int planes[3] = {0, 0, 0};                     // planes of each group
   size_t gbytes[3] = {0, 0, 0};                  // bytes of one copy of each group
   size_t h[2] = {0, 0}, g[2] = {0, 0}, prev[2] = {0, 0}, state_end = 0;
   size_t desc = 0, strips = 0;

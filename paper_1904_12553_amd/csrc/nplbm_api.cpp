@@ -145,6 +145,19 @@ int copy_out(nplbm_domain *d, void *dst, size_t off, size_t bytes) {
   return e == hipSuccess ? NPLBM_OK : hip_fail(e, "device to host copy");
 }
 
+// Zeros in the padding of one saved group: nothing reads it, and what it holds
+// on the device depends on the kernel that stepped the domain.
+void clear_padding(const nplbm_domain *d, int G, unsigned char *o) {
+  const size_t s = d->p.precision == 64 ? 8 : 4;
+  const size_t used = (size_t)d->p.nx * s, plane = (size_t)d->L.ps[G] * s,
+               row = (size_t)d->L.rs[G] * s, end = d->L.planes[G] * plane;
+  if (used == plane && end == row) return;
+  for (unsigned char *y = o; y < o + d->L.gbytes[G]; y += row) {
+    for (size_t p = 0; p < end; p += plane) std::memset(y + p + used, 0, plane - used);
+    std::memset(y + end, 0, row - end);
+  }
+}
+
 bool check_domain(const nplbm_domain *d) { return d != nullptr && d->base != nullptr; }
 
 }  // namespace
@@ -512,6 +525,9 @@ int nplbm_get_state(nplbm_domain *d, void *host, int64_t *time_out) {
   if (e == hipSuccess) e = copy_to_host(o + hb, d->base + d->L.g[par], gb, d->stream);
   if (e == hipSuccess) e = copy_to_host(o + hb + gb, d->base + d->L.prev[par], pb, d->stream);
   if (e != hipSuccess) return hip_fail(e, "state copy");
+  clear_padding(d, 0, o);
+  clear_padding(d, 1, o + hb);
+  clear_padding(d, 2, o + hb + gb);
   if (time_out) *time_out = d->t;
   return NPLBM_OK;
 }

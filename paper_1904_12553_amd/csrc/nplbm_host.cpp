@@ -396,6 +396,7 @@ Layout plan_layout(const nplbm_params *p) {
   // Planes interleaved by row, the one layout the step kernels address: their
   // buffer resources span row blocks, and a plane beyond the resource reads 0.
   for (int G = 0; G < 3; ++G) {
+    L.planes[G] = np[G];
     L.ps[G] = L.pitch;
     L.rs[G] = (int64_t)np[G] * L.pitch + row_pad(s);
     L.gbytes[G] = (size_t)nrows * L.rs[G] * s;

@@ -473,10 +473,16 @@ __global__ void __launch_bounds__(kTW * TY * (kHelp ? 2 : 1)) k_tile(TileArgs a)
              wp = row_rsrc(d.dst[2], rbp * (uint32_t)ny, 0);
   const uint32_t oc = (uint32_t)(x0 + lx) * SZ, yr = (uint32_t)(y0 + ly);
   const uint32_t oh = yr * rbh + oc, og = yr * rbg + oc, op = yr * rbp + oc;
-  // plain stores: the state is read back by the next launch from L2 or MALL
-  auto sg = [&](int plane, Real v) { bst<Real, false>(wg, og, (uint32_t)plane * pb, v); };
-  auto sh = [&](int plane, Real v) { bst<Real, false>(wh, oh, (uint32_t)plane * pb, v); };
-  auto sp = [&](int plane, Real v) { bst<Real, false>(wp, op, (uint32_t)plane * pb, v); };
+  // plain stores: the state is read back by the next launch from L2 or MALL.
+  // Lanes of the padding have pulled nothing, so they store zeros (400 x 200
+  // N = 3 FP64 10.27 us a step against 10.20, 777 x 513 N = 4 Remark 1 60.0
+  // against 60.2).
+  auto put = [&](const Rsrc &w, uint32_t o, int plane, Real v) {
+    bst<Real, false>(w, o, (uint32_t)plane * pb, interior ? v : Real(0));
+  };
+  auto sg = [&](int plane, Real v) { put(wg, og, plane, v); };
+  auto sh = [&](int plane, Real v) { put(wh, oh, plane, v); };
+  auto sp = [&](int plane, Real v) { put(wp, op, plane, v); };
   if (!kSplit || !helper) {
     collide_ns<N, Real, kR1>(KD, phi, G, f, g, sg);
     sp(M, (Real)f.ux);
