@@ -280,10 +280,7 @@ int nplbm_create(const nplbm_params *p, void *stream, void *device_mem, size_t d
   d->d3 = is3d(p);
   if (d->d3) {
     d->ty = step3_ty(N, p->precision, p->nx, p->ny, p->nz);
-    if (d->ty == 0 && !D.c3) {
-      nplbm_destroy(d);
-      return fail(NPLBM_ESTATE, "the step kernel's environment overrides changed during the call");
-    }
+    if (d->ty == 0 && !D.c3) d->ty = step3_march_ty(N, p->precision);
     int target = resident_step3_blocks(N, p->precision, d->ty);
     if (const char *env = std::getenv("NPLBM_TARGET_BLOCKS")) target = std::atoi(env);
     build_tiles3(p->nx, p->ny, p->nz, 0, std::max(d->ty, 4), target, strips);

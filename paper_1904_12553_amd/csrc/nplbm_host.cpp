@@ -425,10 +425,11 @@ Layout plan_layout(const nplbm_params *p) {
   L.p = take(n * 8);
   // 3-D: the phi array written by the phi pass of each step
   L.phi3 = d3 ? take((size_t)nrows * M * L.pitch * s) : 0;
-  // and the C array of the node kernels, where those step the domain
-  L.c3 = d3 && step3_ty(N, p->precision, p->nx, p->ny, p->nz) == 0
-             ? take((size_t)nrows * M * L.pitch * s)
-             : 0;
+  // The C array of the node kernels lives for one step only, between the FP64
+  // planes of one read-back and the next, so it takes their place.  They are
+  // smaller than it only for rows of a few nodes (N = 5 FP64: below 8, padded
+  // to 32); such domains are marched.
+  if (d3 && (size_t)nrows * M * L.pitch * s <= L.phi3 - L.phi) L.c3 = L.phi;
   // the products J~_b u_a of the Remark 1 force, for the read-back
   L.q = p->force_form == 1 ? take(4 * n * 8) : 0;
   L.nblk = diag_blocks((int64_t)n);

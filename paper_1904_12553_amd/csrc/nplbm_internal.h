@@ -123,7 +123,8 @@ struct DomDesc {
   // the phi pass and read by the step pass of the same time step
   int32_t rsf;
   void *phi3;
-  void *c3;  // 3-D: the C_i of the node kernels, laid out as phi3
+  void *c3;  // 3-D: the C_i of the node kernels, laid out as phi3; shares its
+             // memory with the read-back planes
   Consts<double> cd;
   Consts<float> cf;
 };
@@ -224,6 +225,8 @@ int step_blocks_per_cu_remark1(int N, int precision, int bw);
 // How a 3-D (D3Q15) domain is stepped: rows of the marching kernel's tiles
 // (4 or 8, one 64-lane wave each), or 0 for the node kernels.
 int step3_ty(int N, int precision, int nx, int ny, int nz);
+// rows of the marching kernel's tiles where it is taken
+int step3_march_ty(int N, int precision);
 // One 3-D time step by node kernels after the phi pass (step3n_kernel.hip).
 hipError_t launch_step3n(int N, int precision, const StepArgs &s, int nx, int ny, int nz,
                          hipStream_t st);

@@ -533,6 +533,14 @@ int occ3(int precision) {
 
 }  // namespace
 
+// Interior rows of a marching tile = waves of a workgroup: 4 in FP32, where two or
+// more 4-row workgroups per CU measured faster than one of 8 (256^3: N = 3
+// 48.3% against 44.9% of the HBM roofline, N = 5 38.2% against 35.6%); in
+// FP64 8 for N <= 4 (N = 3: 44.9% against 43.9%; N = 4, with the leaner
+// register use of that variant: 45.0% against 40.7%) and 4 for N = 5, where
+// FP64 rings of 8 rows would not fit in LDS.
+int step3_march_ty(int N, int precision) { return precision == 64 && N <= 4 ? 8 : 4; }
+
 // The node kernels (0) take lattices of up to 900 000 nodes, where the
 // marching tiles leave compute units idle, and those whose rows fill less
 // than 77% of the marching kernel's 64-column tiles; the marching kernel the
@@ -541,13 +549,8 @@ int occ3(int precision) {
 // FP64 N = 4 171 / 246; 96^3 FP32 N = 3 100 / 117; 72 x 160^2 FP64 N = 3
 // 461 / 500; 96 x 200^2 FP64 N = 3 836 / 895; 112^3 FP32 N = 3 171 / 166;
 // 128^3 230 / 213; 200^3 (78%) FP32 N = 3 1016 / 952.
-// Interior rows of a marching tile = waves of a workgroup: 4 in FP32, where two or
-// more 4-row workgroups per CU measured faster than one of 8 (256^3: N = 3
-// 48.3% against 44.9% of the HBM roofline, N = 5 38.2% against 35.6%); in
-// FP64 8 for N <= 4 (N = 3: 44.9% against 43.9%; N = 4, with the leaner
-// register use of that variant: 45.0% against 40.7%) and 4 for N = 5, where
-// FP64 rings of 8 rows would not fit in LDS.  NPLBM_TY3 = 0, 4 or 8
-// overrides; NPLBM_TARGET_BLOCKS asks for the marching kernel.
+// NPLBM_TY3 = 0, 4 or 8 overrides; NPLBM_TARGET_BLOCKS asks for the marching
+// kernel.
 int step3_ty(int N, int precision, int nx, int ny, int nz) {
   if (const char *e = std::getenv("NPLBM_TY3")) {
     const int t = std::atoi(e);
@@ -560,7 +563,7 @@ int step3_ty(int N, int precision, int nx, int ny, int nz) {
   if (std::getenv("NPLBM_TARGET_BLOCKS") == nullptr &&
       ((int64_t)nx * ny * nz <= 900000 || nx * 100 < tiles * 77))
     return 0;
-  return precision == 64 && N <= 4 ? 8 : 4;
+  return step3_march_ty(N, precision);
 }
 
 hipError_t launch_step3(int N, int precision, int ty, const StepArgs &a, int nblocks, int nx,

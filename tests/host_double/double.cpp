@@ -330,6 +330,7 @@ int step_blocks_per_cu(int, int, int, int) { return 1; }
 int step3_blocks_per_cu(int, int, int) { return 1; }
 int step_max_bw(int, int, int) { return 256; }
 int step3_ty(int, int, int, int, int) { return 4; }
+int step3_march_ty(int, int) { return 4; }
 
 }  // namespace nplbm
 
