@@ -52,7 +52,8 @@ def kernel_hash():
     whitespace removed), so that the committed counter record is used only
     for the code it was taken on."""
     h = hashlib.sha256()
-    for f in ("step_kernel.hip", "node_math.h", "buffer_io.h", "nplbm_internal.h", "lattice.h"):
+    for f in ("step_kernel.hip", "node_math.h", "relaxation.h", "buffer_io.h", "nplbm_internal.h",
+              "lattice.h"):
         with open(os.path.join(ROOT, "paper_1904_12553_amd", "csrc", f)) as fh:
             src = fh.read()
         src = re.sub(r"/\*.*?\*/", " ", src, flags=re.S)

@@ -16,6 +16,7 @@
 #include "buffer_io.h"
 #include "lattice.h"
 #include "nplbm_internal.h"
+#include "relaxation.h"
 
 namespace nplbm {
 
@@ -163,7 +164,7 @@ struct GradSums {
 
 // Density, force and velocity of a node.
 struct NodeFlow {
-  Acc rho, irho, Fx, Fy, ux, uy;
+  Acc rho, Fx, Fy, ux, uy;
 };
 
 // phi: order parameters; G: the sums above; divx, divy: -div(J~ u) of
@@ -184,14 +185,14 @@ __device__ __forceinline__ NodeFlow flow_node(const NPL_CONST Consts<double> &KD
     f.Fx -= divx;
     f.Fy -= divy;
   }
-  f.irho = Acc(1) / f.rho;
+  const Acc irho = Acc(1) / f.rho;
   Acc g[9];
 #pragma unroll
   for (int k = 1; k < 9; ++k) g[k] = gin[k];
   const Acc mx = (g[1] - g[3]) + (g[5] - g[6]) + (g[8] - g[7]);
   const Acc my = (g[2] - g[4]) + (g[5] + g[6]) - (g[7] + g[8]);
-  f.ux = (mx + Acc(0.5) * f.Fx) * f.irho;  // eq:N22_1
-  f.uy = (my + Acc(0.5) * f.Fy) * f.irho;
+  f.ux = (mx + Acc(0.5) * f.Fx) * irho;  // eq:N22_1
+  f.uy = (my + Acc(0.5) * f.Fy) * irho;
   return f;
 }
 
@@ -201,7 +202,7 @@ __device__ __forceinline__ void collide_ns(const NPL_CONST Consts<double> &KD,
                                            const Real (&phi)[N - 1], const GradSums<Real> &G,
                                            const NodeFlow &f, const Real (&gin)[9], SG sg) {
   constexpr int M = N - 1;
-  const Acc rho = f.rho, irho = f.irho, Fx = f.Fx, Fy = f.Fy, ux = f.ux, uy = f.uy;
+  const Acc rho = f.rho, Fx = f.Fx, Fy = f.Fy, ux = f.ux, uy = f.uy;
   const Acc grx = G.grs, gry = G.gys, Jx = G.Jxs, Jy = G.Jys;
   Acc itau, srcg, theta;
   if (KD.const_tau) {
@@ -212,14 +213,7 @@ __device__ __forceinline__ void collide_ns(const NPL_CONST Consts<double> &KD,
     Acc mu = KD.ma;
 #pragma unroll
     for (int i = 0; i < M; ++i) mu += KD.mA[i] * phi[i];
-    // tau_g = 1/2 + mu / (rho c_s^2)  (eq:N21_1 with nu = mu / rho); its
-    // reciprocal and that of tau_g - 1/2 share one division
-    const Acc tm = Acc(3) * mu * irho;  // tau_g - 1/2
-    const Acc tg = Acc(0.5) + tm;
-    const Acc r = Acc(1) / (tm * tg);
-    itau = tm * r;
-    srcg = Acc(1) - Acc(0.5) * itau;
-    theta = tg * r;
+    ns_relaxation(mu, rho, itau, srcg, theta);
   }
   Acc g[9];
 #pragma unroll

@@ -143,12 +143,7 @@ __device__ __forceinline__ void collide_node3(const NPL_CONST Consts<Real> &K,
     srcg = KD.src_g;
     theta = KD.theta_g;
   } else {
-    const Acc tm = Acc(3) * S.mu * irho;  // tau_g - 1/2 (eq:N21_1)
-    const Acc tg = Acc(0.5) + tm;
-    const Acc r = Acc(1) / (tm * tg);
-    itau = tm * r;
-    srcg = Acc(1) - Acc(0.5) * itau;
-    theta = tg * r;
+    ns_relaxation(S.mu, rho, itau, srcg, theta);
   }
   Acc m[3] = {Acc(0), Acc(0), Acc(0)}, sumg = Acc(0);
 #pragma unroll

@@ -11,6 +11,10 @@ enum hipError_t {
   hipErrorOutOfMemory = 2,
   hipErrorLaunchFailure = 719
 };
+#define __host__
+#define __device__
+#define __forceinline__ inline
+
 struct ihipStream;
 struct ihipEvent;
 struct ihipGraph;
