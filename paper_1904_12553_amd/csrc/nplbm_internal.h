@@ -176,6 +176,21 @@ struct TileArgs {
   TileDom d;
   uint32_t ntx, div, ntile, per;
 };
+// The tile grid of an nx x ny domain with tiles of ty rows; ntx = 0 where its
+// launches take the table instead.  The kernel's t / ntx is the high half of t
+// div, div = 2^32 / ntx + e with e < 1: exact for all t < ntile while ntx ntile
+// < 2^32.  That holds for whatever the host's rule gives tiles (at most 2 GiB
+// of state: 7e8, in 4 rows); one tile column has no 32-bit reciprocal.
+inline void tile_grid(int nx, int ny, int ty, TileArgs &t) {
+  const uint64_t ntx = ((uint64_t)nx + kTileWidth - 1) / kTileWidth,
+                 ntile = ntx * (((uint64_t)ny + ty - 1) / ty);
+  t.ntx = t.div = t.ntile = t.per = 0;
+  if (ntx == 1 || ntx * ntile >> 32) return;
+  t.ntx = (uint32_t)ntx;
+  t.div = (uint32_t)((((uint64_t)1 << 32) + ntx - 1) / ntx);
+  t.ntile = (uint32_t)ntile;
+  t.per = (uint32_t)((ntile + 7) / 8);
+}
 
 // f(std::integral_constant<int, N>) for a validated number of phases
 template <typename F>

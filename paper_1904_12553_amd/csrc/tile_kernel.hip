@@ -598,17 +598,8 @@ hipError_t launch_geom_step(int N, int precision, int scheme, const StepGeom &g,
     t.d.nx = one->nx;
     t.d.ny = one->ny;
     t.d.wall = one->wall;
-    t.ntx = (uint32_t)((one->nx + kTileWidth - 1) / kTileWidth);
-    // t = div * ntile stays below 2^32 for every lattice the host's rule
-    // admits, so the high product is the exact quotient; ntx = 1 has no
-    // 32-bit reciprocal and takes the table
-    t.div = (uint32_t)((((uint64_t)1 << 32) + t.ntx - 1) / t.ntx);
-    t.ntile = t.ntx * (uint32_t)((one->ny + g.ty - 1) / g.ty);
-    t.per = (t.ntile + 7) / 8;
-    if (t.ntx == 1)
-      t.ntx = 0;
-    else
-      nblocks = (int)(t.per * 8);
+    tile_grid(one->nx, one->ny, g.ty, t);
+    if (t.ntx) nblocks = (int)(t.per * 8);
   }
   return launch_tile(N, precision, scheme, g.ty, t, nblocks, st);
 }
