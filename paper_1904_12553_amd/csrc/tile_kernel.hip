@@ -213,15 +213,21 @@ __global__ void __launch_bounds__(kTW * TY * (kHelp ? 2 : 1)) k_tile(TileArgs a)
   };
 
   // ---- stage A: all loads of the step ----
-  // own node; threads up to kHalo beyond a ragged edge bring halo nodes
+  // own node; threads up to kHalo beyond a ragged edge bring halo nodes, those
+  // further right the last of these once more
   const bool active = kSplit || !helper;  // has part in a node's collision
-  const bool own = active && lx < ncol + kHalo && ly < nrow + kHalo;
-  const bool interior = active && lx < ncol && ly < nrow;
+  const bool own = active && ly < nrow + kHalo;
   // Columns past a ragged right end are stored too: they fall into the
   // padding of the row pitch, which nothing reads, and whole lines store
   // faster than parts of one (100 x 96 N = 2 FP32: 5.5 us against 6.5 us).
+  // They collide what they pulled on the last column's phi and C, so that
+  // every value they store is a defined one (against lanes that pull nothing
+  // there: 400 x 200 N = 3 FP64 9.97 -> 10.00 us a step, 128 x 96 N = 2 FP32 3.79
+  // -> 3.84, N = 3 4.99 -> 4.90, 200 x 320 N = 5 mixed 11.80 -> 11.65; zeros
+  // selected at each store: 10.06, 3.79, 5.00, 11.79).
   const bool storing = active && ly < nrow;
-  const int x = own ? col_of(lx) : 0, y = own ? row_of(ly) : 0;
+  const int lc0 = min(lx, ncol - 1);  // column of phi and C at the collision
+  const int x = own ? col_of(min(lx, ncol + kHalo - 1)) : 0, y = own ? row_of(ly) : 0;
   Real h[kPh][9], hi[kPh], g[9], pu[2];
   if (own) {
     uint32_t o[9];
@@ -286,7 +292,7 @@ __global__ void __launch_bounds__(kTW * TY * (kHelp ? 2 : 1)) k_tile(TileArgs a)
   if (halo)
 #pragma unroll
     for (int r = 0; r < kGroup; ++r) load_item(r, hv[r]);
-  if (interior) {
+  if (storing) {
     if (!helper) {
       uint32_t o[9];
       sources(x, y, rbg, o);
@@ -387,7 +393,7 @@ __global__ void __launch_bounds__(kTW * TY * (kHelp ? 2 : 1)) k_tile(TileArgs a)
   Real phi[M], Cv[kKeep ? M : 1];
   GradSums<Real> G{};
   NodeFlow f;
-  int lc = lx;
+  int lc = lc0;
   auto grad = [&](auto at, Real &gx, Real &gy) {
     if constexpr (kTwoHop)
       grad_two_hop<Real>(at, gx, gy);
@@ -419,8 +425,8 @@ __global__ void __launch_bounds__(kTW * TY * (kHelp ? 2 : 1)) k_tile(TileArgs a)
   if (!kSplit || (!helper && storing)) {
 #pragma unroll
     for (int i = 0; i < M; ++i) {
-      phi[i] = sphi[i][ly + kHalo][lx + kHalo];
-      const Real C = sC[i][ly + kRing][lx + kRing];
+      phi[i] = sphi[i][ly + kHalo][lc0 + kHalo];
+      const Real C = sC[i][ly + kRing][lc0 + kRing];
       if constexpr (kKeep) Cv[i] = C;
       in_turn();
       phi_grads(i, C);
@@ -433,7 +439,7 @@ __global__ void __launch_bounds__(kTW * TY * (kHelp ? 2 : 1)) k_tile(TileArgs a)
                 sS = wall && y0 + ly == 0 ? s0 : s0 - 1;
       auto q = [&](int c) {
         return [&, c](int dx, int dy) {
-          return sQ[c][dy == 0 ? s0 : (dy > 0 ? sN : sS)][lx + 1 + dx];
+          return sQ[c][dy == 0 ? s0 : (dy > 0 ? sN : sS)][lc0 + 1 + dx];
         };
       };
       divx = ddx_central(q(0)) + ddy_central(q(1));
@@ -473,16 +479,10 @@ __global__ void __launch_bounds__(kTW * TY * (kHelp ? 2 : 1)) k_tile(TileArgs a)
              wp = row_rsrc(d.dst[2], rbp * (uint32_t)ny, 0);
   const uint32_t oc = (uint32_t)(x0 + lx) * SZ, yr = (uint32_t)(y0 + ly);
   const uint32_t oh = yr * rbh + oc, og = yr * rbg + oc, op = yr * rbp + oc;
-  // plain stores: the state is read back by the next launch from L2 or MALL.
-  // Lanes of the padding have pulled nothing, so they store zeros (400 x 200
-  // N = 3 FP64 10.27 us a step against 10.20, 777 x 513 N = 4 Remark 1 60.0
-  // against 60.2).
-  auto put = [&](const Rsrc &w, uint32_t o, int plane, Real v) {
-    bst<Real, false>(w, o, (uint32_t)plane * pb, interior ? v : Real(0));
-  };
-  auto sg = [&](int plane, Real v) { put(wg, og, plane, v); };
-  auto sh = [&](int plane, Real v) { put(wh, oh, plane, v); };
-  auto sp = [&](int plane, Real v) { put(wp, op, plane, v); };
+  // plain stores: the state is read back by the next launch from L2 or MALL
+  auto sg = [&](int plane, Real v) { bst<Real, false>(wg, og, (uint32_t)plane * pb, v); };
+  auto sh = [&](int plane, Real v) { bst<Real, false>(wh, oh, (uint32_t)plane * pb, v); };
+  auto sp = [&](int plane, Real v) { bst<Real, false>(wp, op, (uint32_t)plane * pb, v); };
   if (!kSplit || !helper) {
     collide_ns<N, Real, kR1>(KD, phi, G, f, g, sg);
     sp(M, (Real)f.ux);
@@ -496,8 +496,8 @@ __global__ void __launch_bounds__(kTW * TY * (kHelp ? 2 : 1)) k_tile(TileArgs a)
         pj = phi[j];
         Cj = Cv[j];
       } else {
-        pj = sphi[ph0 + j][ly + kHalo][lx + kHalo];
-        Cj = sC[ph0 + j][ly + kRing][lx + kRing];
+        pj = sphi[ph0 + j][ly + kHalo][lc0 + kHalo];
+        Cj = sC[ph0 + j][ly + kRing][lc0 + kRing];
       }
       collide_ch<Real>(K, ph0 + j, pj, Cj, f.ux, f.uy, hi[j], pu, h[j], sh, sp);
     }
