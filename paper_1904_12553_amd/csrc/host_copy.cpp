@@ -5,7 +5,7 @@
 // memory, so that thread also takes a page fault every 4 KiB: 268 MB (c, u
 // and p of 2048^2, N = 5) took 30 ms where the link needs 5.  Large copies
 // here are cut into chunks that several threads move: each takes the next
-// chunk, has it copied into a pinned buffer of its own and copies it on (11
+// chunk, has it copied into a pinned buffer of its own and copies it on (14
 // ms).
 #include <hip/hip_runtime.h>
 
@@ -25,13 +25,17 @@ namespace nplbm {
 namespace {
 
 constexpr size_t kChunk = (size_t)1 << 20;  // bytes of one chunk
-// Copies below this go the plain way.  The threads save time from about 10 MB
-// on (c, u and p in 24 + 10 + 5 MB 1.8 ms against 2.4, 52 + 21 + 10 MB 3.5
-// against 7.3), but afterwards a caller with as many threads of its own as
-// there are cores now and then finds one of them pushed aside: 16 OpenMP
-// threads that convert the frame on 16 cores took 20 ms more in one pass of
-// four, so a 606 000-node solve of 12 ms took 32.  With 168 + 67 + 34 MB the
-// copies take 10.5 against 29 ms and the conversion 8 against 6.7 on average.
+// Copies below this go the plain way.  The copy itself gains from 32 MB on, but
+// a caller with as many threads of its own as there are cores now and then
+// finds one of them pushed aside after it, and waits up to 20 ms at its own
+// barrier: any other threads of the process disturb the wake-up of those, also
+// threads that make no runtime call, and it happens (in one pass of a hundred)
+// without them.  The line is where copy and what follows cross: get_c of one
+// array and its conversion by 16 OpenMP threads on 16 cores, mean of 100
+// passes, plain / threads: 24 MB 1.8 - 2.7 / 3.9 - 4.2 ms, 32 MB 4.0 / 4.4 -
+// 4.7, 48 MB 6.0 / 6.3 - 7.0, 64 MB 8.8 - 9.3 / 8.2 - 8.4, 96 MB 14.2 - 14.9 /
+// 11.3 - 12.0.  A frame of 168 + 67 + 34 MB: 35.1 - 35.9 ms / 21.8 - 24.2, the
+// worst of 150 passes 55 - 58 / 44 - 47.
 constexpr size_t kLarge = 56 * kChunk;
 constexpr int kMaxThreads = 8;
 

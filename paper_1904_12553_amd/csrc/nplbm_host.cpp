@@ -490,8 +490,12 @@ StepGeom step_geom(int N, int precision, int scheme) {
 // (1000^2, tile against strips: FP32 N = 6 143 / 127, mixed 157 / 161, N = 7
 // 174 / 174, mixed 187 / 191, N = 8 mixed 216 / 227; 700^2 FP64: N = 6 124 /
 // 117, mixed 130 / 149, Remark 1 135 / 155, N = 8 mixed 200 / 208), with the
-// most further out (1500^2: FP64 N = 8 746 / 866, Remark 1 931 / 1051, FP32
-// Remark 1 483 / 523); eight times keeps every group below 2^31 bytes.
+// most at eight times (1000^2: FP64 N = 8 354 / 391, Remark 1 425 / 480, FP32
+// Remark 1 226 / 253; 1500^2, 1.4 GB, FP32 Remark 1 483 / 523).  The lines are
+// on the safe side of what was measured: in FP64 tiles are faster a little
+// above the cache for fewer phases too (530^2 N = 6, 270 MB, 67 / 80, but 700^2
+// above), and at N = 8 still beyond eight times (1500^2, 2.9 GB, 746 / 866,
+// Remark 1 931 / 1051).
 // Tiles have 8 rows; 4 while that gives each compute unit at most one tile
 // (160 x 200, 250 tiles: N = 2 FP32 4.6 against 5.0 us with 8, N = 5 FP32 7.7
 // against 8.7, N = 8 FP32 10.9 against 12.6, N = 3 FP64 6.4 against 7.5; 256 x
