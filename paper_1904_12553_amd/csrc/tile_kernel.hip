@@ -214,7 +214,9 @@ __global__ void __launch_bounds__(kTW * TY * (kHelp ? 2 : 1)) k_tile(TileArgs a)
 
   // ---- stage A: all loads of the step ----
   // own node; threads up to kHalo beyond a ragged edge bring halo nodes, those
-  // further right the last of these once more
+  // further right the last of these once more.  x and y are a node's for every
+  // thread (rows further up are not pulled), which spares the branches of a
+  // choice (128 x 96 N = 2 FP32 3.78 us a step against 3.84).
   const bool active = kSplit || !helper;  // has part in a node's collision
   const bool own = active && ly < nrow + kHalo;
   // Columns past a ragged right end are stored too: they fall into the
@@ -222,12 +224,12 @@ __global__ void __launch_bounds__(kTW * TY * (kHelp ? 2 : 1)) k_tile(TileArgs a)
   // faster than parts of one (100 x 96 N = 2 FP32: 5.5 us against 6.5 us).
   // They collide what they pulled on the last column's phi and C, so that
   // every value they store is a defined one (against lanes that pull nothing
-  // there: 400 x 200 N = 3 FP64 9.97 -> 10.00 us a step, 128 x 96 N = 2 FP32 3.79
-  // -> 3.84, N = 3 4.99 -> 4.90, 200 x 320 N = 5 mixed 11.80 -> 11.65; zeros
-  // selected at each store: 10.06, 3.79, 5.00, 11.79).
+  // there: 400 x 200 N = 3 FP64 10.04 -> 10.05 us a step, 128 x 96 N = 2 FP32 3.78
+  // -> 3.78, N = 3 4.99 -> 4.89, 200 x 320 N = 5 mixed 11.82 -> 11.60; with zeros
+  // selected at each store 10.12, 3.79, 5.00, 11.79).
   const bool storing = active && ly < nrow;
   const int lc0 = min(lx, ncol - 1);  // column of phi and C at the collision
-  const int x = own ? col_of(min(lx, ncol + kHalo - 1)) : 0, y = own ? row_of(ly) : 0;
+  const int x = col_of(min(lx, ncol + kHalo - 1)), y = row_of(min(ly, nrow + kHalo - 1));
   Real h[kPh][9], hi[kPh], g[9], pu[2];
   if (own) {
     uint32_t o[9];
