@@ -52,7 +52,7 @@ size_t nnodes(const nplbm_domain *d) { return (size_t)d->p.nx * d->p.ny * dom_nz
 hipError_t launch_any_step(nplbm_domain *d, const StepArgs &a) {
   if (d->d3)
     return launch_step3(d->p.N, d->p.precision, d->ty, a, d->nstrips, d->p.nx, d->p.ny, d->p.nz,
-                        d->stream);
+                        d->L.pitch, d->stream);
   return launch_geom_step(d->p.N, d->p.precision, step_scheme(&d->p), d->geom, a, d->nstrips,
                           &d->desc, d->stream);
 }

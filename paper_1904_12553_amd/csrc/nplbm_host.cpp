@@ -426,10 +426,10 @@ Layout plan_layout(const nplbm_params *p) {
   // 3-D: the phi array written by the phi pass of each step
   L.phi3 = d3 ? take((size_t)nrows * M * L.pitch * s) : 0;
   // The C array of the node kernels lives for one step only, between the FP64
-  // planes of one read-back and the next, so it takes their place.  They are
-  // smaller than it only for rows of a few nodes (N = 5 FP64: below 8, padded
-  // to 32); such domains are marched.
-  if (d3 && (size_t)nrows * M * L.pitch * s <= L.phi3 - L.phi) L.c3 = L.phi;
+  // planes of one read-back and the next, so it takes their place.  It fits
+  // there unless NPLBM_PITCH_PAD widens the pitch; such domains are marched.
+  if (d3 && (size_t)nrows * M * node3_stride(p->nx, p->precision, L.pitch) * s <= L.phi3 - L.phi)
+    L.c3 = L.phi;
   // the products J~_b u_a of the Remark 1 force, for the read-back
   L.q = p->force_form == 1 ? take(4 * n * 8) : 0;
   L.nblk = diag_blocks((int64_t)n);

@@ -123,8 +123,8 @@ struct DomDesc {
   // the phi pass and read by the step pass of the same time step
   int32_t rsf;
   void *phi3;
-  void *c3;  // 3-D: the C_i of the node kernels, laid out as phi3; shares its
-             // memory with the read-back planes
+  void *c3;  // 3-D: the C_i of the node kernels, [(z * ny + y)][i][node3_stride];
+             // shares its memory with the read-back planes
   Consts<double> cd;
   Consts<float> cf;
 };
@@ -242,13 +242,29 @@ int step_blocks_per_cu_remark1(int N, int precision, int bw);
 int step3_ty(int N, int precision, int nx, int ny, int nz);
 // rows of the marching kernel's tiles where it is taken
 int step3_march_ty(int N, int precision);
+// Columns of a row in the node kernels: nx rounded up to whole 128-byte lines.
+inline int node3_width(int nx, int precision) {
+  const int line = 128 / (precision / 8);
+  return (nx + line - 1) / line * line;
+}
+// The widest rows of which their workgroups hold two and more, and copy the rows
+// that the stencils read to LDS.
+constexpr int kRows3Width = 128;
+// Elements between the planes of C, and so M times that between its rows: the
+// rows' columns where these are read through LDS, the pitch of phi otherwise
+// (whose offsets then serve both).  The pitch may be twice the columns; only
+// with these does C fit in the place of the read-back planes for every nx >= 4.
+inline int node3_stride(int nx, int precision, int pitch) {
+  const int W = node3_width(nx, precision);
+  return W <= kRows3Width ? W : pitch;
+}
 // One 3-D time step by node kernels after the phi pass (step3n_kernel.hip).
-hipError_t launch_step3n(int N, int precision, const StepArgs &s, int nx, int ny, int nz,
+hipError_t launch_step3n(int N, int precision, const StepArgs &s, int nx, int ny, int nz, int pitch,
                          hipStream_t st);
 // One 3-D time step: the phi pass over all nx * ny * nz nodes of domain 0
 // of a.doms, then the tiled step pass over nblocks tiles.
 hipError_t launch_step3(int N, int precision, int ty, const StepArgs &a, int nblocks, int nx,
-                        int ny, int nz, hipStream_t st);
+                        int ny, int nz, int pitch, hipStream_t st);
 int step3_blocks_per_cu(int N, int precision, int ty);
 // 3-D initialisation and read-back, the counterparts of launch_init /
 // launch_macro below on dense (nz * ny * nx) planes; u has 3 planes.

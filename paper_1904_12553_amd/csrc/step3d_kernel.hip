@@ -567,7 +567,7 @@ int step3_ty(int N, int precision, int nx, int ny, int nz) {
 }
 
 hipError_t launch_step3(int N, int precision, int ty, const StepArgs &a, int nblocks, int nx,
-                        int ny, int nz, hipStream_t st) {
+                        int ny, int nz, int pitch, hipStream_t st) {
   if (nblocks <= 0) return hipSuccess;
   // one block per 64 x 4 row segments of a plane, in a 1-D grid whose
   // size is a multiple of 8 (the phi pass maps block numbers to XCDs)
@@ -583,7 +583,7 @@ hipError_t launch_step3(int N, int precision, int ty, const StepArgs &a, int nbl
     default: return hipErrorInvalidValue;
   }
   if (e != hipSuccess) return e;
-  if (ty == 0) return launch_step3n(N, precision, a, nx, ny, nz, st);
+  if (ty == 0) return launch_step3n(N, precision, a, nx, ny, nz, pitch, st);
   if (ty == 4) {
     switch (N) {
       case 2: return launch3<2, 4>(precision, a, nblocks, st);

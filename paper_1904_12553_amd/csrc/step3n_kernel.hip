@@ -36,6 +36,7 @@ namespace nplbm {
 namespace {
 
 constexpr int kT3n = 256;  // threads of a workgroup
+static_assert(2 * kRows3Width == kT3n, "two rows to a workgroup");
 constexpr int kT3r = 512;  // and of one of k_chem3r
 
 // The node of a thread and how to reach its neighbours.  Blocks are numbered
@@ -148,6 +149,7 @@ __device__ __forceinline__ void copy_rows3(const Rows3<Real> &q, const Rsrc (&r)
 struct Step3nArgs {
   StepArgs s;
   int32_t W, R;
+  int32_t cs;  // node3_stride
   uint32_t nblk, per_plane;
 };
 
@@ -168,14 +170,15 @@ __global__ void __launch_bounds__(kT3r) k_chem3r(Step3nArgs a) {
   copy_rows3<N - 1, Real>(q, r, rbf, pb, ny, W, R, s);
   __syncthreads();
   if (!q.use || q.n.y >= ny) return;
-  const Rsrc w = row_rsrc(D->c3, plf, q.n.z);
-  const uint32_t ow = (uint32_t)q.n.y * rbf + q.n.own;
+  const uint32_t pbc = (uint32_t)a.cs * SZ, rbc = (N - 1) * pbc;
+  const Rsrc w = row_rsrc(D->c3, (uint32_t)ny * rbc, q.n.z);
+  const uint32_t ow = (uint32_t)q.n.y * rbc + q.n.own;
   chem_node3<N, Real>(
       K,
       [&](int i, int dx, int dy, int dz) {
         return s[((i * 3 + dz + 1) * (R + 2) + q.ly + 1 + dy) * W + q.cx[dx + 1]];
       },
-      [&](int i, Real v) { bst<Real, false>(w, ow, (uint32_t)i * pb, v); });
+      [&](int i, Real v) { bst<Real, false>(w, ow, (uint32_t)i * pbc, v); });
 }
 
 template <int N, typename Real>
@@ -240,10 +243,11 @@ __global__ void __launch_bounds__(kT3n) k_step3n(Step3nArgs a) {
   if constexpr (kRows) {
     const Rsrc rf[3] = {row_rsrc(D->phi3, plf, n.pz[0]), row_rsrc(D->phi3, plf, n.pz[1]),
                         row_rsrc(D->phi3, plf, n.pz[2])};
-    const Rsrc rc[3] = {row_rsrc(D->c3, plf, n.pz[0]), row_rsrc(D->c3, plf, n.pz[1]),
-                        row_rsrc(D->c3, plf, n.pz[2])};
+    const uint32_t pbc = (uint32_t)a.cs * SZ, rbc = M * pbc, plc = (uint32_t)ny * rbc;
+    const Rsrc rc[3] = {row_rsrc(D->c3, plc, n.pz[0]), row_rsrc(D->c3, plc, n.pz[1]),
+                        row_rsrc(D->c3, plc, n.pz[2])};
     copy_rows3<M, Real>(q, rf, rbf, pb, ny, a.W, a.R, sf);
-    copy_rows3<M, Real>(q, rc, rbf, pb, ny, a.W, a.R, sc);
+    copy_rows3<M, Real>(q, rc, rbc, pbc, ny, a.W, a.R, sc);
     __syncthreads();
     if (!q.use || n.y >= ny) return;
   }
@@ -352,7 +356,7 @@ hipError_t launch3n(Step3nArgs a, bool cached, int ny, int nz, hipStream_t st) {
     return (b.R * b.W + 63) / 64 * 64;
   };
   // whole rows while two and more of them are a workgroup of kT3n threads
-  if (a.W <= kT3n / 2) {
+  if (a.W <= kRows3Width) {
     const int tc = rows(kT3r);
     hipLaunchKernelGGL((k_chem3r<N, Real>), dim3((b.nblk + 7) / 8 * 8), dim3(tc),
                        row * (b.R + 2), st, b);
@@ -367,12 +371,12 @@ hipError_t launch3n(Step3nArgs a, bool cached, int ny, int nz, hipStream_t st) {
 
 }  // namespace
 
-hipError_t launch_step3n(int N, int precision, const StepArgs &s, int nx, int ny, int nz,
+hipError_t launch_step3n(int N, int precision, const StepArgs &s, int nx, int ny, int nz, int pitch,
                          hipStream_t st) {
   Step3nArgs a{};
   a.s = s;
-  const int line = 128 / (precision / 8);
-  a.W = (nx + line - 1) / line * line;
+  a.W = node3_width(nx, precision);
+  a.cs = node3_stride(nx, precision, pitch);
   const int64_t per = ((int64_t)a.W * ny + kT3n - 1) / kT3n;
   if (per * nz > (int64_t)1 << 30) return hipErrorInvalidValue;
   a.per_plane = (uint32_t)per;

@@ -19,7 +19,7 @@
 #include <thread>
 #include <vector>
 
-#include "nplbm_internal.h"
+#include "host_internal.h"
 
 struct ihipGraph {
   std::vector<std::function<void()>> ops;
@@ -262,7 +262,7 @@ hipError_t launch_geom_step(int N, int precision, int scheme, const StepGeom &g,
   });
   return launched();
 }
-hipError_t launch_step3(int, int, int, const StepArgs &a, int, int, int, int, hipStream_t st) {
+hipError_t launch_step3(int, int, int, const StepArgs &a, int, int, int, int, int, hipStream_t st) {
   ENTER("launch_step3");
   work(st, [=] { advance(*a.doms, a.substep); });
   return launched();
@@ -357,6 +357,8 @@ int double_threads() { return (int)g_threads.size(); }
 // memory freed or streams destroyed while a stream had work that nothing waited for
 int64_t double_unsafe() { return g_unsafe; }
 int64_t double_pinned() { return g_live_host; }
+// whether the plan of a 3-D domain has room for the node kernels' array of C
+int double_node_array(const nplbm_params *p) { return nplbm::plan_layout(p).c3 != 0; }
 int double_launches() { return (int)g_launches.size(); }
 // launch i: N, precision, tile rows (0: strips), domains, from a graph, stream
 void double_launch(int i, int64_t *out) {

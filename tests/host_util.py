@@ -49,7 +49,7 @@ def lib():
                 ("double_calls", [ctypes.c_char_p], i64), ("double_reset", [], None),
                 ("double_stream", [], vp), ("double_threads", [], ctypes.c_int),
                 ("double_unsafe", [], i64), ("double_pinned", [], i64),
-                ("double_launches", [], ctypes.c_int),
+                ("double_launches", [], ctypes.c_int), ("double_node_array", [vp], ctypes.c_int),
                 ("double_launch", [ctypes.c_int, vp], None)):
             f = getattr(_LIB, name)
             f.argtypes, f.restype = args, res

@@ -1,6 +1,8 @@
 """The C array of the 3-D node kernels takes the place of the read-back planes:
 a domain needs no more memory with them than with the marching kernel, and
 read-backs between steps change nothing."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -21,6 +23,16 @@ def test_footprint_does_not_depend_on_the_kernel(N, nx, ny, nz, bits, monkeypatc
             monkeypatch.setenv("NPLBM_TY3", ty)
         sizes.add(P.footprint(**kw))
     assert len(sizes) == 1 and sizes.pop() > 0
+
+
+def test_the_array_fits_for_every_row_length():
+    import host_util as H
+    L = H.lib()
+    for nx in list(range(4, 70)) + [112, 113, 127, 128, 129, 224, 225, 256, 1000]:
+        for N in (2, 3, 4, 5):
+            for bits in (32, 64):
+                p, keep = H.params(N, nx, 9, bits, nz=5)
+                assert L.double_node_array(ctypes.addressof(p)), (nx, N, bits)
 
 
 @pytest.mark.gpu
