@@ -342,7 +342,10 @@ __global__ void __launch_bounds__(k3W * TY) k_step3(StepArgs a) {
     Sums3<Real> S = sums3_begin<N, Real>(KD);
 #pragma unroll
     for (int i = 0; i < M; ++i) {
-      sums3_order(ln, S);
+      // (not with kLean, whose stencils leave registers enough: 192^3 N = 4
+      // FP64 2050 us a step with it, 2031 without; N = 5 FP64 2878 / 2916,
+      // FP32 1257 / 1264)
+      if constexpr (!kLean) sums3_order(ln, S);
       phi[i] = sphi[s0][i][pr][ln];
       Cv[i] = sC[c0][i][cr][ln];
       Real gp[3], gc[3];
