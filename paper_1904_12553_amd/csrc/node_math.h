@@ -164,7 +164,7 @@ struct GradSums {
 
 // Density, force and velocity of a node.
 struct NodeFlow {
-  Acc rho, Fx, Fy, ux, uy;
+  Acc rho, irho, Fx, Fy, ux, uy;
 };
 
 // phi: order parameters; G: the sums above; divx, divy: -div(J~ u) of
@@ -185,14 +185,14 @@ __device__ __forceinline__ NodeFlow flow_node(const NPL_CONST Consts<double> &KD
     f.Fx -= divx;
     f.Fy -= divy;
   }
-  const Acc irho = Acc(1) / f.rho;
+  f.irho = Acc(1) / f.rho;
   Acc g[9];
 #pragma unroll
   for (int k = 1; k < 9; ++k) g[k] = gin[k];
   const Acc mx = (g[1] - g[3]) + (g[5] - g[6]) + (g[8] - g[7]);
   const Acc my = (g[2] - g[4]) + (g[5] + g[6]) - (g[7] + g[8]);
-  f.ux = (mx + Acc(0.5) * f.Fx) * irho;  // eq:N22_1
-  f.uy = (my + Acc(0.5) * f.Fy) * irho;
+  f.ux = (mx + Acc(0.5) * f.Fx) * f.irho;  // eq:N22_1
+  f.uy = (my + Acc(0.5) * f.Fy) * f.irho;
   return f;
 }
 
@@ -213,7 +213,7 @@ __device__ __forceinline__ void collide_ns(const NPL_CONST Consts<double> &KD,
     Acc mu = KD.ma;
 #pragma unroll
     for (int i = 0; i < M; ++i) mu += KD.mA[i] * phi[i];
-    ns_relaxation(mu, rho, itau, srcg, theta);
+    ns_relaxation(mu, rho, f.irho, itau, srcg, theta);
   }
   Acc g[9];
 #pragma unroll

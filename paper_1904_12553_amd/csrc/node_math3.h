@@ -143,7 +143,7 @@ __device__ __forceinline__ void collide_node3(const NPL_CONST Consts<Real> &K,
     srcg = KD.src_g;
     theta = KD.theta_g;
   } else {
-    ns_relaxation(S.mu, rho, itau, srcg, theta);
+    ns_relaxation(S.mu, rho, irho, itau, srcg, theta);
   }
   Acc m[3] = {Acc(0), Acc(0), Acc(0)}, sumg = Acc(0);
 #pragma unroll

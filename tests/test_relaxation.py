@@ -23,7 +23,7 @@ int main() {
     const double rho = std::exp(U(g) * 7 - 3), mu = rho * std::pow(10.0, 5 * U(g) - 4);
     const long double tm = 3.0L * mu / rho, it = 1 / (0.5L + tm), th = 1 / tm;
     double itau, srcg, theta;
-    nplbm::ns_relaxation(mu, rho, itau, srcg, theta);
+    nplbm::ns_relaxation(mu, rho, 1.0 / rho, itau, srcg, theta);
     w[0] = std::max(w[0], (double)(fabsl(itau - it) / (it * u)));
     w[1] = std::max(w[1], (double)(fabsl(srcg - (1 - 0.5L * it)) / ((2 * it + 1) * u)));
     w[2] = std::max(w[2], (double)(fabsl(theta - th) / (th * u)));
